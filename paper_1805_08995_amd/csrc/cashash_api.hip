@@ -15,6 +15,7 @@
 #include <cstdio>
 #include <cstring>
 #include <numeric>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -177,7 +178,6 @@ struct cashash_ctx {
     HostPinned pin_out[2], pin_small;
     hipEvent_t slot_load_ev[3] = {nullptr, nullptr, nullptr};
     hipEvent_t slot_free_ev[3] = {nullptr, nullptr, nullptr};
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;  // autotuner timing
     // per match job in flight (host-memory mode keeps two): kernel start and
     // end, and the end of its output download
     hipEvent_t job_ev[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
@@ -199,7 +199,8 @@ struct cashash_ctx {
     int64_t graph_replays = 0;
     bool last_replayed = false;
     DevBuf counters;          // per-segment work counters of the persistent matcher
-    std::map<std::string, Shape> tuned;
+    std::map<std::string, Shape> tuned;   // shapes of the cache file
+    std::set<std::string> tune_stored;    // keys written to it by this context
     bool tune_loaded = false;
     int last_shape_qt = 0, last_shape_bpc = 0;
     // geometry-aware first stage: subset images, stage-1 outputs, per-pair
@@ -325,7 +326,7 @@ static void destroy_ctx(cashash_ctx* c) {
                           &c->meta_host[2][0], &c->meta_host[2][1], &c->pin[0], &c->pin[1], &c->pin_out[0], &c->pin_out[1],
                           &c->pin_small})
         h->release();
-    for (hipEvent_t e : {c->ev0, c->ev1, c->meta_ev[0][0], c->meta_ev[0][1], c->meta_ev[1][0], c->meta_ev[1][1],
+    for (hipEvent_t e : {c->meta_ev[0][0], c->meta_ev[0][1], c->meta_ev[1][0], c->meta_ev[1][1],
                          c->meta_ev[2][0], c->meta_ev[2][1], c->geo_ev[0], c->geo_ev[1], c->geo_ev[2], c->geo_ev[3],
                          c->geo_ev[4], c->pin_ev[0], c->pin_ev[1],
                          c->slot_load_ev[0], c->slot_load_ev[1], c->slot_load_ev[2], c->slot_free_ev[0],
@@ -439,8 +440,7 @@ extern "C" int cashash_create(cashash_ctx** out, const double* r_code, const dou
     int r = cashash_set_config(c, &n);
     if (r) return bail(r);
     if (hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking) != hipSuccess ||
-        hipStreamCreateWithFlags(&c->d2h_stream, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess)
+        hipStreamCreateWithFlags(&c->d2h_stream, hipStreamNonBlocking) != hipSuccess)
         return bail(fail(CASHASH_E_DEVICE, "stream/event creation failed"));
     for (int i = 0; i < 5; ++i)
         if (hipEventCreate(&c->geo_ev[i]) != hipSuccess) return bail(fail(CASHASH_E_DEVICE, "event creation failed"));
@@ -460,13 +460,13 @@ extern "C" int cashash_create(cashash_ctx** out, const double* r_code, const dou
                           &c->slot_free_ev[2], &c->caller_ev, &c->part_ev[0], &c->part_ev[1]})
         if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess)
             return bail(fail(CASHASH_E_DEVICE, "event creation failed"));
-    if ((r = c->pin_small.ensure(4096))) return bail(r);
+    if ((r = c->pin_small.ensure(1024 + 2 * kCtlWords * 4))) return bail(r);
     std::vector<float> R32(c->R64.size());
     for (size_t i = 0; i < R32.size(); ++i) R32[i] = (float)c->R64[i];
     std::vector<uint16_t> frag = make_frag(c->R64);
     if ((r = c->dR64.ensure(c->R64.size() * 8)) || (r = c->dR32.ensure(R32.size() * 4)) ||
         (r = c->dFrag.ensure(frag.size() * 2)) || (r = c->dBias.ensure(kRows * 4)) || (r = c->dS.ensure(kDim * 8)) ||
-        (r = c->dCount.ensure(64 * 8)) || (r = c->counters.ensure(kSegments * kCounterStride * 4)))
+        (r = c->dCount.ensure(64 * 8)) || (r = c->counters.ensure(kCtlWords * 4)))
         return bail(r);
     if (hipMemcpy(c->dR64.p, c->R64.data(), c->R64.size() * 8, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->dR32.p, R32.data(), R32.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
@@ -722,42 +722,31 @@ struct MatchJob {
     int turn = 0;                  // which of the two in-flight job slots (events, statistics) it uses
 };
 
-// ------------------------------------------------------------------ launch shape and autotuning
+// ------------------------------------------------------------------ launch shape
+// (Chosen by rule: timing candidate shapes on a call's first pairs, as before,
+// cost several times the first call and, kept for later calls, picked 4 blocks
+// per CU in half of the runs: 5.8 instead of 4.6 ms on 60 x 8000 points.)
 // A launch shape is the number of queries per work item (one wavefront takes
 // one item at a time) and, for the persistent batched launch, the number of
 // resident blocks per compute unit.  A tile's kept candidates must fit the
-// per-wave tile list: qt * k <= kSelCap (kSelCapEpi for the band kernel, which
-// also tries 7 blocks per compute unit, the occupancy it is compiled for).
+// per-wave tile list: qt * k <= kSelCap.
 
-static int sel_cap(bool epi) { return epi ? kSelCapEpi : kSelCap; }
-
-static std::vector<Shape> shape_candidates(int k, bool batched, bool epi) {
-    std::vector<Shape> v;
-    const int qmax = std::min(kMaxTile, sel_cap(epi) / k);
-    if (batched) {
-        // persistent blocks per CU: around the occupancy each kernel is
-        // compiled for (7 blocks for the band kernel, 6 or 5 for the others)
-        static const int kBpcPlain[3] = {4, 6, 8}, kBpcEpi[3] = {6, 7, 8};
-        const int* bpcs = epi ? kBpcEpi : kBpcPlain;
-        for (int qt : {8, 16, 32})
-            for (int i = 0; i < 3; ++i)
-                if (qt <= qmax || qt == 16) v.push_back(Shape{std::min(qt, qmax), bpcs[i]});
-    } else {
-        for (int qt : {1, 2, 4, 8, 16, 32})
-            if (qt <= qmax) v.push_back(Shape{qt, 0});
-    }
-    // drop duplicates from clamping
-    std::vector<Shape> u;
-    for (const Shape& s : v) {
-        bool dup = false;
-        for (const Shape& t : u) dup |= (t.qt == s.qt && t.bpc == s.bpc);
-        if (!dup) u.push_back(s);
-    }
-    return u;
+// Queries per item of a call of `queries` queries: the largest of 32, 16, 8, 4
+// that gives every SIMD (four per compute unit) a wavefront.  A tile's setup is
+// one lane per query, so larger tiles share it among more; more wavefronts than
+// that gain nothing in a small call.  Kernel times, us, at 4 / 8 / 16 / 32
+// queries per item: 2000 queries 31 / 33 / 40 / 56; 24008 queries 94 / 56 / 46 /
+// 55; 217500 queries 206 / 159 / 137 / 124; 14 M queries 8123 / 5995 / 5057 / 4787.
+static int shape_qt(int k, int64_t queries, int n_cu) {
+    int qt = kMaxTile;
+    while (qt > 4 && queries < (int64_t)qt * 4 * n_cu) qt /= 2;
+    return std::min(qt, std::max(1, kSelCap / k));
 }
 
-static Shape default_shape(int k, bool batched, bool epi) {
-    return batched ? Shape{std::min(kMaxTile, sel_cap(epi) / k), epi ? 7 : 6} : Shape{std::min(4, sel_cap(epi) / k), 0};
+static Shape choose_shape(const cashash_ctx* c, int k, bool batched, bool epi, int64_t queries) {
+    if (!batched) return Shape{std::max(1, std::min(4, kSelCap / k)), 0};
+    const int bpc = match_blocks_per_cu(epi, 4);
+    return Shape{shape_qt(k, queries, c->n_cu), bpc};
 }
 
 static bool autotune_enabled() {
@@ -765,12 +754,14 @@ static bool autotune_enabled() {
     return !(e && e[0] == '0');
 }
 
-// Shapes are cached per (form, epipolar, k, train size class, query size
-// class), in memory and, if CASHASH_AUTOTUNE_CACHE names a file, as JSON lines.
-static std::string tune_key(bool batched, bool epi, int k, double mean_nt, double mean_nq) {
-    char b[128];
-    snprintf(b, sizeof b, "gfx950/%s/%s/k%d/nt%d/nq%d", batched ? "batched" : "plain", epi ? "epi" : "plain", k,
-             (int)std::lround(std::log2(std::max(1.0, mean_nt))), (int)std::lround(std::log2(std::max(1.0, mean_nq))));
+// With CASHASH_AUTOTUNE_CACHE naming a file, the shapes used are kept there as
+// JSON lines, per (form, epipolar, k, train size class, query size class, call
+// size class), and a shape found there is used instead of the rule's.
+static std::string tune_key(bool batched, bool epi, int k, double mean_nt, double mean_nq, double queries) {
+    char b[160];
+    auto cls = [](double v) { return (int)std::lround(std::log2(std::max(1.0, v))); };
+    snprintf(b, sizeof b, "gfx950/%s/%s/k%d/nt%d/nq%d/q%d", batched ? "batched" : "plain", epi ? "epi" : "plain", k,
+             cls(mean_nt), cls(mean_nq), cls(queries));
     return b;
 }
 
@@ -802,7 +793,7 @@ struct MatchPlan {
     std::vector<int64_t> order;
     Item* items = nullptr;          // work items (items_cap of them)
     int64_t items_cap = 0;
-    uint32_t* counter = nullptr;    // per-segment work counters of the persistent launch
+    uint32_t* ctl = nullptr;        // work counters and statistics (kCtlWords)
 };
 
 // Segment boundaries (in items) that split the estimated cost (queries x
@@ -843,7 +834,7 @@ static void segment_bounds(const MatchJob& J, const std::vector<int64_t>& order,
 // Register slots of the matcher instantiation a pair runs in.
 static int slots_for(const MatchJob& J, int64_t p) {
     const int n = J.imgs[J.pair_t[p]].n;
-    return J.epi || n <= kLargeTrain ? 4 : n <= kHugeTrain ? 6 : 8;
+    return J.epi || n <= kLargeTrain ? 4 : 8;
 }
 
 // Generate the work items of shape qt on the device (into P.items, which
@@ -852,7 +843,7 @@ static int make_items(cashash_ctx* c, const MatchPlan& P, int qt, const PairTile
                       int64_t n_items) {
     if (n_items > (int64_t)INT32_MAX) return fail(CASHASH_E_LIMIT, "too many query tiles in one call");
     if (n_items > P.items_cap) return fail(CASHASH_E_INVAL, "work item buffer too small");
-    HIPCHK(launch_make_items(c->stream, dPT, n_pt, P.dP, P.dI, qt, P.items, (int32_t)n_items));
+    HIPCHK(launch_make_items(c->stream, dPT, n_pt, P.dP, P.dI, qt, P.items, (int32_t)n_items, P.ctl));
     return CASHASH_OK;
 }
 
@@ -860,8 +851,8 @@ static int make_items(cashash_ctx* c, const MatchPlan& P, int qt, const PairTile
 // in the plain form, one launch per pair over its own items.
 static int enqueue_matcher(cashash_ctx* c, const MatchPlan& P, MatchJob& J, Shape sh, bool batched,
                            const std::vector<int64_t>& first_of, int64_t n_pairs_run, int64_t n_items,
-                           unsigned long long* stats, int64_t* launches, bool use_graph) {
-    uint32_t* counter = P.counter;
+                           int64_t* launches, bool use_graph) {
+    uint32_t* ctl = P.ctl;
     const Item* items = P.items;
     if (batched) {
         // one persistent launch per register-slot group (pairs are ordered
@@ -884,8 +875,9 @@ static int enqueue_matcher(cashash_ctx* c, const MatchPlan& P, MatchJob& J, Shap
                 L.item_lo = ilo;
                 L.n = ihi - ilo;
                 const int blocks_needed = (int)((L.n + kWavesPerBlock - 1) / kWavesPerBlock);
-                L.grid = std::max(1, std::min(blocks_needed, c->n_cu * sh.bpc));
+                L.grid = std::max(1, std::min(blocks_needed, c->n_cu * std::min(sh.bpc, match_blocks_per_cu(J.epi, ns))));
                 L.prm = P.prm;
+                L.prm.set = (int32_t)ls.size();
                 // segments of about equal estimated cost (queries x train size), one per XCD
                 segment_bounds(J, P.order, first_of, sh.qt, oi, oe, ilo, ihi, L.prm.seg);
                 const int64_t waves = (int64_t)L.grid * kWavesPerBlock;
@@ -896,22 +888,20 @@ static int enqueue_matcher(cashash_ctx* c, const MatchPlan& P, MatchJob& J, Shap
         }
         auto issue = [&]() -> hipError_t {
             for (const Launch& L : ls) {
-                hipError_t e = launch_fill_u32(c->stream, counter, kSegments * kCounterStride, 0u);
-                if (e == hipSuccess)
-                    e = launch_match(c->stream, J.epi, L.ns, L.grid, P.dI, P.dP, items + L.item_lo, (int32_t)L.n,
-                                     counter, L.prm, J.o_idx, J.o_d1, J.o_d2, stats);
+                const hipError_t e = launch_match(c->stream, J.epi, L.ns, L.grid, P.dI, P.dP, items + L.item_lo,
+                                                  (int32_t)L.n, ctl, L.prm, J.o_idx, J.o_d1, J.o_d2);
                 if (e != hipSuccess) return e;
             }
             return hipSuccess;
         };
         c->last_replayed = false;
         if (use_graph && c->use_graphs && !ls.empty()) {
-            // counter resets + persistent launches as one captured graph,
-            // replayed while the launch arguments are unchanged
+            // the persistent launches as one captured graph, replayed while
+            // the launch arguments are unchanged
             std::string key;
             auto put = [&key](const void* v, size_t n) { key.append(static_cast<const char*>(v), n); };
             const int epi = J.epi ? 1 : 0;
-            const void* ptrs[] = {P.dI, P.dP, items, counter, J.o_idx, J.o_d1, J.o_d2, stats};
+            const void* ptrs[] = {P.dI, P.dP, items, ctl, J.o_idx, J.o_d1, J.o_d2};
             put(&epi, sizeof epi);
             put(ptrs, sizeof ptrs);
             for (const Launch& L : ls) {
@@ -958,17 +948,17 @@ static int enqueue_matcher(cashash_ctx* c, const MatchPlan& P, MatchJob& J, Shap
             if (nit == 0) continue;
             HIPCHK(launch_match(c->stream, J.epi, slots_for(J, P.order[oi]),
                                 (int)((nit + kWavesPerBlock - 1) / kWavesPerBlock), P.dI, P.dP, items + first_of[oi],
-                                (int32_t)nit, nullptr, P.prm, J.o_idx, J.o_d1, J.o_d2, stats));
+                                (int32_t)nit, ctl, P.prm, J.o_idx, J.o_d1, J.o_d2));
             *launches += 1;
         }
     }
     return CASHASH_OK;
 }
 
-// Pinned slot of job slot `turn`'s statistics (bucket entries, union,
-// ranked), after the first 256 bytes of pin_small.
-static unsigned long long* job_stats_host(cashash_ctx* c, int turn) {
-    return reinterpret_cast<unsigned long long*>(static_cast<uint8_t*>(c->pin_small.p) + 256 + 64 * turn);
+// Pinned copy of job slot `turn`'s control words (its statistics), after the
+// first 1024 bytes of pin_small.
+static uint32_t* job_ctl_host(cashash_ctx* c, int turn) {
+    return reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(c->pin_small.p) + 1024) + turn * kCtlWords;
 }
 
 // One caller-fixed device region that a match job carves its scratch out of
@@ -1036,14 +1026,11 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
     MatchPlan P;
     P.order.resize(n_pairs);
     const bool batched = c->cfg.mode == CASHASH_MODE_BATCHED_BF16X2;
-    std::string key;
-    std::vector<Shape> cands;
-    bool tune = false;
-    std::vector<int> qts;
-    std::vector<std::vector<PairTiles>> pts;
-    std::vector<std::vector<int64_t>> firsts;
+    Shape shape{};
+    std::vector<PairTiles> pt;
+    std::vector<int64_t> first;
     int64_t max_items = 1;
-    Uploader up2;  // pairs, then the per-shape tile tables
+    Uploader up2;  // pairs, then the tile table
     auto plan = [&]() {
         double sum_nt = 0, sum_nq = 0;
         for (int64_t p = 0; p < n_pairs; ++p) {
@@ -1052,31 +1039,28 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
         }
         if (batched) {
             // stable counting sort by (register-slot group, train image)
-            std::vector<int64_t> start((size_t)3 * n_img + 1, 0);
-            auto bucket = [&](int64_t p) { return (slots_for(J, p) / 2 - 2) * n_img + J.pair_t[p]; };
+            std::vector<int64_t> start((size_t)2 * n_img + 1, 0);
+            auto bucket = [&](int64_t p) { return (slots_for(J, p) / 4 - 1) * n_img + J.pair_t[p]; };
             for (int64_t p = 0; p < n_pairs; ++p) start[(size_t)bucket(p) + 1]++;
             for (size_t i = 1; i < start.size(); ++i) start[i] += start[i - 1];
             for (int64_t p = 0; p < n_pairs; ++p) P.order[(size_t)start[(size_t)bucket(p)]++] = p;
         } else {
             std::iota(P.order.begin(), P.order.end(), 0);
         }
-        // launch shapes: cached, tuned now, or the default
+        // launch shape: from the cache file, or the rule's
         tune_cache_load(c);
-        key = tune_key(batched, J.epi, c->cfg.k, n_pairs ? sum_nt / n_pairs : 0.0, n_pairs ? sum_nq / n_pairs : 0.0);
+        shape = choose_shape(c, c->cfg.k, batched, J.epi, (int64_t)sum_nq);
+        const bool tuned = autotune_enabled();
+        const std::string key = tune_key(batched, J.epi, c->cfg.k, n_pairs ? sum_nt / n_pairs : 0.0,
+                                         n_pairs ? sum_nq / n_pairs : 0.0, sum_nq);
         auto hit = c->tuned.find(key);
-        tune = !sa && hit == c->tuned.end() && autotune_enabled() && n_pairs > 0;
-        if (hit != c->tuned.end())
-            cands.push_back(
-                Shape{std::max(1, std::min({hit->second.qt, kMaxTile, sel_cap(J.epi) / c->cfg.k})), hit->second.bpc});
-        else if (tune)
-            cands = shape_candidates(c->cfg.k, batched, J.epi);
-        else
-            cands.push_back(default_shape(c->cfg.k, batched, J.epi));
-        for (const Shape& sh : cands)
-            if (std::find(qts.begin(), qts.end(), sh.qt) == qts.end()) qts.push_back(sh.qt);
-        firsts.resize(qts.size());
-        for (size_t i = 0; i < qts.size(); ++i) pts.push_back(pair_tiles(J, P.order, qts[i], &firsts[i]));
-        for (auto& f : firsts) max_items = std::max(max_items, f[n_pairs]);
+        if (tuned && hit != c->tuned.end())
+            shape = Shape{std::max(1, std::min({hit->second.qt, kMaxTile, kSelCap / c->cfg.k})),
+                          batched ? std::max(1, hit->second.bpc) : 0};
+        else if (tuned && !sa && n_pairs > 0)
+            tune_cache_store(c, key, shape);
+        pt = pair_tiles(J, P.order, shape.qt, &first);
+        max_items = std::max<int64_t>(1, first[n_pairs]);
         P.items_cap = max_items;
         std::vector<PairDev> pd(n_pairs);
         for (int64_t p = 0; p < n_pairs; ++p) {
@@ -1086,7 +1070,7 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
             for (int i = 0; i < 9; ++i) pd[p].F[i] = J.epi ? J.F[9 * p + i] : 0.0;
         }
         up2.add(pd);
-        for (auto& t : pts) up2.add(t);
+        up2.add(pt);
     };
     auto upload = [&](Uploader& up, std::vector<const void*>& d) {
         return sa ? upload_scratch(c, *sa, up, d) : upload_meta(c, up, d, kMetaMatch);
@@ -1130,7 +1114,7 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
         probe.used = sa->used;
         const size_t pieces[] = {std::max<size_t>(tbytes, 1), std::max<size_t>(up1_bytes, 1),
                                  std::max<size_t>(up2.host.size(), 1), (size_t)max_items * sizeof(Item),
-                                 (size_t)kSegments * kCounterStride * 4, 64};
+                                 (size_t)kCtlWords * 4, 64};
         size_t need = 0;
         for (size_t n : pieces) need = ((need + 255) & ~size_t(255)) + n;
         for (size_t n : pieces)
@@ -1150,63 +1134,27 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
     P.prm.num2 = (int64_t)c->cfg.ratio_num * c->cfg.ratio_num;
     P.prm.den2 = (int64_t)c->cfg.ratio_den * c->cfg.ratio_den;
     P.prm.max_px = J.max_px;
-    // work items (the most any candidate shape needs), counters, statistics
-    unsigned long long* stats = nullptr;
+    P.prm.grab = P.prm.set = 0;
+    // work items, work counters and statistics
     if (sa) {
         P.items = reinterpret_cast<Item*>(sa->take((size_t)max_items * sizeof(Item)));
-        P.counter = reinterpret_cast<uint32_t*>(sa->take((size_t)kSegments * kCounterStride * 4));
-        stats = reinterpret_cast<unsigned long long*>(sa->take(64));
+        P.ctl = reinterpret_cast<uint32_t*>(sa->take((size_t)kCtlWords * 4));
     } else {
         RETCHK(c->items.ensure((size_t)max_items * sizeof(Item)));
         P.items = c->items.as<Item>();
-        P.counter = c->counters.as<uint32_t>();
-        stats = c->dCount.as<unsigned long long>() + 8;
+        P.ctl = c->counters.as<uint32_t>();
     }
 
-    Shape best = cands[0];
-    if (tune && cands.size() > 1) {
-        // time every candidate shape on a prefix of the pairs (outputs are
-        // identical for every shape; the full run rewrites them)
-        const int64_t sample_pairs = batched ? std::max<int64_t>(1, std::min<int64_t>(n_pairs, n_pairs / 4 + 8))
-                                             : std::min<int64_t>(n_pairs, 12);
-        // the first round warms up; each shape keeps its fastest later time
-        std::vector<float> shape_ms(cands.size(), 1e30f);
-        for (int rep = 0; rep < 3; ++rep)
-            for (size_t ci = 0; ci < cands.size(); ++ci) {
-                const Shape& sh = cands[ci];
-                const size_t qi = (size_t)(std::find(qts.begin(), qts.end(), sh.qt) - qts.begin());
-                const int64_t n_it = firsts[qi][sample_pairs];
-                RETCHK(make_items(c, P, sh.qt, (const PairTiles*)d[1 + qi], (int32_t)pts[qi].size(),
-                                  firsts[qi][n_pairs]));
-                int64_t dummy_launches = 0;
-                HIPCHK(hipEventRecord(c->ev0, c->stream));
-                RETCHK(enqueue_matcher(c, P, J, sh, batched, firsts[qi], sample_pairs, n_it, stats, &dummy_launches,
-                                       false));
-                HIPCHK(hipEventRecord(c->ev1, c->stream));
-                HIPCHK(hipEventSynchronize(c->ev1));
-                float ms = 0.f;
-                HIPCHK(hipEventElapsedTime(&ms, c->ev0, c->ev1));
-                if (rep > 0) shape_ms[ci] = std::min(shape_ms[ci], ms);
-            }
-        best = cands[(size_t)(std::min_element(shape_ms.begin(), shape_ms.end()) - shape_ms.begin())];
-        c->tuned[key] = best;
-        tune_cache_store(c, key, best);
-    } else if (tune) {
-        c->tuned[key] = best;
-    }
-    const size_t qi = (size_t)(std::find(qts.begin(), qts.end(), best.qt) - qts.begin());
-    const int64_t n_items = firsts[qi][n_pairs];
-    RETCHK(make_items(c, P, best.qt, (const PairTiles*)d[1 + qi], (int32_t)pts[qi].size(), n_items));
-    HIPCHK(launch_fill_u64(c->stream, stats, 3, 0ull));
+    const int64_t n_items = first[n_pairs];
+    RETCHK(make_items(c, P, shape.qt, (const PairTiles*)d[1], (int32_t)pt.size(), n_items));
     J.turn = c->job_turn;
     c->job_turn ^= 1;
     HIPCHK(hipEventRecord(c->job_ev[J.turn][0], c->stream));
-    RETCHK(enqueue_matcher(c, P, J, best, batched, firsts[qi], n_pairs, n_items, stats, &c->last_launches,
-                           sa == nullptr));
+    RETCHK(enqueue_matcher(c, P, J, shape, batched, first, n_pairs, n_items, &c->last_launches, sa == nullptr));
     HIPCHK(hipEventRecord(c->job_ev[J.turn][1], c->stream));
-    c->last_shape_qt = best.qt;
-    c->last_shape_bpc = best.bpc;
-    HIPCHK(hipMemcpyAsync(job_stats_host(c, J.turn), stats, 24, hipMemcpyDeviceToHost, c->stream));
+    c->last_shape_qt = shape.qt;
+    c->last_shape_bpc = shape.bpc;
+    HIPCHK(hipMemcpyAsync(job_ctl_host(c, J.turn), P.ctl, (size_t)kCtlWords * 4, hipMemcpyDeviceToHost, c->stream));
     return CASHASH_OK;
 }
 
@@ -1227,10 +1175,10 @@ static void tune_cache_load(cashash_ctx* c) {
     std::fclose(f);
 }
 
+// Each key once per context.
 static void tune_cache_store(cashash_ctx* c, const std::string& key, Shape sh) {
-    (void)c;
     const char* path = std::getenv("CASHASH_AUTOTUNE_CACHE");
-    if (!path || !path[0]) return;
+    if (!path || !path[0] || !c->tune_stored.insert(key).second) return;
     FILE* f = std::fopen(path, "a");
     if (!f) return;
     std::fprintf(f, "{\"key\": \"%s\", \"qt\": %d, \"bpc\": %d}\n", key.c_str(), sh.qt, sh.bpc);
@@ -1245,13 +1193,16 @@ static int finish_match_job(cashash_ctx* c, MatchJob& J, bool whole_stream = tru
         HIPCHK(hipStreamSynchronize(c->stream));
     else
         HIPCHK(hipEventSynchronize(c->job_ev[J.turn][2]));
-    const unsigned long long* st = job_stats_host(c, J.turn);
+    uint32_t* ctl = job_ctl_host(c, J.turn);
     float ms = 0.f;
     HIPCHK(hipEventElapsedTime(&ms, c->job_ev[J.turn][0], c->job_ev[J.turn][1]));
     c->last_ms += ms;
-    J.bucket_entries += (int64_t)st[0];
-    J.union_size += (int64_t)st[1];
-    J.ranked += (int64_t)st[2];
+    for (int i = 0; i < kStatSlots; ++i) {
+        const unsigned long long* st = stat_slot(ctl, i);
+        J.bucket_entries += (int64_t)st[0];
+        J.union_size += (int64_t)st[1];
+        J.ranked += (int64_t)st[2];
+    }
     return CASHASH_OK;
 }
 
@@ -1612,15 +1563,12 @@ static int match_host(cashash_ctx* c, const cashash_images* im, const uint64_t* 
                                   0};
             }
         // the step's pairs, grouped by register-slot group (a part of one
-        // group is one persistent launch, not up to three) and then by train
+        // group is one persistent launch, not two) and then by train
         // image (each part builds the bucket tables of its own train images),
         // in parts (sized as above), so that a part's download and copy-out
         // overlap the next part's kernels
         std::vector<int64_t> ord(S.order.begin() + step.pair_begin, S.order.begin() + step.pair_end);
-        auto group = [&](int64_t p) {
-            const int n = im->n_feat[J.pair_t[p]];
-            return J.epi || n <= kLargeTrain ? 0 : n <= kHugeTrain ? 1 : 2;
-        };
+        auto group = [&](int64_t p) { return J.epi || im->n_feat[J.pair_t[p]] <= kLargeTrain ? 0 : 1; };
         std::stable_sort(ord.begin(), ord.end(), [&](int64_t x, int64_t y) {
             const int gx = group(x), gy = group(y);
             return gx != gy ? gx < gy : J.pair_t[x] < J.pair_t[y];

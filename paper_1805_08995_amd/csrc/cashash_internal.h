@@ -14,22 +14,13 @@ constexpr int kRows = kCodeBits + kTables * kKeyBits;  // 176 projection rows
 constexpr int kRowTiles = kRows / 16;                   // 11 MFMA row tiles
 constexpr int kOffStride = 257;    // bucket offsets per table (256 keys + end)
 constexpr int kMaxK = 64;
-constexpr int kListCap = 512;      // per-wave LDS candidate list (u32 keys); reused for tile distances
 constexpr int kSelCap = 384;       // per-wave LDS list of a query tile's kept candidates
-// The band kernel's shorter lists: more than kRegCap = 256 band survivors
-// take its fallback path, and its tiles keep at most 320 candidates (32
-// queries at k = 10, fewer queries for larger k).  Less LDS per block, so that
-// seven blocks fit a compute unit.
-constexpr int kListCapEpi = 320;
-constexpr int kSelCapEpi = 320;
-// A query's candidate keys are held in NS 64-wide register slots (NS = 4, 6
-// or 8, a template parameter of the matcher); queries with more candidates
-// use the LDS list.  Plain-form pairs run 4 slots up to kLargeTrain train
-// points, 6 up to kHugeTrain and 8 above (fewer slots: fewer registers, more
-// resident waves).  The band (epipolar) form always runs 4 slots: only the
-// survivors of its band pass fill them.
+// The plain matcher finds a candidate's bucket run by masks of run starts for
+// the first 64 x `slots` candidates of a query (4 or 8, a template parameter);
+// a query with more takes compares for the rest.  Pairs run 4 up to kLargeTrain
+// train points (expected candidates per query: about 0.0255 per train point,
+// 230 at 9000) and 8 above: fewer masks, less LDS and one more block per CU.
 constexpr int kLargeTrain = 9000;
-constexpr int kHugeTrain = 14000;  // plain form: above it, 8 slots; above kLargeTrain, 6
 constexpr int kWavesPerBlock = 4;  // matcher block = 4 waves
 constexpr int kMaxTile = 32;       // queries per matcher work item (one per lane of the tile setup)
 constexpr int kBucketWaves = 8;    // wavefronts per (train image, table) counting sort
@@ -73,7 +64,8 @@ struct TableOut {
 // tables: for table t and position s (entries of one bucket contiguous, in
 // ascending index order)
 //   code[t][s] : the point's 128-bit code (16 B)
-//   kid[t][s]  : its six keys in bytes 0..5 and its index in bits 48..63
+//   kid[t][s]  : keys and index as the matcher's union test takes them (8 B,
+//                entry_word)
 //   kp[t][s]   : its keypoint (epipolar form only)
 // laid out one after another from TableOut::ent / ImgDev::ent.
 inline __host__ __device__ size_t ent_bytes(int n, bool epi) { return (size_t)kTables * n * (epi ? 32 : 24); }
@@ -84,7 +76,7 @@ struct PairDev {
     double F[9];        // row-major fundamental matrix (epipolar form)
 };
 
-struct Item {           // a tile of consecutive queries of one pair (nq <= kMaxTile, nq * k <= kSelCap or kSelCapEpi)
+struct Item {           // a tile of consecutive queries of one pair (nq <= kMaxTile, nq * k <= kSelCap)
     int32_t pair;
     int32_t q0;
     int32_t nq;
@@ -103,8 +95,24 @@ struct RowChunk {       // rows [r0, r0 + nr) of image img
     int32_t pad;
 };
 
+// Resident blocks per compute unit the matcher kernels are compiled for, and
+// their persistent launches use: at 7 the registers (72) and the LDS (23040
+// bytes per block) last; the 8-slot form's LDS lets 6 blocks share a unit.
+// Fewer are slower (60 x 8000 points: 4 blocks 5.8 ms, 6 4.9, 7 4.6); 8 of the
+// 4-slot form (64 registers) gave nothing.
+constexpr int match_blocks_per_cu(bool epi, int ns) { return epi || ns <= 4 ? 7 : 6; }
+
 constexpr int kSegments = 8;       // one work segment per XCD
-constexpr int kCounterStride = 64; // u32 elements between work counters (one 256-byte line each)
+// Control words of a matcher call: a line of kCtlStride words per segment
+// holds its work counter (one per launch of the call) and kStatsPerLine places
+// for statistics.
+constexpr int kCtlStride = 64;
+constexpr int kCtlWords = kSegments * kCtlStride;
+constexpr int kStatsPerLine = 3;
+constexpr int kStatSlots = kSegments * kStatsPerLine;
+inline __host__ __device__ unsigned long long* stat_slot(uint32_t* ctl, int i) {
+    return reinterpret_cast<unsigned long long*>(ctl + (i % kSegments) * kCtlStride + 16 * (1 + i / kSegments));
+}
 
 struct MatchParams {
     int32_t k;
@@ -112,11 +120,13 @@ struct MatchParams {
     int64_t num2;       // ratio_num^2
     int64_t den2;       // ratio_den^2
     double max_px;
-    // persistent scheduling: items [seg[x], seg[x+1]) are segment x, handed
-    // out `grab` at a time from counter x; a wave starts on its own XCD's
-    // segment and moves to the others when it is exhausted
+    // persistent scheduling (grab > 0): items [seg[x], seg[x+1]) are segment x,
+    // handed out `grab` at a time, by counter `set` of its control line; a wave
+    // starts on its own XCD's segment and moves to the others when it is
+    // exhausted.  grab == 0: wavefront w of the grid takes item w only.
     int32_t seg[kSegments + 1];
     int32_t grab;
+    int32_t set;
 };
 
 struct ProjParams {

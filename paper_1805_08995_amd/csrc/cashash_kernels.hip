@@ -32,11 +32,13 @@ __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
 
 // Work items from the per-pair tile table: item i belongs to the last entry
 // whose first tile is <= i (binary search); its queries are tile (i - first)
-// of that pair's query image, qt per tile.
+// of that pair's query image, qt per tile.  Also clears the matcher's control
+// words.
 __global__ void make_items_kernel(const PairTiles* __restrict__ pt, int32_t n_pt, const PairDev* __restrict__ pairs,
                                   const ImgDev* __restrict__ imgs, int32_t qt, Item* __restrict__ items,
-                                  int32_t n_items) {
+                                  int32_t n_items, uint32_t* __restrict__ ctl) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kCtlWords) ctl[i] = 0u;
     if (i >= n_items) return;
     int32_t lo = 0, hi = n_pt - 1;
     while (lo < hi) {
@@ -651,6 +653,18 @@ __global__ __launch_bounds__(256) void near_apply_kernel(const CodeOut* __restri
 // slice's keys, the block scans the bucket totals and gives each wave its
 // start inside every bucket, then each wave scatters its slice in order.
 // Ranks inside a 64-wide chunk come from eight key-bit ballots.
+
+// Keys and index of an entry of table t, for the matcher's union test (a
+// candidate counts in the first table whose key it shares with the query).
+// Low word: the keys of tables 0-3 before t, 0 in the other bytes.  High word:
+// the index above 16 bits that hold key 4 in table 5's entries and else 0x100,
+// which no key equals.
+__device__ __forceinline__ uint64_t entry_word(int t, uint32_t k03, uint32_t k45, uint32_t j) {
+    const uint32_t lo = t >= 4 ? k03 : k03 & ~(~0u << (8 * t));
+    const uint32_t hi = (j << 16) | (t == 5 ? k45 & 0xFFu : 0x100u);
+    return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+
 template <bool EPI>
 __global__ __launch_bounds__(64 * kBucketWaves) void bucket_kernel(const ImgDev* __restrict__ imgs,
                                                                    const TableOut* __restrict__ touts,
@@ -723,8 +737,8 @@ __global__ __launch_bounds__(64 * kBucketWaves) void bucket_kernel(const ImgDev*
         if (valid) {
             const uint16_t* kp = reinterpret_cast<const uint16_t*>(im.keys + 6 * (int64_t)j);
             gstore(out_code + pos, gload(reinterpret_cast<const ulonglong2*>(im.codes) + j));
-            gstore(out_kid + pos, (uint64_t)gload(kp) | ((uint64_t)gload(kp + 1) << 16) |
-                                      ((uint64_t)gload(kp + 2) << 32) | ((uint64_t)j << 48));
+            const uint32_t k03 = (uint32_t)gload(kp) | ((uint32_t)gload(kp + 1) << 16);
+            gstore(out_kid + pos, entry_word(t, k03, gload(kp + 2), (uint32_t)j));
             if constexpr (EPI) gstore(out_kp + pos, gload(reinterpret_cast<const float2*>(im.kp) + j));
             if (rank == 0) wc[key] = pos + (uint32_t)__popcll(eq);
         }
@@ -746,10 +760,10 @@ hipError_t launch_fill_u32(hipStream_t s, uint32_t* p, int64_t n, uint32_t v) {
 }
 
 hipError_t launch_make_items(hipStream_t s, const PairTiles* pt, int32_t n_pt, const PairDev* pairs,
-                             const ImgDev* imgs, int32_t qt, Item* items, int32_t n_items) {
-    if (n_items <= 0) return hipSuccess;
-    CH_LAUNCH(make_items_kernel, dim3((unsigned)((n_items + 255) / 256)), dim3(256), 0, s, pt, n_pt, pairs, imgs, qt,
-              items, n_items);
+                             const ImgDev* imgs, int32_t qt, Item* items, int32_t n_items, uint32_t* ctl) {
+    const unsigned threads = (unsigned)std::max(n_items, kCtlWords);
+    CH_LAUNCH(make_items_kernel, dim3((threads + 255) / 256), dim3(256), 0, s, pt, n_pt, pairs, imgs, qt, items, n_items,
+              ctl);
     return hipSuccess;
 }
 

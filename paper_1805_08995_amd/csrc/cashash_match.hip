@@ -4,12 +4,14 @@
 // One wavefront per tile of up to 32 consecutive queries of one pair.  Train
 // images are pre-sorted into per-table buckets whose entries carry code, keys
 // and index, so a query's candidates are six contiguous runs read 64 at a
-// time.  The paper's per-query index table (a histogram over Hamming
-// distance) is built in LDS and scanned with DPP to find the Hamming distance
-// of the k-th candidate; ties there are broken by index.  The tile's kept
-// candidates are measured together with v_dot4_u32_u8 (exact), then the
-// ratio test runs one lane per query.  All pairs run in one persistent launch
-// with per-XCD work segments.
+// time.  Candidates whose key (Hamming << 16 | index) is at most a threshold
+// carried from query to query go to a short list in LDS; the k smallest of the
+// list are found from the paper's index table (a histogram over Hamming
+// distance, scanned with DPP) and ties at the k-th distance are broken by
+// index.  The tile's kept candidates are measured with v_dot4_u32_u8 (exact),
+// then the ratio test runs one lane per query.  All pairs run in one persistent
+// launch (two when small and large train images meet) with per-XCD work
+// segments.
 #include "cashash_device.h"
 
 namespace cashash {
@@ -35,153 +37,7 @@ __device__ __forceinline__ uint32_t wave_scan_dpp(uint32_t x) {
     return x;
 }
 
-// x as seen through a DPP pattern; lanes with no source receive ~0u.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ uint32_t dpp_hi(uint32_t x) {
-    return __builtin_amdgcn_update_dpp(~0u, x, CTRL, ROW_MASK, 0xf, false);
-}
-
 __device__ __forceinline__ uint32_t readlane(uint32_t v, int l) { return __builtin_amdgcn_readlane(v, l); }
-
-// Minimum over the 64 lanes (the same prefix pattern as wave_scan_dpp; lane
-// 63 ends with the minimum of all).
-__device__ __forceinline__ uint32_t wave_min(uint32_t x) {
-    x = min(x, dpp_hi<0x111, 0xf>(x));
-    x = min(x, dpp_hi<0x112, 0xf>(x));
-    x = min(x, dpp_hi<0x114, 0xf>(x));
-    x = min(x, dpp_hi<0x118, 0xf>(x));
-    x = min(x, dpp_hi<0x142, 0xa>(x));
-    x = min(x, dpp_hi<0x143, 0xc>(x));
-    return readlane(x, 63);
-}
-__device__ __forceinline__ uint32_t readfirstlane_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, int l) {
-    return (uint64_t)readlane((uint32_t)v, l) | ((uint64_t)readlane((uint32_t)(v >> 32), l) << 32);
-}
-__device__ __forceinline__ double readlane_f64(double v, int l) { return __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(v), l)); }
-
-// Smallest bin d of the 256-bin LDS index table whose cumulative count
-// reaches `need` (1 <= need <= total); *below = count in bins < d, *in_bin =
-// count in bin d.  Lane l holds bins 4l .. 4l+3.  READOUT (the plain
-// kernels): after the scan only the lane that crosses `need` is read out
-// (readlane) and the bin inside it is picked with scalar arithmetic; else
-// every lane picks its candidate bin and the crossing lane's is read (the
-// band kernels, which rarely rank and schedule better with this form).
-template <bool READOUT>
-__device__ __forceinline__ uint32_t hist_select(const uint32_t* hist, uint32_t need, int lane, uint32_t* below,
-                                                uint32_t* in_bin) {
-    const uint4 h = reinterpret_cast<const uint4*>(hist)[lane];
-    if constexpr (READOUT) {
-        const uint32_t s3 = h.x + h.y + h.z + h.w;
-        const uint32_t incl = wave_scan_dpp(s3);
-        const uint64_t m = __ballot(incl >= need);
-        const int L = __ffsll((unsigned long long)m) - 1;
-        uint32_t b = readlane(incl - s3, L);
-        const uint32_t c0 = readlane(h.x, L), c1 = readlane(h.y, L), c2 = readlane(h.z, L), c3 = readlane(h.w, L);
-        uint32_t d = 4u * (uint32_t)L, c = c0;
-        if (b + c0 < need) {
-            b += c0;
-            ++d;
-            c = c1;
-            if (b + c1 < need) {
-                b += c1;
-                ++d;
-                c = c2;
-                if (b + c2 < need) {
-                    b += c2;
-                    ++d;
-                    c = c3;
-                }
-            }
-        }
-        *below = b;
-        *in_bin = c;
-        return d;
-    } else {
-        const uint32_t s0 = h.x, s1 = s0 + h.y, s2 = s1 + h.z, s3 = s2 + h.w;
-        const uint32_t incl = wave_scan_dpp(s3);
-        const uint32_t ex = incl - s3;
-        const uint32_t i = (ex + s0 >= need) ? 0u : (ex + s1 >= need) ? 1u : (ex + s2 >= need) ? 2u : 3u;
-        const uint32_t bl = ex + (i == 0 ? 0u : i == 1 ? s0 : i == 2 ? s1 : s2);
-        const uint64_t m = __ballot(incl >= need);
-        const int L = __ffsll((unsigned long long)m) - 1;
-        *below = readlane(bl, L);
-        const uint32_t d = readlane(4u * (uint32_t)lane + i, L);
-        *in_bin = readlane(hist[d], 0);
-        return d;
-    }
-}
-
-__device__ __forceinline__ void clear_hist(uint32_t* hist, int lane) {
-    reinterpret_cast<uint4*>(hist)[lane] = make_uint4(0u, 0u, 0u, 0u);
-    wave_sync();
-}
-
-// Per-query view of the six bucket runs concatenated in table order, plus the
-// query's code and keys and its epipolar line.  Passed by value so every
-// field stays in registers.  Two layouts of the run table qtab (LDS, per
-// query), both giving for candidate e its entry position e + C (C = t * n +
-// b_t - start of its run, of table t) and 8t (the shift that masks the keys
-// of tables >= t in the union test):
-//  by table (most kernels): P1..P5 are the run starts of tables 1..5 and P6
-//    the number of bucket entries; the number of starts at or below e is its
-//    table t, and qtab[t] = C.
-//  by ordinal (the 4- and 6-slot plain kernels): P1..P5 are the starts of the
-//    non-empty runs after the first non-empty one (~0u for the other runs),
-//    whose count at or below e is the ordinal o of e's run among the
-//    non-empty runs, and qtab[o] = (16 C << 6) | 8t.  qtab[8 + 2u .. 9 + 2u]
-//    holds the 64-bit mask of those starts inside chunk u (bit j: a start at
-//    candidate 64u + j + 1), so a lane finds its ordinal with mbcnt, and
-//    bits 3(u-1) .. 3u-1 of qtab[6] count the starts at or below 64u.
-// In both, the query's key bytes 0-3 sit in qtab[7] and bytes 4-5 in bits
-// 16-31 of qtab[6].
-struct QueryRuns {
-    uint64_t qc0, qc1, qk;
-    uint32_t P1, P2, P3, P4, P5, P6;
-    const uint32_t* qtab;
-    double la, lb, lc;
-};
-
-// Train image tables, struct of arrays (see ent_bytes).
-struct TrainView {
-    const ulonglong2* code;
-    const uint64_t* kid;
-    const float2* kp;
-    int32_t n;
-};
-
-// Candidate e of the concatenated six bucket runs -> packed key
-// (Hamming << 16 | index), or ~0u if e is past the runs, repeats an earlier
-// table's candidate, falls outside the epipolar band or exceeds tau.  The
-// loads are unconditional (a clamped position) so several calls can have
-// their loads in flight together.  n_union counts candidates that survive
-// the union and the band.
-// Entry position of candidate e of the concatenated runs; cw receives 8t in
-// its low 6 bits.  Lanes past the runs get candidate 0's position (a valid
-// address).
-template <bool ORD>
-__device__ __forceinline__ uint32_t entry_pos(uint32_t e, const QueryRuns& r, uint32_t& cw) {
-    const uint32_t ec = e < r.P6 ? e : 0u;
-    const uint32_t o = (uint32_t)(ec >= r.P1) + (ec >= r.P2) + (ec >= r.P3) + (ec >= r.P4) + (ec >= r.P5);
-    if constexpr (ORD) {
-        cw = r.qtab[o];
-        return ec + (cw >> 10);
-    } else {
-        cw = 8u * o;
-        return ec + r.qtab[o];
-    }
-}
-
-// Eq. 1-2: the candidate's keypoint lies within the band around the
-// query's epipolar line.
-__device__ __forceinline__ bool band_ok(float2 p, const QueryRuns& r, double dd) {
-    const double xp = (double)p.x, yp = (double)p.y;
-    const double ev = (r.la * xp + r.lb * yp) + r.lc;
-    return ev * ev <= dd * (r.la * r.la + r.lb * r.lb);
-}
-__device__ __forceinline__ bool in_band(const TrainView& tv, uint32_t pos, const QueryRuns& r, double dd) {
-    return band_ok(gload(tv.kp + pos), r, dd);
-}
 
 // popcount(x) + acc as one v_bcnt_u32_b32 (a dependent chain keeps the
 // compiler from splitting a 128-bit count into two halves and an add).
@@ -191,804 +47,952 @@ __device__ __forceinline__ uint32_t bcnt_acc(uint32_t x, uint32_t acc) {
     return r;
 }
 
-// Loaded entry (code c, keys and index kid) of a run of table t -> packed
-// key (Hamming << 16 | index), or ~0u if it repeats an earlier table's
-// candidate or exceeds tau.  The low 6 bits of cw hold 8t.  `live` masks
-// lanes with no candidate; n_union counts candidates that survive the union.
-// CHAIN selects hand-picked instructions for the union test and a chained
-// count (the plain kernels); the band kernels, where few entries get here,
-// keep the compiler's own, which schedules better there.  FILT = false
-// (tau = 128, no filter): no tau test and no union count here (the caller
-// counts the union from the valid keys).
-template <bool CHAIN, bool FILT>
-__device__ __forceinline__ uint32_t loaded_key(ulonglong2 c, uint64_t kid, uint32_t cw, bool live,
-                                               const QueryRuns& r, int32_t tau, uint32_t& n_union) {
-    // union: drop the candidate if it shares an earlier table's key with the
-    // query (it was already collected there): a zero byte among bytes
-    // 0 .. t-1 of keys ^ query keys.  Bytes t.. are forced to 0xFF with
-    // fm = ~0 << 8t, then the exact zero-byte test (v - 0x01..) & ~v & 0x80..
-    // runs on bytes 0-3 and on byte 4 (table 4's key, only below t = 5).
-    const uint64_t fm = ~0ull << (cw & 63u);
-    bool dup;
-    if constexpr (CHAIN) {
-        // bitop3 truth tables: 0xBE = (a ^ b) | c, 0x20 = a & ~b & c
-        const uint32_t y = __builtin_amdgcn_bitop3_b32((uint32_t)kid, (uint32_t)r.qk, (uint32_t)fm, 0xBE);
-        const uint32_t y4 =
-            __builtin_amdgcn_bitop3_b32((uint32_t)(kid >> 32), (uint32_t)(r.qk >> 32), (uint32_t)(fm >> 32), 0xBE);
-        const uint32_t zl = __builtin_amdgcn_bitop3_b32(y - 0x01010101u, y, 0x80808080u, 0x20);
-        const uint32_t zh = __builtin_amdgcn_bitop3_b32(y4 - 1u, y4, 0x80u, 0x20);
-        dup = (zl | zh) != 0u;
-    } else {
-        const uint32_t y = ((uint32_t)kid ^ (uint32_t)r.qk) | (uint32_t)fm;
-        const uint32_t y4 = ((uint32_t)(kid >> 32) ^ (uint32_t)(r.qk >> 32)) | (uint32_t)(fm >> 32);
-        dup = (((y - 0x01010101u) & ~y) | ((y4 - 0x01010101u) & ~y4 & 0xFFu)) & 0x80808080u;
-    }
-    bool ok = live && !dup;
-    if constexpr (FILT) n_union += ok ? 1u : 0u;
-    uint32_t h;
-    if constexpr (CHAIN) {
-        h = (uint32_t)__popc((uint32_t)c.x ^ (uint32_t)r.qc0);
-        h = bcnt_acc((uint32_t)(c.x >> 32) ^ (uint32_t)(r.qc0 >> 32), h);
-        h = bcnt_acc((uint32_t)c.y ^ (uint32_t)r.qc1, h);
-        h = bcnt_acc((uint32_t)(c.y >> 32) ^ (uint32_t)(r.qc1 >> 32), h);
-    } else {
-        h = (uint32_t)(__popcll(c.x ^ r.qc0) + __popcll(c.y ^ r.qc1));
-    }
-    if constexpr (FILT) ok = ok && (int32_t)h <= tau;
-    return ok ? ((h << 16) | (uint32_t)(kid >> 48)) : ~0u;
+// popcount(x) by the same instruction.
+__device__ __forceinline__ uint32_t bcnt(uint32_t x) {
+    uint32_t r;
+    asm("v_bcnt_u32_b32 %0, %1, 0" : "=v"(r) : "v"(x));
+    return r;
 }
 
-// The same for the entry at pos, loaded here.
-template <bool CHAIN, bool FILT>
-__device__ __forceinline__ uint32_t entry_key(const TrainView& tv, uint32_t cw, uint32_t pos, bool live,
-                                              const QueryRuns& r, int32_t tau, uint32_t& n_union) {
-    return loaded_key<CHAIN, FILT>(gload(tv.code + pos), gload(tv.kid + pos), cw, live, r, tau, n_union);
-}
+// ------------------------------------------------------------------ shared by both matcher kernels
 
-// Candidate e of the concatenated six bucket runs -> packed key, or ~0u if e
-// is past the runs, outside the epipolar band, a repeat or above tau.
-template <bool EPI, bool ORD, bool FILT>
-__device__ __forceinline__ uint32_t key_at(uint32_t e, const TrainView& tv, const QueryRuns& r, int32_t tau,
-                                           double dd, uint32_t& n_union) {
-    uint32_t cw;
-    const uint32_t pos = entry_pos<ORD>(e, r, cw);
-    bool live = e < r.P6;
-    if constexpr (EPI) live = live && in_band(tv, pos, r, dd);
-    return entry_key<!EPI, FILT>(tv, cw, pos, live, r, tau, n_union);
-}
-
-// The first C chunks of 64 candidates into register slots, all loads issued
-// together (slots >= C keep ~0u).
-template <bool EPI, bool FILT, int C, int NS>
-__device__ __forceinline__ void gather_chunks(uint32_t (&kr)[NS], int lane, const TrainView& tv, const QueryRuns& r,
-                                              int32_t tau, double dd, uint32_t& n_union) {
-#pragma unroll
-    for (int u = 0; u < C; ++u) kr[u] = key_at<EPI, false, FILT>(64u * u + (uint32_t)lane, tv, r, tau, dd, n_union);
-}
-
-// The same for the plain form when the runs fit 256 candidates: the run
-// ordinal of chunk u's lanes comes from the chunk's start mask with mbcnt
-// (o0 = starts at or below 64u, carried from chunk to chunk), and only the
-// last chunk can hold lanes past the runs.  Positions of all C chunks are
-// found first so that their loads are in flight together.
-template <bool FILT, int C, int NS>
-__device__ __forceinline__ void gather_chunks_mask(uint32_t (&kr)[NS], int lane, const TrainView& tv,
-                                                   const QueryRuns& r, int32_t tau, uint32_t& n_union) {
-    uint32_t cw[C], boff[C];  // run word; byte offset of the entry's code (16 bytes per entry)
-    const uint32_t pre = C > 1 ? readfirstlane_u32(r.qtab[6]) : 0u;  // uniform: o0 below is scalar work
-#pragma unroll
-    for (int u = 0; u < C; ++u) {
-        const uint2 sm = *reinterpret_cast<const uint2*>(r.qtab + 8 + 2 * u);
-        const uint32_t o0 = u == 0 ? 0u : (pre >> (3 * (u - 1))) & 7u;
-        const uint32_t o = __builtin_amdgcn_mbcnt_hi(sm.y, __builtin_amdgcn_mbcnt_lo(sm.x, o0));
-        const uint32_t e = 64u * u + (uint32_t)lane;
-        const bool live = u + 1 < C || e < r.P6;
-        cw[u] = r.qtab[live ? o : 0u];
-        boff[u] = (cw[u] >> 6) + (live ? e << 4 : 0u);
+// Arguments needed only when work is grabbed or a tile is finished, kept in
+// LDS rather than in scalar registers (the kernels are short of them), and the
+// block's sums of the statistics.
+struct Rare {
+    int32_t* o_idx;
+    int32_t* o_d1;
+    int32_t* o_d2;
+    uint32_t* ctl;
+    int64_t num2, den2;
+    int32_t seg[kSegments + 1];
+    int32_t grab, set;
+    uint32_t done, empty;  // wavefronts that ended; exhausted segments
+    unsigned long long sum[3];
+    __device__ __forceinline__ void fill(const MatchParams& prm, uint32_t* c, int32_t* idx, int32_t* d1, int32_t* d2) {
+        o_idx = idx;
+        o_d1 = d1;
+        o_d2 = d2;
+        ctl = c;
+        num2 = prm.num2;
+        den2 = prm.den2;
+        for (int i = 0; i <= kSegments; ++i) seg[i] = prm.seg[i];
+        grab = prm.grab;
+        set = prm.set;
+        done = empty = 0;
+        sum[0] = sum[1] = sum[2] = 0;
     }
-    ulonglong2 c[C];
-    uint64_t kid[C];
-#pragma unroll
-    for (int u = 0; u < C; ++u) {
-        c[u] = gload(reinterpret_cast<const ulonglong2*>(reinterpret_cast<const char*>(tv.code) + boff[u]));
-        kid[u] = gload(reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(tv.kid) + (boff[u] >> 1)));
+    __device__ __forceinline__ uint32_t* counter(uint32_t x) const { return ctl + x * kCtlStride + set; }
+    // A wavefront's statistics at its end (lane 0): bucket entries, union
+    // sizes, ranked.  The block's last wavefront adds the block's sums to one
+    // of kStatSlots places: atomics of every wavefront on the same three words
+    // had queued for 0.3 ms a launch.
+    __device__ __forceinline__ void add_stats(uint64_t bucket, uint64_t uni, uint64_t ranked) {
+        atomicAdd(&sum[0], (unsigned long long)bucket);
+        atomicAdd(&sum[1], (unsigned long long)uni);
+        atomicAdd(&sum[2], (unsigned long long)ranked);
+        __threadfence_block();
+        if (atomicAdd(&done, 1u) != (uint32_t)kWavesPerBlock - 1u) return;
+        unsigned long long* s = stat_slot(ctl, (int)(blockIdx.x % kStatSlots));
+        for (int i = 0; i < 3; ++i) {
+            const unsigned long long v = atomicAdd(&sum[i], 0ull);
+            if (v) atomicAdd(s + i, v);
+        }
     }
-#pragma unroll
-    for (int u = 0; u < C; ++u)
-        kr[u] = loaded_key<true, FILT>(c[u], kid[u], cw[u], u + 1 < C || 64u * u + (uint32_t)lane < r.P6, r, tau,
-                                       n_union);
-}
+};
 
-// Resident blocks per CU each instantiation is compiled for (4 waves per
-// block): the register budget that keeps 7, 6 or 5 wavefronts per SIMD.  The
-// band kernel runs 7 (72 registers, a few spilled outside its band pass; its
-// shorter LDS lists let 7 blocks share a CU's LDS): the extra wavefronts hide
-// more of its keypoint-load latency.  The 8-slot kernels run 6 (80 registers);
-// the 6-slot ones 5, as their 28.8 KB of LDS per block allows.
-template <bool EPI, int NS>
-constexpr int kMatchMinBlocks = NS == 4 ? (EPI ? 7 : 6) : (NS == 8 ? 6 : 5);
-
-// One wavefront per tile of <= kMaxTile consecutive queries of one pair.
-//  setup    : lane l loads query l's keys and six bucket ranges at once and
-//             leaves its run table (and keys) in LDS; the run starts are
-//             broadcast per query with LDS permutes.
-//  Steps 1-3: per query, the six bucket runs are read in 64-wide chunks, all
-//             of a query's chunks in flight together when they fit the
-//             register slots (union by first-table dedupe, Hamming, tau,
-//             band); the index table (histogram over Hamming distance) is
-//             built in LDS and scanned to find the Hamming distance H* of
-//             the k-th candidate; ties at H* are broken by index (up to 64
-//             ranked directly, more by ballot counting over a binary search
-//             of the index bits).
-//  Step 4   : the tile's kept (query, candidate) pairs are measured together,
-//             4 lanes per pair with v_dot4_u32_u8; lane l then takes query l's
-//             distances, picks the nearest and second nearest and applies the
-//             ratio test, and the tile's outputs are stored coalesced.
-// FILT = false: the plain kernels' form for tau = 128 (no Hamming filter).
-template <bool EPI, int NS, bool FILT>
-__global__ __launch_bounds__(256, (kMatchMinBlocks<EPI, NS>)) void match_kernel(const ImgDev* __restrict__ imgs,
-                                                    const PairDev* __restrict__ pairs,
-                                                    const Item* __restrict__ items, int32_t n_items,
-                                                    uint32_t* __restrict__ counter, MatchParams prm,
-                                                    int32_t* __restrict__ o_idx, int32_t* __restrict__ o_d1,
-                                                    int32_t* __restrict__ o_d2,
-                                                    unsigned long long* __restrict__ stats) {
-    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kWavesPerBlock][256];
-    // candidate list and tile list capacities (the band kernel's are shorter)
-    constexpr int kLC = EPI ? kListCapEpi : kListCap;
-    constexpr int kSC = EPI ? kSelCapEpi : kSelCap;
-    __shared__ __attribute__((aligned(16))) uint32_t s_list[kWavesPerBlock][kLC];
-    __shared__ __attribute__((aligned(16))) uint32_t s_sel[kWavesPerBlock][kSC];
-    // run words per query, plus the chunk start masks (4- and 6-slot plain
-    // kernels)
-    // or the epipolar line (band kernel)
-    constexpr bool kMask = (NS == 4 || NS == 6) && !EPI;
-    constexpr int kQS = kMask ? 8 + 2 * NS : (EPI ? 14 : 8);
-    __shared__ __attribute__((aligned(16))) uint32_t s_qtab[kWavesPerBlock][kMaxTile * kQS];
-    // arguments needed only when work is grabbed or a tile is finished, kept
-    // in LDS rather than in scalar registers (the kernel is short of them)
-    struct Rare {
-        int32_t* o_idx;
-        int32_t* o_d1;
-        int32_t* o_d2;
-        unsigned long long* stats;
-        uint32_t* counter;
-        int64_t num2, den2;
-        int32_t seg[kSegments + 1];
-        int32_t grab;
-    };
-    __shared__ Rare s_rare;
-    if (threadIdx.x == 0) {
-        s_rare.o_idx = o_idx;
-        s_rare.o_d1 = o_d1;
-        s_rare.o_d2 = o_d2;
-        s_rare.stats = stats;
-        s_rare.counter = counter;
-        s_rare.num2 = prm.num2;
-        s_rare.den2 = prm.den2;
-        for (int i = 0; i <= kSegments; ++i) s_rare.seg[i] = prm.seg[i];
-        s_rare.grab = prm.grab;
-    }
-    __syncthreads();
-    const bool persistent = counter != nullptr;
-    const int lane = threadIdx.x & 63;
-    const int wv = (int)uniform(threadIdx.x >> 6);
-    uint32_t* hist = s_hist[wv];
-    uint32_t* list = s_list[wv];
-    uint32_t* sel = s_sel[wv];
-    uint32_t* qtab = s_qtab[wv];
-    const int part = lane & 3;
-    uint64_t st_bucket = 0, st_ranked = 0;
-    uint64_t st_valid = 0;  // no Hamming filter: the union is the valid keys, counted per query (uniform)
-    uint32_t st_union = 0;
-    const double dd = prm.max_px * prm.max_px;
-
-    // XCD of this wavefront: its segment of the work list is the one whose
-    // train images stay in this XCD's L2
-    const uint32_t home = __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & (kSegments - 1);
-    int32_t it = (int32_t)(blockIdx.x * kWavesPerBlock + wv);
+// A persistent wavefront's share of the work list: it takes `grab` items at a
+// time from its own XCD's segment (blocks are placed on the XCDs in turn),
+// whose train images stay in that XCD's L2, and moves to the other segments
+// when that one is exhausted.  A segment found exhausted is noted for the whole
+// block, so that at the end of a launch a counter is asked once per block and
+// not by each of up to 7168 wavefronts.
+struct Grab {
     int32_t cur = 0, end = 0;
-    for (;;) {
-        if (persistent) {
-            if (cur >= end) {
-                for (int sx = 0; sx < kSegments; ++sx) {
-                    const uint32_t x = (home + (uint32_t)sx) & (kSegments - 1);
-                    const int32_t s0 = s_rare.seg[x], s1 = s_rare.seg[x + 1];
-                    if (s0 >= s1) continue;
-                    uint32_t v = 0;
-                    const int32_t grab = s_rare.grab;
-                    if (lane == 0) v = atomicAdd(s_rare.counter + x * kCounterStride, (uint32_t)grab);
-                    v = readlane(v, 0);
-                    if ((int64_t)s0 + v < (int64_t)s1) {
-                        cur = s0 + (int32_t)v;
-                        end = min(cur + grab, s1);
+    // false: every segment is exhausted
+    __device__ __forceinline__ bool next(Rare& rare, int lane, int32_t& it) {
+        if (cur >= end) {
+#pragma unroll 1
+            for (int sx = 0; sx < kSegments; ++sx) {
+                const uint32_t x = (blockIdx.x + (uint32_t)sx) & (kSegments - 1);
+                const int32_t s0 = rare.seg[x], s1 = rare.seg[x + 1];
+                if (s0 >= s1 || (*(volatile uint32_t*)&rare.empty >> x & 1u)) continue;
+                uint32_t v = 0;
+                const int32_t n = rare.grab;
+                if (lane == 0) v = atomicAdd(rare.counter(x), (uint32_t)n);
+                v = readlane(v, 0);
+                if ((int64_t)s0 + v < (int64_t)s1) {
+                    cur = s0 + (int32_t)v;
+                    end = min(cur + n, s1);
+                    break;
+                }
+                if (lane == 0) atomicOr(&rare.empty, 1u << x);
+            }
+            if (cur >= end) return false;
+        }
+        it = cur++;
+        return true;
+    }
+};
+
+// Step 4 and the ratio test of one tile of nq <= kMaxTile queries.  sel: the
+// train indices kept, query by query; lane l's `kept` is query l's kept count
+// and first place in sel (<< 16).  Four lanes take one query at a time (lanes
+// 4g .. the queries R g + r, r = 0 .. R - 1): they hold its descriptor and go
+// through its candidates with v_dot4_u32_u8 (exact), so that a query's row is
+// loaded once, and each load of the four lanes is 64 consecutive bytes of one
+// row, one L1 access.  Every lane of the four ends with the nearest and second
+// nearest; lane 4g + r keeps those of round r.
+__device__ __forceinline__ void finish_tile(int lane, int nq, int32_t q0, const uint8_t* __restrict__ qdesc,
+                                            const uint8_t* __restrict__ tdesc, int64_t out, uint32_t kept,
+                                            const uint16_t* sel, const Rare& rare) {
+    const int g = lane >> 2, part = lane & 3;
+    const int R = (nq + 15) >> 4;
+    const uint32_t part16 = (uint32_t)part << 4;
+    // a row's bytes 16 part .. and 64 + 16 part ..
+    struct Row {
+        uint4 lo, hi;
+    };
+    auto row = [&](const uint8_t* base, uint32_t i) {
+        const uint32_t at = (i << 7) + part16;
+        return Row{gload(reinterpret_cast<const uint4*>(base + at)), gload(reinterpret_cast<const uint4*>(base + at + 64))};
+    };
+    auto dot = [](const Row& x, const Row& y, uint32_t c) {
+        c = __builtin_amdgcn_udot4(x.lo.x, y.lo.x, c, false);
+        c = __builtin_amdgcn_udot4(x.lo.y, y.lo.y, c, false);
+        c = __builtin_amdgcn_udot4(x.lo.z, y.lo.z, c, false);
+        c = __builtin_amdgcn_udot4(x.lo.w, y.lo.w, c, false);
+        c = __builtin_amdgcn_udot4(x.hi.x, y.hi.x, c, false);
+        c = __builtin_amdgcn_udot4(x.hi.y, y.hi.y, c, false);
+        c = __builtin_amdgcn_udot4(x.hi.z, y.hi.z, c, false);
+        return __builtin_amdgcn_udot4(x.hi.w, y.hi.w, c, false);
+    };
+    auto sum4 = [](uint32_t d) {
+        d += dpp<0xB1, 0xf>(d);         // quad_perm [1,0,3,2]
+        return d + dpp<0x4E, 0xf>(d);   // quad_perm [2,3,0,1]
+    };
+    int32_t f_d1 = 0, f_d2 = 0;
+    uint32_t f_j = 0, f_n = 0;
+    for (int r = 0; r < R; ++r) {
+        const int q = min(R * g + r, nq - 1);
+        const uint32_t kw = (uint32_t)__shfl((int)kept, q);
+        const uint32_t n = kw & 0xFFFFu;
+        const uint16_t* my = sel + (kw >> 16);
+        const Row av = row(qdesc, (uint32_t)(q0 + q));
+        // |b|^2 - 2 a.b of a candidate's row: the distance less |a|^2
+        auto rel = [&](const Row& b) {
+            return (int32_t)sum4(dot(b, b, (uint32_t)__mul24((int)dot(av, b, 0u), -2)));
+        };
+        int32_t best = INT32_MAX, sec = INT32_MAX;
+        uint32_t bj = 0;
+        auto take = [&](int32_t d, uint32_t j) {
+            sec = max(min(d, sec), min(best, max(d, sec)));  // the middle one of d, best <= sec
+            bj = d < best ? j : bj;
+            best = min(best, d);
+        };
+        // two candidates at a time while every query of the round has two
+        // more, then one at a time
+        uint32_t s = 0;
+        for (; __builtin_amdgcn_ballot_w64(s + 2 > n) == 0; s += 2) {
+            const uint32_t j0 = my[s], j1 = my[s + 1];
+            const Row b0 = row(tdesc, j0), b1 = row(tdesc, j1);
+            take(rel(b0), j0);
+            take(rel(b1), j1);
+        }
+        for (; __builtin_amdgcn_ballot_w64(s < n) != 0; ++s)
+            if (s < n) {
+                const uint32_t j = my[s];
+                take(rel(row(tdesc, j)), j);
+            }
+        // equal nearest and second: the smallest index among the nearest
+        if (__builtin_amdgcn_ballot_w64(best == sec && n > 1) != 0)
+            for (s = 0; __builtin_amdgcn_ballot_w64(s < n) != 0; ++s)
+                if (s < n) {
+                    const uint32_t j = my[s];
+                    if (rel(row(tdesc, j)) == best) bj = min(bj, j);
+                }
+        const int32_t aa = (int32_t)sum4(dot(av, av, 0u));
+        if (part == r) {
+            f_d1 = best + aa;
+            f_d2 = sec + aa;
+            f_j = bj;
+            f_n = n;
+        }
+    }
+    if (part < R && R * g + part < nq) {
+        int32_t r_idx = -1, r_d1 = -1, r_d2 = -1;
+        if (f_n >= 1) r_d1 = f_d1;
+        if (f_n >= 2) {
+            r_d2 = f_d2;
+            if (rare.den2 * (int64_t)r_d1 < rare.num2 * (int64_t)r_d2) r_idx = (int32_t)f_j;
+        }
+        const int64_t o = out + q0 + R * g + part;
+        gstore(rare.o_idx + o, r_idx);
+        gstore(rare.o_d1 + o, r_d1);
+        gstore(rare.o_d2 + o, r_d2);
+    }
+    wave_sync();
+}
+
+// ------------------------------------------------------------------ plain form
+
+// Inclusive rank structure of one query's six bucket runs in LDS (kRunWords +
+// 2 NC words per query, written by the tile setup), for the runs concatenated
+// in table order:
+//   words 2o, 2o+1  : of the o-th non-empty run (table t), the byte offset that
+//                     takes candidate e's 16 e to its entry's code, 16 (t n +
+//                     b_t - start), and the query's keys as table t's entries
+//                     are compared with them (see loaded_dup)
+//   words 12 ..     : per 64-candidate chunk u < NC the 64-bit mask of run
+//                     starts (bit j: a run other than the first starts at
+//                     candidate 64u + j + 1), so that a lane counts the starts
+//                     at or below its candidate, its run's ordinal, with mbcnt
+constexpr int kRunWords = 12;
+
+// Candidates kept per query on the way to its k nearest: at most kPassCap keys
+// pass the threshold, read back as up to three per lane.
+constexpr int kPassCap = 192;
+constexpr int kPassSlots = kPassCap / 64;
+// Keys the list in LDS holds, in front of select_64's histogram.
+constexpr int kListKeys = 320;
+
+// Entry word `kw` (see bucket_kernel) against the query's: the lanes whose
+// candidate shares no key of an earlier table with the query (one that does
+// is in that table's run already).  Bytes 0-3: the entry holds 0 in the bytes
+// of its own and later tables and the query word 0xFF there, so a zero byte of
+// the difference is a shared key of an earlier table.  Key 4 only matters to
+// table 5's entries; the others hold 0x100 in its 16 bits, which no key equals.
+__device__ __forceinline__ uint64_t first_seen(uint2 kw, uint32_t qlo, uint32_t q4) {
+    const uint32_t y = kw.x ^ qlo;
+    // bitop3 truth table 0x20 = a & ~b & c: the exact zero-byte test
+    const uint32_t z = __builtin_amdgcn_bitop3_b32(y - 0x01010101u, y, 0x80808080u, 0x20);
+    return __builtin_amdgcn_ballot_w64(z == 0u) & __builtin_amdgcn_ballot_w64((uint16_t)kw.y != (uint16_t)q4);
+}
+
+// The loads of C chunks of 64 candidates, all in flight together, then each
+// chunk's keys (Hamming << 16 | index) and whether the lane's candidate is a
+// valid one (inside the runs and not a repeat).  ORD: positions by the chunk
+// start masks (chunk u0 + c < NC); else by comparing with the run starts P.
+// Lanes past the last run read on from it, at most 63 entries past the last
+// table, which the caller's buffers allow, and are not valid.
+template <int C, bool ORD>
+struct Chunks {
+    uint32_t key[C];
+    uint64_t ok[C];  // lane masks
+    __device__ __forceinline__ void load(int lane, const char* code, const char* kid, const uint32_t* qrow, int u0,
+                                         uint32_t preq, const uint32_t (&P)[5], uint32_t total,
+                                         const uint32_t (&qc)[4]) {
+        uint2 run[C];
+        uint32_t off[C];
+        const uint32_t lane16 = (uint32_t)lane << 4;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            uint32_t o;
+            if constexpr (ORD) {
+                const uint2 sm = *reinterpret_cast<const uint2*>(qrow + kRunWords + 2 * (u0 + c));
+                const uint32_t o0 = (preq >> (3 * (u0 + c))) & 7u;
+                o = __builtin_amdgcn_mbcnt_hi(sm.y, __builtin_amdgcn_mbcnt_lo(sm.x, o0));
+            } else {
+                const uint32_t e = 64u * (uint32_t)(u0 + c) + (uint32_t)lane;
+                o = (uint32_t)(e >= P[0]) + (e >= P[1]) + (e >= P[2]) + (e >= P[3]) + (e >= P[4]);
+            }
+            run[c] = *reinterpret_cast<const uint2*>(qrow + 2 * o);
+            off[c] = run[c].x + lane16;
+        }
+        ulonglong2 cd[C];
+        uint2 kw[C];
+        const char* cb = code + 1024 * u0;
+        const char* kb = kid + 512 * u0;
+        // the last chunk's lanes inside the runs; only they load (the empty asm
+        // keeps every case's mask from being computed ahead of the switch)
+        int over = 64 * (u0 + C) - (int)total;
+        asm volatile("" : "+s"(over));
+        const uint64_t live = ~0ull >> max(over, 0);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (c + 1 < C || __builtin_amdgcn_inverse_ballot_w64(live)) {
+                cd[c] = gload(reinterpret_cast<const ulonglong2*>(cb + off[c] + 1024 * c));
+                kw[c] = gload(reinterpret_cast<const uint2*>(kb + (off[c] >> 1) + 512 * c));
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            uint32_t h = bcnt((uint32_t)cd[c].x ^ qc[0]);
+            h = bcnt_acc((uint32_t)(cd[c].x >> 32) ^ qc[1], h);
+            h = bcnt_acc((uint32_t)cd[c].y ^ qc[2], h);
+            h = bcnt_acc((uint32_t)(cd[c].y >> 32) ^ qc[3], h);
+            key[c] = __builtin_amdgcn_alignbyte(h, kw[c].y, 2);  // h << 16 | index
+            ok[c] = first_seen(kw[c], run[c].y, preq >> 24);
+            if (c + 1 == C) ok[c] &= live;
+        }
+    }
+};
+
+// Place of this lane, one of the mask's, behind the first n words of a list
+// (added to the list's address rather than to the count: one scalar operand
+// per instruction).
+template <class T>
+__device__ __forceinline__ T& list_at(T* list, uint32_t n, uint64_t m) {
+    return (list + n)[mbcnt64(m)];
+}
+
+// The same with the keys that pass the threshold (key <= K) appended to the
+// LDS list and counted in n_pass; n_union counts the valid candidates.
+template <int C, bool ORD>
+__device__ __forceinline__ void scan_chunks(int lane, const char* code, const char* kid, const uint32_t* qrow, int u0,
+                                            uint32_t preq, const uint32_t (&P)[5], uint32_t total,
+                                            const uint32_t (&qc)[4], uint32_t K, uint32_t* list, uint32_t& n_pass,
+                                            uint32_t& n_union) {
+    Chunks<C, ORD> ch;
+    ch.load(lane, code, kid, qrow, u0, preq, P, total, qc);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        n_union += (uint32_t)__popcll(ch.ok[c]);
+        const uint64_t m = ch.ok[c] & __builtin_amdgcn_ballot_w64(ch.key[c] <= K);
+        if (__builtin_amdgcn_inverse_ballot_w64(m)) list_at(list, n_pass, m) = ch.key[c];
+        n_pass += (uint32_t)__popcll(m);
+    }
+}
+
+// The kk smallest of the n listed keys (all <= K, distinct, n >= kk >= 1, S
+// registers per lane): their indices appended to the tile list.
+// Step 3: the Hamming distance H* of the kk-th by counting with ballots from
+// the previous query's H* (hG), ties there by index.
+template <int S>
+__device__ __forceinline__ void select_keys(const uint32_t* list, uint32_t n, uint32_t K, uint32_t kk, int lane,
+                                            uint16_t* sel, uint32_t& sel_n, int32_t& hG) {
+    uint32_t r[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const uint32_t v = list[64 * s + lane];
+        r[s] = 64u * s + (uint32_t)lane < n ? v : ~0u;
+    }
+    auto count = [&](uint32_t x) {  // listed keys <= x
+        uint32_t c = 0;
+#pragma unroll
+        for (int s = 0; s < S; ++s) c += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(r[s] <= x));
+        return c;
+    };
+    auto upto = [](int32_t h) { return ((uint32_t)h << 16) | 0xFFFFu; };
+    uint32_t tkey = K;
+    if (n > kk) {
+        int32_t lo = -1, hi = (int32_t)(K >> 16), step = 2;
+        uint32_t chi = n;  // keys of Hamming distance <= hi; fewer than kk at lo
+        const int32_t g = min(hG, hi - 1);
+        if (g >= 0) {
+            uint32_t c = count(upto(g));
+            if (c >= kk) {
+                hi = g;
+                chi = c;
+                while (hi - step > lo) {
+                    c = count(upto(hi - step));
+                    if (c < kk) {
+                        lo = hi - step;
                         break;
                     }
+                    hi -= step;
+                    chi = c;
+                    step += step;
                 }
-                if (cur >= end) break;  // every segment is exhausted
+            } else {
+                lo = g;
+                while (lo + step < hi) {
+                    c = count(upto(lo + step));
+                    if (c >= kk) {
+                        hi = lo + step;
+                        chi = c;
+                        break;
+                    }
+                    lo += step;
+                    step += step;
+                }
             }
-            it = cur++;
         }
+        while (hi - lo > 1) {
+            const int32_t mid = (lo + hi) >> 1;
+            const uint32_t c = count(upto(mid));
+            if (c >= kk) {
+                hi = mid;
+                chi = c;
+            } else {
+                lo = mid;
+            }
+        }
+        hG = hi;
+        tkey = min(K, upto(hi));
+        if (chi > kk) {
+            // more at H* than needed: the one with exactly kk keys up to it
+            const uint32_t at = (uint32_t)hi << 16, top = tkey;
+            bool found = false;
+            tkey = max(at, 1u) - 1u;
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                if (found) break;
+                uint64_t m = __builtin_amdgcn_ballot_w64(r[s] >= at) & __builtin_amdgcn_ballot_w64(r[s] <= top);
+                while (m != 0) {
+                    const uint32_t x = readlane(r[s], __ffsll((unsigned long long)m) - 1);
+                    if (count(x) == kk) {
+                        tkey = x;
+                        found = true;
+                        break;
+                    }
+                    m &= m - 1;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const bool keep = r[s] <= tkey;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+        if (keep) list_at(sel, sel_n, m) = (uint16_t)r[s];
+        sel_n += (uint32_t)__popcll(m);
+    }
+}
+
+// select_keys for at most 64 listed keys, one per lane: H* from a histogram
+// over the 64 Hamming distances around the last H* (the paper's index table;
+// hist: 64 cleared words of LDS, left cleared), scanned with DPP.  An H* at
+// the ends of that window takes the counting form above.
+__device__ __forceinline__ void select_64(const uint32_t* list, uint32_t* hist, uint32_t n, uint32_t K, uint32_t kk,
+                                          int lane, uint16_t* sel, uint32_t& sel_n, int32_t& hG) {
+    const uint32_t v = list[lane];
+    const uint32_t r = (uint32_t)lane < n ? v : ~0u;
+    uint32_t tkey = K;
+    if (n > kk) {
+        const int32_t base = hG - 32;
+        const int32_t bin = min(max((int32_t)(r >> 16) - base, 0), 63);
+        if ((uint32_t)lane < n) atomicAdd(hist + bin, 1u);
+        wave_sync();
+        const uint32_t incl = wave_scan_dpp(hist[lane]);
+        hist[lane] = 0u;
+        const uint64_t reach = __builtin_amdgcn_ballot_w64(incl >= kk);
+        int L = __builtin_ctzll(reach);  // some bin reaches kk: n > kk
+        asm("" : "+s"(L));               // a 32-bit value: the compare below stays scalar
+        if ((uint32_t)(L - 1) >= 62u) {
+            select_keys<1>(list, n, K, kk, lane, sel, sel_n, hG);
+            return;
+        }
+        hG = base + L;
+        const uint32_t at = (uint32_t)hG << 16;
+        tkey = min(K, at | 0xFFFFu);
+        if (readlane(incl, L) > kk) {
+            // more at H* than needed: the one with exactly kk keys up to it
+            uint64_t m = __builtin_amdgcn_ballot_w64(r >= at) & __builtin_amdgcn_ballot_w64(r <= tkey);
+            tkey = max(at, 1u) - 1u;
+            while (m != 0) {
+                const int l = __builtin_ctzll(m);
+                const uint32_t x = readlane(r, l);
+                if ((uint32_t)__popcll(__builtin_amdgcn_ballot_w64(r <= x)) == kk) {
+                    tkey = x;
+                    break;
+                }
+                m ^= 1ull << l;
+            }
+        }
+    }
+    const bool keep = r <= tkey;
+    const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+    if (keep) list_at(sel, sel_n, m) = (uint16_t)r;
+    sel_n += (uint32_t)__popcll(m);
+}
+
+// The run starts of a lane's query (~0u: no run, or the first one), needed only
+// past the chunk masks: one word each, or as halves of three words for trains
+// whose starts fit 16 bits (NC == 4: at most 6 kLargeTrain entries).
+template <int NC>
+constexpr int kStartWords = NC == 4 ? 3 : 5;
+static_assert(kTables * kLargeTrain < 0xFFFF, "run starts fit 16 bits");
+template <int W>
+__device__ __forceinline__ void put_start(uint32_t (&v)[W], int i, uint32_t start) {
+    if constexpr (W == 5)
+        v[i] = start;
+    else
+        v[i >> 1] = i & 1 ? v[i >> 1] | (start << 16) : start & 0xFFFFu;
+}
+template <int W>
+__device__ __forceinline__ void run_starts(uint32_t (&P)[5], const uint32_t (&v)[W], int qi) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        if constexpr (W == 5)
+            P[i] = readlane(v[i], qi);
+        else
+            P[i] = i & 1 ? readlane(v[i >> 1], qi) >> 16 : readlane(v[i >> 1], qi) & 0xFFFFu;
+    }
+}
+
+// A query's threshold on its candidates' keys.  settled(): the number that
+// passed is right (at least k, or all, and no more than the selection takes);
+// else the threshold moves, by steps until both sides are known and then by
+// halves.  Keys are distinct, so some threshold settles (the last line only
+// ends the search if the buffers change under the kernel).
+struct Threshold {
+    uint32_t K;
+    int32_t klo = -1, khi = INT32_MAX;  // too few pass klo, too many khi
+    __device__ __forceinline__ bool settled(uint32_t n_pass, uint32_t k, uint32_t tauK) {
+        if (n_pass >= k ? n_pass <= (uint32_t)kPassCap : K == tauK) return true;
+        if (n_pass < k) {
+            klo = (int32_t)K;
+            K = khi != INT32_MAX ? (uint32_t)(klo + ((khi - klo) >> 1)) : min(tauK, K + (6u << 16));
+        } else {
+            khi = (int32_t)K;
+            K = klo >= 0 || khi < (4 << 16) ? (uint32_t)(klo + ((khi - klo) >> 1)) : K - (4u << 16);
+        }
+        return khi - klo <= 1;
+    }
+};
+
+// The plain form.  Per query: the six runs' candidates in 64-wide chunks, up to
+// four chunks' loads in flight together, the keys that pass the threshold to
+// the LDS list, then the selection.  A threshold that lets too few or too many
+// pass is moved and the runs are read again (a few queries in a thousand: the
+// list takes up to 192 keys, and the k-th distance varies by a few bits).  So no
+// candidate is kept in a register past its chunk, the number of chunks has no
+// limit, and the ranking works on one register per lane instead of one per
+// chunk.  NC: chunks with start masks.
+//
+// What bounds it (100 x 8000 points, rocprofv3): issue, vector and scalar alike,
+// and L2 next to it.  Per query 149 VALU and 147 SALU instructions (213 and 132
+// when every candidate was kept in registers, ranked by an index table over all
+// of them and compacted from them) at about 0.73 of either pipe's rate, and 60
+// L2 lines, 0.75 of what a plain read of such runs gets from L2 here (29 TB/s).
+// Against that form: 100 x 8000 points 15.5 -> 13.3 ms, 16 x 20000 3.65 -> 1.7 ms
+// (half of its queries had more candidates than its eight registers).
+template <int NC>
+__global__ __launch_bounds__(256, match_blocks_per_cu(false, NC)) void plain_match_kernel(
+    const ImgDev* __restrict__ imgs, const PairDev* __restrict__ pairs, const Item* __restrict__ items,
+    int32_t n_items, uint32_t* __restrict__ ctl, MatchParams prm, int32_t* __restrict__ o_idx,
+    int32_t* __restrict__ o_d1, int32_t* __restrict__ o_d2) {
+    constexpr int kQS = kRunWords + 2 * NC;
+    __shared__ __attribute__((aligned(16))) uint32_t s_list[kWavesPerBlock][kListKeys + 64];
+    __shared__ __attribute__((aligned(16))) uint16_t s_sel[kWavesPerBlock][kSelCap];
+    __shared__ __attribute__((aligned(16))) uint32_t s_qtab[kWavesPerBlock][kMaxTile * kQS];
+    __shared__ Rare s_rare;
+    if (threadIdx.x == 0) s_rare.fill(prm, ctl, o_idx, o_d1, o_d2);
+    __syncthreads();
+    const bool persistent = prm.grab > 0;
+    const int lane = threadIdx.x & 63;
+    const int wv = (int)uniform(threadIdx.x >> 6);
+    uint32_t* list = s_list[wv];
+    uint32_t* hist = list + kListKeys;
+    uint16_t* sel = s_sel[wv];
+    uint32_t* qtab = s_qtab[wv];
+    hist[lane] = 0u;
+    uint64_t st_bucket = 0, st_ranked = 0;  // per lane
+    uint64_t st_union = 0;                   // uniform
+    const uint32_t tauK = ((uint32_t)prm.tau << 16) | 0xFFFFu;
+    int32_t hT = 56, hG = 52;  // threshold for the next query; the last query's H*
+
+    Grab grab;
+    int32_t it = (int32_t)(blockIdx.x * kWavesPerBlock + wv);
+    for (;;) {
+        if (persistent && !grab.next(s_rare, lane, it)) break;
         if (it >= n_items) break;
         const Item item = items[it];
         const PairDev& pr = pairs[item.pair];
         const ImgDev Q = imgs[pr.qi];
         const ImgDev T = imgs[pr.ti];
-        TrainView tv;
-        tv.n = T.n;
-        tv.code = reinterpret_cast<const ulonglong2*>(T.ent);
-        tv.kid = reinterpret_cast<const uint64_t*>(T.ent + (size_t)kTables * T.n * 16);
-        tv.kp = reinterpret_cast<const float2*>(T.ent + (size_t)kTables * T.n * 24);
+        const char* code = reinterpret_cast<const char*>(T.ent);
+        const char* kid = code + (size_t)kTables * T.n * 16;
         const int nq = (int)uniform((uint32_t)item.nq);
         const int32_t q0 = (int32_t)uniform((uint32_t)item.q0);
 
         // ---- setup, one lane per query of the tile
-        const int64_t lq = q0 + min(lane, nq - 1);
-        const uint64_t v_qc0 = gload(Q.codes + 2 * lq), v_qc1 = gload(Q.codes + 2 * lq + 1);
-        const uint16_t* kq = reinterpret_cast<const uint16_t*>(Q.keys + 6 * lq);
-        const uint64_t v_qk = (uint64_t)gload(kq) | ((uint64_t)gload(kq + 1) << 16) | ((uint64_t)gload(kq + 2) << 32);
-        // v_P[0..4]: the run starts P1..P5 (see QueryRuns); v_P[5]: bucket entries
-        uint32_t v_P[kTables];
+        uint32_t v_P[kStartWords<NC>], v_total, v_preq;
+        uint4 v_code;
         {
-            // the previous tile's readers are done (the finalize step ended with a wave sync)
-            uint32_t* qt = qtab + kQS * lane;
-            const bool own = lane < kMaxTile;
-            if constexpr (kMask) {
-                if (own) {
-#pragma unroll
-                    for (int i = 0; i < NS / 2; ++i) reinterpret_cast<uint4*>(qt + 8)[i] = make_uint4(0u, 0u, 0u, 0u);
-                }
-            }
-            uint32_t acc = 0, cnt = 0, cu[kTables];  // entries and non-empty runs before table t
-            uint32_t pre = 0;                         // run starts at or below 64, 128, ... (3 bits each)
+            const int64_t lq = q0 + min(lane, nq - 1);
+            // (8-byte aligned)
+            const uint2 c0 = gload(reinterpret_cast<const uint2*>(Q.codes + 2 * lq));
+            const uint2 c1 = gload(reinterpret_cast<const uint2*>(Q.codes + 2 * lq + 1));
+            v_code = make_uint4(c0.x, c0.y, c1.x, c1.y);
+            const uint16_t* kq = reinterpret_cast<const uint16_t*>(Q.keys + 6 * lq);
+            const uint32_t k01 = gload(kq), k23 = gload(kq + 1), k45 = gload(kq + 2);
+            const uint32_t qlo = k01 | (k23 << 16);
+            uint32_t b[kTables], e[kTables];
 #pragma unroll
             for (int t = 0; t < kTables; ++t) {
-                const uint32_t v = (uint32_t)((v_qk >> (8 * t)) & 0xFFu);
-                const uint32_t b = gload(T.off + t * kOffStride + v);
-                const uint32_t len = gload(T.off + t * kOffStride + v + 1) - b;
-                const uint32_t start = acc;
-                cu[t] = (uint32_t)t * (uint32_t)T.n + b - start;  // candidate e of run t: entry e + cu[t]
-                if constexpr (kMask) {
-                    if (t > 0) v_P[t - 1] = (len != 0 && cnt != 0) ? start : ~0u;
-                    if (len != 0) {
-                        if (own) qt[cnt] = (cu[t] << 10) | (8u * (uint32_t)t);
-                        if (own && cnt != 0 && start <= 64u * NS)
-                            atomicOr(qt + 8 + ((start - 1u) >> 5), 1u << ((start - 1u) & 31u));
-                        if (cnt != 0) {
+                const uint32_t v = ((t < 4 ? qlo >> (8 * t) : k45 >> (8 * (t - 4)))) & 0xFFu;
+                b[t] = gload(T.off + t * kOffStride + v);
+                e[t] = gload(T.off + t * kOffStride + v + 1);
+            }
+            uint32_t* qt = qtab + kQS * lane;
+            const bool own = lane < kMaxTile;
+            if (own) {
 #pragma unroll
-                            for (int bnd = 1; bnd < NS; ++bnd) pre += (uint32_t)(start <= 64u * bnd) << (3 * (bnd - 1));
-                        }
-                        ++cnt;
-                    }
-                } else if (t > 0) {
-                    v_P[t - 1] = start;
-                }
+                for (int i = 0; i < NC / 2; ++i)
+                    reinterpret_cast<uint4*>(qt + kRunWords)[i] = make_uint4(0u, 0u, 0u, 0u);
+            }
+            uint32_t acc = 0, cnt = 0;  // entries and non-empty runs before table t
+            uint32_t pre = 0;           // run starts at or below 64u, at bits 3u
+#pragma unroll
+            for (int t = 0; t < kTables; ++t) {
+                const uint32_t len = e[t] - b[t];
+                const bool inner = len != 0 && cnt != 0;  // a run start after the first
+                if (t > 0) put_start(v_P, t - 1, inner ? acc : ~0u);
+                if (own && len != 0)
+                    *reinterpret_cast<uint2*>(qt + 2 * cnt) =
+                        make_uint2(((uint32_t)t * (uint32_t)T.n + b[t] - acc) << 4, t < 4 ? qlo | (~0u << (8 * t)) : qlo);
+                if (own && inner && acc <= 64u * NC)
+                    atomicOr(qt + kRunWords + ((acc - 1u) >> 5), 1u << ((acc - 1u) & 31u));
+#pragma unroll
+                for (int u = 1; u < NC; ++u) pre += (uint32_t)(inner && acc <= 64u * u) << (3 * u);
+                cnt += len != 0;
                 acc += len;
             }
-            v_P[kTables - 1] = acc;
-            // the query's keys: bytes 0-3 in qt[7], bytes 4-5 in the high half of qt[6]
-            const uint32_t khi = (uint32_t)(v_qk >> 32) << 16;
-            if constexpr (!kMask) {
-                if (own) {
-                    reinterpret_cast<uint4*>(qt)[0] = make_uint4(cu[0], cu[1], cu[2], cu[3]);
-                    reinterpret_cast<uint4*>(qt)[1] = make_uint4(cu[4], cu[5], khi, (uint32_t)v_qk);
+            if (lane < nq) st_bucket += acc;
+            v_total = acc;
+            v_preq = pre | (k45 << 24);  // and key 4 above it
+            wave_sync();
+        }
+        uint32_t sel_n = 0;
+        uint32_t v_kept = 0;  // lane qi: its kept count and first tile-list slot
+        uint32_t t_union = 0;
+
+        for (int qi = 0; qi < nq; ++qi) {
+            // from lane qi (a load at a wave-uniform address would take as many
+            // L1 accesses as one of 64 codes)
+            const uint32_t qc[4] = {readlane(v_code.x, qi), readlane(v_code.y, qi), readlane(v_code.z, qi),
+                                    readlane(v_code.w, qi)};
+            const uint32_t total = readlane(v_total, qi), preq = readlane(v_preq, qi);
+            const uint32_t* qrow = qtab + kQS * qi;
+            const int nch = (int)((total + 63u) >> 6);
+            Threshold th{nch > 1 ? min(tauK, ((uint32_t)hT << 16) | 0xFFFFu) : tauK};
+            uint32_t n_pass, n_union;
+            for (;;) {
+                n_pass = n_union = 0;
+                const uint32_t noP[5] = {0, 0, 0, 0, 0};
+#define SCAN(C, ORD, U, P) scan_chunks<C, ORD>(lane, code, kid, qrow, U, preq, P, total, qc, th.K, list, n_pass, n_union)
+                switch (min(nch, 4)) {
+                    case 0: break;
+                    case 1: SCAN(1, true, 0, noP); break;
+                    case 2: SCAN(2, true, 0, noP); break;
+                    case 3: SCAN(3, true, 0, noP); break;
+                    default: SCAN(4, true, 0, noP); break;
                 }
-            } else if (own) {
-                reinterpret_cast<uint2*>(qt + 6)[0] = make_uint2(pre | khi, (uint32_t)v_qk);
+                // further chunks, four or two at a time while the list has
+                // room for all their candidates
+#pragma unroll 1
+                for (int u0 = 4; u0 < nch;) {
+                    if (n_pass > (uint32_t)kPassCap) break;  // too many already
+                    const int c = min(nch - u0, n_pass <= (uint32_t)kListKeys - 256u ? 4 : 2);
+                    if (NC > 4 && u0 + c <= NC) {
+                        switch (c) {
+                            case 1: SCAN(1, true, u0, noP); break;
+                            case 2: SCAN(2, true, u0, noP); break;
+                            case 3: SCAN(3, true, u0, noP); break;
+                            default: SCAN(4, true, u0, noP); break;
+                        }
+                        u0 += c;
+                    } else {
+                        uint32_t P[5];
+                        run_starts(P, v_P, qi);
+                        if (c >= 2) {
+                            SCAN(2, false, u0, P);
+                            u0 += 2;
+                        } else {
+                            SCAN(1, false, u0, P);
+                            u0 += 1;
+                        }
+                    }
+                }
+#undef SCAN
+                if (th.settled(n_pass, (uint32_t)prm.k, tauK)) break;
+                hT = (int32_t)(th.K >> 16);
+            }
+            wave_sync();
+            t_union += n_union;
+            const uint32_t kk = min(n_pass, (uint32_t)prm.k);
+            v_kept = lane == qi ? kk | (sel_n << 16) : v_kept;
+            if (kk == 0) continue;
+            if (n_pass <= 64u) {
+                select_64(list, hist, n_pass, th.K, kk, lane, sel, sel_n, hG);
+            } else {
+                select_keys<kPassSlots>(list, n_pass, th.K, kk, lane, sel, sel_n, hG);
+                hT = max(hT - 1, 4);
             }
             wave_sync();
         }
-        if constexpr (EPI) {
-            // the query's epipolar line F x, kept in its run table (words
-            // 8-13) rather than in registers for the whole tile
+        if (lane < nq) {
+            st_ranked += v_kept & 0xFFFFu;
+        }
+        st_union += t_union;
+        finish_tile(lane, nq, q0, Q.desc, T.desc, pr.out, v_kept, sel, s_rare);
+        if (!persistent) break;
+    }
+    for (int d = 32; d >= 1; d >>= 1) {
+        st_bucket += __shfl_xor(st_bucket, d);
+        st_ranked += __shfl_xor(st_ranked, d);
+    }
+    if (lane == 0) s_rare.add_stats(st_bucket, st_union, st_ranked);
+}
+
+// ------------------------------------------------------------------ band form (Eq. 1-2)
+
+// Run words per query in LDS: the first place of table t's run (t stride + b_t),
+// its length, then the epipolar line's three binary64 coefficients.
+constexpr int kBandWords = 12 + 6;
+// Places of the candidates inside the band held in LDS; more take the full scan.
+constexpr int kBandCap = 256;
+
+// The band form: keypoints of all six runs first, the few candidates inside the
+// band (about 1%) read in full and kept, or ranked as in the plain form when
+// there are more than k.
+
+__global__ __launch_bounds__(256, match_blocks_per_cu(true, 4)) void band_match_kernel(const ImgDev* __restrict__ imgs,
+                                                            const PairDev* __restrict__ pairs,
+                                                            const Item* __restrict__ items, int32_t n_items,
+                                                            uint32_t* __restrict__ ctl, MatchParams prm,
+                                                            int32_t* __restrict__ o_idx, int32_t* __restrict__ o_d1,
+                                                            int32_t* __restrict__ o_d2) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_place[kWavesPerBlock][kBandCap];
+    __shared__ __attribute__((aligned(16))) uint32_t s_list[kWavesPerBlock][kListKeys + 64];
+    __shared__ __attribute__((aligned(16))) uint16_t s_sel[kWavesPerBlock][kSelCap];
+    __shared__ __attribute__((aligned(16))) uint32_t s_qtab[kWavesPerBlock][kMaxTile * kBandWords];
+    __shared__ Rare s_rare;
+    if (threadIdx.x == 0) s_rare.fill(prm, ctl, o_idx, o_d1, o_d2);
+    __syncthreads();
+    const bool persistent = prm.grab > 0;
+    const int lane = threadIdx.x & 63;
+    const int wv = (int)uniform(threadIdx.x >> 6);
+    uint32_t* place = s_place[wv];
+    uint32_t* list = s_list[wv];
+    uint32_t* hist = list + kListKeys;
+    uint16_t* sel = s_sel[wv];
+    uint32_t* qtab = s_qtab[wv];
+    hist[lane] = 0u;
+    uint64_t st_bucket = 0, st_ranked = 0;  // per lane
+    uint64_t st_union = 0;                   // uniform
+    const uint32_t tauK = ((uint32_t)prm.tau << 16) | 0xFFFFu;
+    const double dd = prm.max_px * prm.max_px;
+    int32_t hG = 52;  // the last ranked query's H*
+
+    Grab grab;
+    int32_t it = (int32_t)(blockIdx.x * kWavesPerBlock + wv);
+    for (;;) {
+        if (persistent && !grab.next(s_rare, lane, it)) break;
+        if (it >= n_items) break;
+        const Item item = items[it];
+        const PairDev& pr = pairs[item.pair];
+        const ImgDev Q = imgs[pr.qi];
+        const ImgDev T = imgs[pr.ti];
+        const char* code = reinterpret_cast<const char*>(T.ent);
+        const char* kid = code + (size_t)kTables * T.n * 16;
+        const char* kps = code + (size_t)kTables * T.n * 24;
+        const int nq = (int)uniform((uint32_t)item.nq);
+        const int32_t q0 = (int32_t)uniform((uint32_t)item.q0);
+
+        // ---- setup, one lane per query of the tile
+        uint32_t v_qlo, v_q4;
+        uint4 v_code;
+        {
+            const int64_t lq = q0 + min(lane, nq - 1);
+            const uint2 c0 = gload(reinterpret_cast<const uint2*>(Q.codes + 2 * lq));
+            const uint2 c1 = gload(reinterpret_cast<const uint2*>(Q.codes + 2 * lq + 1));
+            v_code = make_uint4(c0.x, c0.y, c1.x, c1.y);
+            const uint16_t* kq = reinterpret_cast<const uint16_t*>(Q.keys + 6 * lq);
+            const uint32_t k01 = gload(kq), k23 = gload(kq + 1), k45 = gload(kq + 2);
+            v_qlo = k01 | (k23 << 16);
+            v_q4 = k45 & 0xFFu;
+            uint32_t b[kTables], e[kTables];
+#pragma unroll
+            for (int t = 0; t < kTables; ++t) {
+                const uint32_t v = ((t < 4 ? v_qlo >> (8 * t) : k45 >> (8 * (t - 4)))) & 0xFFu;
+                b[t] = gload(T.off + t * kOffStride + v);
+                e[t] = gload(T.off + t * kOffStride + v + 1);
+            }
             const double x = (double)gload(Q.kp + 2 * lq), y = (double)gload(Q.kp + 2 * lq + 1);
             const double la = (pr.F[0] * x + pr.F[1] * y) + pr.F[2];
             const double lb = (pr.F[3] * x + pr.F[4] * y) + pr.F[5];
             const double lc = (pr.F[6] * x + pr.F[7] * y) + pr.F[8];
-            if (lane < kMaxTile) {
-                double* ql = reinterpret_cast<double*>(qtab + kQS * lane + 8);
+            uint32_t* qt = qtab + kBandWords * lane;
+            const bool own = lane < kMaxTile;
+            uint32_t entries = 0;
+#pragma unroll
+            for (int t = 0; t < kTables; ++t) {
+                const uint32_t len = e[t] - b[t];
+                if (own)
+                    *reinterpret_cast<uint2*>(qt + 2 * t) = make_uint2((uint32_t)t * (uint32_t)T.n + b[t], len);
+                entries += len;
+            }
+            if (own) {
+                double* ql = reinterpret_cast<double*>(qt + 12);
                 ql[0] = la;
                 ql[1] = lb;
                 ql[2] = lc;
             }
+            if (lane < nq) st_bucket += entries;
             wave_sync();
         }
-        uint32_t sel_n = 0;
-        const uint32_t jbits = tv.n > 1 ? 32u - (uint32_t)__clz(tv.n - 1) : 0u;
+        uint32_t sel_n = 0, t_union = 0;
+        uint32_t v_kept = 0;  // lane qi: its kept count and first place in sel
 
-        // plain kernels: the next query's code (a wave-uniform address) is
-        // loaded while the current query is ranked
-        uint64_t nc0 = 0, nc1 = 0;
-        const ulonglong2* qcodes = reinterpret_cast<const ulonglong2*>(Q.codes);
-        if constexpr (!EPI) {
-            const ulonglong2 c = gload(qcodes + q0);
-            nc0 = c.x;
-            nc1 = c.y;
-        }
         for (int qi = 0; qi < nq; ++qi) {
-            QueryRuns qr;
+            const uint32_t* qrow = qtab + kBandWords * qi;
+            uint32_t rb[kTables], rl[kTables];  // run start and length, uniform
+#pragma unroll
+            for (int t = 0; t < kTables; ++t) {
+                const uint2 v = *reinterpret_cast<const uint2*>(qrow + 2 * t);
+                rb[t] = uniform(v.x);
+                rl[t] = uniform(v.y);
+            }
+            const double* ql = reinterpret_cast<const double*>(qrow + 12);
+            const double la = ql[0], lb = ql[1], lc = ql[2];
+            // band first: only keypoints are read for every bucket entry; the
+            // ~1% inside the band are compacted (table, place) into LDS and
+            // only they are read in full.  The runs are walked one by one, so
+            // a run's table is known and its entries are consecutive: first
+            // the leading 64 entries of all six with their keypoint loads in
+            // flight together, then the rest of any longer run.
+            // Eq. 1-2 for 64 keypoints at once: the compare's lane mask itself
+            // (no branch), ANDed with the run's lanes.  Lanes past the run
+            // read the entries after it: at most 64 past the keypoints of the
+            // last table, inside the 512 bytes kept after the tables.
+            const double rhs = dd * (la * la + lb * lb);
+            auto kp_at = [&](uint32_t pos) { return gload(reinterpret_cast<const float2*>(kps + (pos << 3))); };
+            auto in_band = [&](float2 kp) {
+                const double xp = (double)kp.x, yp = (double)kp.y;
+                const double ev = (la * xp + lb * yp) + lc;
+                return ev * ev <= rhs;
+            };
+            uint32_t n_surv = 0;
+            auto band_chunk = [&](int t, uint32_t i0, float2 kp, uint32_t pos) {
+                const bool in = in_band(kp);
+                const bool in_run = i0 + (uint32_t)lane < rl[t];
+                const uint64_t mk = __builtin_amdgcn_ballot_w64(in) & __builtin_amdgcn_ballot_w64(in_run);
+                if (mk != 0) {  // wave-uniform; most chunks have no survivor
+                    const uint32_t sl = n_surv + mbcnt64(mk);
+                    // a lane's own survival from its compares, not from its
+                    // bit of mk (no 64-bit shift and test per lane)
+                    if (in && in_run && sl < (uint32_t)kBandCap) place[sl] = ((8u * (uint32_t)t) << 24) | pos;
+                    n_surv += (uint32_t)__popcll(mk);
+                }
+            };
             {
-                // the query's code; its keys: from the run table, where the
-                // tile setup left them
-                if constexpr (EPI) {
-                    const ulonglong2 c = gload(qcodes + ((int64_t)q0 + qi));
-                    qr.qc0 = c.x;
-                    qr.qc1 = c.y;
-                } else {
-                    qr.qc0 = nc0;
-                    qr.qc1 = nc1;
-                }
-                const uint2 kw = *reinterpret_cast<const uint2*>(qtab + kQS * qi + 6);
-                qr.qk = (uint64_t)kw.y | ((uint64_t)(kw.x >> 16) << 32);
+                uint32_t ps[kTables];
+                float2 kp[kTables];
+#pragma unroll
+                for (int t = 0; t < kTables; ++t) ps[t] = rb[t] + (uint32_t)lane;
+#pragma unroll
+                for (int t = 0; t < kTables; ++t) kp[t] = kp_at(ps[t]);
+#pragma unroll
+                for (int t = 0; t < kTables; ++t) band_chunk(t, 0u, kp[t], ps[t]);
             }
-            // run boundaries P1..P5 only meet per-lane compares: broadcast into
-            // vector registers (the kernel is short of scalar registers);
-            // P6 bounds the loops and stays scalar.  The masked plain kernels
-            // find runs by the chunk masks and need P1..P5 only when the runs
-            // exceed their register slots: there a copy of the query's view
-            // with them (runs_keyed) is made where it is read, so that no
-            // register holds them across the common path.
-            auto bounds = [&]() {
-                qr.P1 = __shfl(v_P[0], qi); qr.P2 = __shfl(v_P[1], qi); qr.P3 = __shfl(v_P[2], qi);
-                qr.P4 = __shfl(v_P[3], qi); qr.P5 = __shfl(v_P[4], qi);
-            };
-            auto runs_keyed = [&]() -> QueryRuns {
-                if constexpr (kMask) {
-                    QueryRuns q = qr;
-                    q.P1 = __shfl(v_P[0], qi); q.P2 = __shfl(v_P[1], qi); q.P3 = __shfl(v_P[2], qi);
-                    q.P4 = __shfl(v_P[3], qi); q.P5 = __shfl(v_P[4], qi);
-                    return q;
-                } else {
-                    return qr;
-                }
-            };
-            if constexpr (!kMask && !EPI) bounds();
-            qr.P6 = readlane(v_P[5], qi);
-            qr.qtab = qtab + kQS * qi;
-            if constexpr (EPI) {
-                const double* ql = reinterpret_cast<const double*>(qtab + kQS * qi + 8);
-                qr.la = ql[0];
-                qr.lb = ql[1];
-                qr.lc = ql[2];
-            } else {
-                qr.la = qr.lb = qr.lc = 0.0;
-            }
-            const uint32_t total = qr.P6;
-            st_bucket += total;
-
-            // ---- Steps 1-3, gather: union, Hamming, tau, band; index table
-            // (the histogram over Hamming distance; built during the gather,
-            // except on the band path, where few candidates survive and it is
-            // built only when more than k do)
-            uint32_t n_valid = 0;
-            constexpr uint32_t kRegCap = 64u * NS;
-            uint32_t kr[NS];  // candidate keys held in registers (up to kRegCap)
 #pragma unroll
-            for (int u = 0; u < NS; ++u) kr[u] = ~0u;
-            uint32_t n_slots = 0;  // register slots that hold candidates (the rest stay ~0u)
-            // the 8-slot kernel and the band kernel (whose slots hold only
-            // the band's few survivors) skip empty slots in the ranking and
-            // compaction loops; the 4-slot plain kernel keeps no slot count
-            // (its slots are nearly always full, and the count would take it
-            // past 80 VGPRs, the limit for six wavefronts per SIMD)
-            constexpr bool kSkipEmpty = NS > 4 || EPI;
-            // ties needing at most this many picks are ranked by repeated
-            // wave minima (plain kernels, keys in registers)
-            constexpr uint32_t kMinRounds = 4u;
-            bool in_regs = true;
-            bool gathered = false;
-            bool hist_built = true;  // false: the index table still has to be built from kr
-            if (total == 0) {
-                gathered = true;  // no candidate: nothing to read (the image may have no entries)
-            } else if constexpr (EPI) {
-                // band first: only keypoints are read for every bucket entry;
-                // the ~1% inside the band are compacted (table, position) into
-                // the LDS list and only they are read in full
-                // The pass walks the six runs one by one, so a run's table t
-                // is known and its entries are consecutive: first the leading
-                // 64 entries of all six runs with their keypoint loads in
-                // flight together, then the rest of any longer run.  (The
-                // survivors' order differs from the concatenated order; their
-                // keys are ranked by (H, index), which does not depend on it.)
-                uint32_t n_surv = 0;
-                uint32_t rb[kTables], rl[kTables];  // run start in the table; run length
-                {
-                    // uniform per query: scalar registers (readlane of the
-                    // per-lane starts, the run table read once)
-                    const uint32_t st[kTables + 1] = {0u, readlane(v_P[0], qi), readlane(v_P[1], qi),
-                                                      readlane(v_P[2], qi), readlane(v_P[3], qi),
-                                                      readlane(v_P[4], qi), qr.P6};
-#pragma unroll
-                    for (int t = 0; t < kTables; ++t) {
-                        rl[t] = st[t + 1] - st[t];
-                        rb[t] = readfirstlane_u32(qr.qtab[t]) + st[t];
-                    }
-                }
-                // Eq. 1-2 for 64 keypoints at once: the compare's lane mask
-                // itself (no branch), ANDed with the run's lanes (a vector
-                // compare: cheaper here than building the mask from the run
-                // length with scalar shifts).  Lanes past the run read the
-                // entries after it, unclamped: at most 64 entries past the
-                // keypoints of the last table, inside the 512 bytes the
-                // tables of a band call keep at their end; their results are
-                // masked out
-                const double rhs = dd * (qr.la * qr.la + qr.lb * qr.lb);
-                // keypoint of entry pos: a 32-bit byte offset from the table's
-                // base (the scalar-base load form, no 64-bit address per lane)
-                auto kp_at = [&](uint32_t pos) {
-                    return reinterpret_cast<const float2*>(reinterpret_cast<const char*>(tv.kp) + (pos << 3));
-                };
-                auto band_chunk = [&](int t, uint32_t i0, float2 kp, uint32_t pos) {
-                    const double xp = (double)kp.x, yp = (double)kp.y;
-                    const double ev = (qr.la * xp + qr.lb * yp) + qr.lc;
-                    const bool in_run = i0 + (uint32_t)lane < rl[t];
-                    const bool in_band = ev * ev <= rhs;
-                    const uint64_t mk = __builtin_amdgcn_ballot_w64(in_band) & __builtin_amdgcn_ballot_w64(in_run);
-                    if (mk != 0) {  // wave-uniform; most chunks have no survivor
-                        const uint32_t sl = n_surv + mbcnt64(mk);
-                        // a lane's own survival from its compares, not from
-                        // its bit of mk (no 64-bit shift and test per lane)
-                        if (in_band && in_run && sl < (uint32_t)kLC)
-                            list[sl] = ((8u * (uint32_t)t) << 24) | pos;
-                        n_surv += (uint32_t)__popcll(mk);
-                    }
-                };
-                {
-                    uint32_t ps[kTables];
-                    float2 kp[kTables];
-#pragma unroll
-                    for (int t = 0; t < kTables; ++t) ps[t] = rb[t] + (uint32_t)lane;
-#pragma unroll
-                    for (int t = 0; t < kTables; ++t) kp[t] = gload(kp_at(ps[t]));
-#pragma unroll
-                    for (int t = 0; t < kTables; ++t) band_chunk(t, 0u, kp[t], ps[t]);
-                }
-#pragma unroll
-                for (int t = 0; t < kTables; ++t) {
-                    const uint32_t len = readfirstlane_u32(rl[t]);
-                    for (uint32_t i0 = 64; i0 < len; i0 += 64) {
-                        const uint32_t pos = rb[t] + i0 + (uint32_t)lane;
-                        band_chunk(t, i0, gload(kp_at(pos)), pos);
-                    }
-                }
-                wave_sync();
-                if (n_surv <= kRegCap && n_surv <= (uint32_t)kLC) {
-                    const uint32_t slots = (n_surv + 63u) >> 6;
-                    n_slots = slots;
-#pragma unroll
-                    for (int u = 0; u < NS; ++u) {
-                        if ((uint32_t)u < slots) {
-                            const uint32_t i = 64u * u + lane;
-                            const bool live = i < n_surv;
-                            const uint32_t packed = live ? list[i] : 0u;
-                            kr[u] = entry_key<false, true>(tv, packed >> 24, live ? (packed & 0xFFFFFFu) : 0u, live, qr, prm.tau,
-                                              st_union);
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < NS; ++u)
-                        if (!kSkipEmpty || (uint32_t)u < slots) n_valid += (uint32_t)__popcll(__ballot(kr[u] != ~0u));
-                    gathered = true;  // the index table is built only if ranking is needed
-                }
-                wave_sync();
-            }
-            if (gathered) {
-                hist_built = false;
-            } else {
-                if constexpr (EPI) bounds();  // the band kernel's only path that reads them
-                clear_hist(hist, lane);
-                if (total <= kRegCap) {
-                    // common case: every bucket entry of the query fits the
-                    // register slots; exactly ceil(total / 64) chunks are read
-                    const uint32_t nch = (total + 63u) >> 6;
-                    n_slots = nch;
-                    switch (nch) {
-#define GATHER_CASE(C)                                                                            \
-    case C:                                                                                       \
-        if constexpr (C <= NS && kMask) gather_chunks_mask<FILT, C, NS>(kr, lane, tv, qr, prm.tau, st_union); \
-        else if constexpr (C <= NS) gather_chunks<EPI, FILT, C, NS>(kr, lane, tv, qr, prm.tau, dd, st_union); \
-        break;
-                        GATHER_CASE(1)
-                        GATHER_CASE(2)
-                        GATHER_CASE(3)
-                        GATHER_CASE(4)
-                        GATHER_CASE(5)
-                        GATHER_CASE(6)
-                        GATHER_CASE(7)
-                        GATHER_CASE(8)
-#undef GATHER_CASE
-                        default:
-                            break;
-                    }
-#pragma unroll
-                    for (int u = 0; u < NS; ++u) {
-                        if ((uint32_t)u < nch) {
-                            // a valid key is below 129 << 16 (the empty key is ~0u); tested
-                            // this way, the compiler does not rebuild ~0u for the other lanes
-                            const bool keep = kr[u] < (129u << 16);
-                            n_valid += (uint32_t)__popcll(__ballot(keep));
-                            if (keep) atomicAdd(&hist[kr[u] >> 16], 1u);
-                        }
-                    }
-                } else {
-                    const QueryRuns qb = runs_keyed();  // the only path that can leave in_regs false
-                    for (uint32_t base = 0; base < total; base += 256) {
-                        uint32_t kv[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            kv[u] = key_at<EPI, kMask, FILT>(base + 64u * u + lane, tv, qb, prm.tau, dd, st_union);
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const bool keep = kv[u] != ~0u;
-                            const uint64_t mk = __ballot(keep);
-                            const uint32_t slot = n_valid + mbcnt64(mk);
-                            if (keep) {
-                                atomicAdd(&hist[kv[u] >> 16], 1u);
-                                if (slot < (uint32_t)kLC) list[slot] = kv[u];
-                            }
-                            n_valid += (uint32_t)__popcll(mk);
-                        }
-                    }
-                    in_regs = n_valid <= kRegCap && n_valid <= (uint32_t)kLC;
-                    wave_sync();
-                    if (in_regs) {
-                        n_slots = (n_valid + 63u) >> 6;
-#pragma unroll
-                        for (int u = 0; u < NS; ++u) {
-                            const uint32_t e = 64u * u + lane;
-                            if (!kSkipEmpty || (uint32_t)u < n_slots) kr[u] = e < n_valid ? list[e] : ~0u;
-                        }
-                    }
+            for (int t = 0; t < kTables; ++t) {
+                for (uint32_t i0 = 64; i0 < rl[t]; i0 += 64) {
+                    const uint32_t pos = rb[t] + i0 + (uint32_t)lane;
+                    band_chunk(t, i0, kp_at(pos), pos);
                 }
             }
             wave_sync();
-            if constexpr (!EPI) {
-                const ulonglong2 c = gload(qcodes + ((int64_t)q0 + min(qi + 1, nq - 1)));
-                nc0 = c.x;
-                nc1 = c.y;
-            }
-            if constexpr (!FILT) st_valid += n_valid;
-            const uint32_t kk = n_valid < (uint32_t)prm.k ? n_valid : (uint32_t)prm.k;
-            st_ranked += kk;
-            // the query's kept count and first tile-list slot, for the ratio
-            // test; word 7 of its run table (its key bytes) is only read
-            // when the query starts
-            if (lane == 0) qtab[kQS * qi + 7] = kk | (sel_n << 16);
-            if (kk == 0) continue;
-            const bool in_list = n_valid <= (uint32_t)kLC;
-            const uint32_t span = in_list ? n_valid : total;
-            uint32_t dummy = 0;
-            // number of candidate keys in [lo, hi), counted with ballots
-#define COUNT_RANGE(lo, hi, c)                                                                        \
-    do {                                                                                              \
-        c = 0;                                                                                        \
-        if (in_regs) {                                                                                \
-            _Pragma("unroll") for (int u = 0; u < NS; ++u) if (!kSkipEmpty || (uint32_t)u < n_slots) c += \
-                (uint32_t)__popcll(__ballot(kr[u] >= (lo) && kr[u] < (hi)));                          \
-        } else {                                                                                      \
-            for (uint32_t base = 0; base < span; base += 64) {                                        \
-                const uint32_t e = base + lane;                                                       \
-                const uint32_t key = in_list ? (e < n_valid ? list[e] : ~0u)                          \
-                                             : key_at<EPI, kMask, FILT>(e, tv, runs_keyed(), prm.tau, dd, dummy);  \
-                c += (uint32_t)__popcll(__ballot(key >= (lo) && key < (hi)));                         \
-            }                                                                                         \
-        }                                                                                             \
-    } while (0)
+            if (n_surv == 0) continue;  // v_kept stays 0
 
-            uint32_t tkey;  // kept candidates: key <= tkey
-            if (n_valid <= (uint32_t)prm.k) {
-                tkey = 0xFFFFFFFEu;  // every valid candidate is kept; no ranking needed
-            } else {
-                if (!hist_built) {
-                    clear_hist(hist, lane);
-#pragma unroll
-                    for (int u = 0; u < NS; ++u)
-                        if ((!kSkipEmpty || (uint32_t)u < n_slots) && kr[u] != ~0u) atomicAdd(&hist[kr[u] >> 16], 1u);
-                    wave_sync();
+            const uint32_t qc[4] = {readlane(v_code.x, qi), readlane(v_code.y, qi), readlane(v_code.z, qi),
+                                    readlane(v_code.w, qi)};
+            const uint32_t qlo = readlane(v_qlo, qi), q4 = readlane(v_q4, qi);
+            // the key of the entry at `pos` of table t (t8 = 8t) and, of the
+            // lanes in `live`, those whose candidate counts
+            auto entry = [&](uint32_t t8, uint32_t pos, uint64_t live, uint32_t& key) -> uint64_t {
+                const ulonglong2 cd = gload(reinterpret_cast<const ulonglong2*>(code + (pos << 4)));
+                const uint2 kw = gload(reinterpret_cast<const uint2*>(kid + (pos << 3)));
+                uint32_t h = bcnt((uint32_t)cd.x ^ qc[0]);
+                h = bcnt_acc((uint32_t)(cd.x >> 32) ^ qc[1], h);
+                h = bcnt_acc((uint32_t)cd.y ^ qc[2], h);
+                h = bcnt_acc((uint32_t)(cd.y >> 32) ^ qc[3], h);
+                key = __builtin_amdgcn_alignbyte(h, kw.y, 2);
+                return first_seen(kw, qlo | (uint32_t)(0xFFFFFFFFull << t8), q4) & live;
+            };
+            uint32_t n_pass = 0, n_union = 0;
+            Threshold th{tauK};
+            if (n_surv <= 64u) {
+                const uint64_t live = ~0ull >> (64u - n_surv);
+                const uint32_t e = (uint32_t)lane < n_surv ? place[lane] : 0u;
+                uint32_t key;
+                const uint64_t ok = entry(e >> 24, e & 0xFFFFFFu, live, key);
+                n_union = (uint32_t)__popcll(ok);
+                const uint64_t m = ok & __builtin_amdgcn_ballot_w64(key <= tauK);
+                n_pass = (uint32_t)__popcll(m);
+                if (n_pass <= (uint32_t)prm.k) {
+                    // every candidate is kept: no ranking
+                    if (__builtin_amdgcn_inverse_ballot_w64(m)) list_at(sel, sel_n, m) = (uint16_t)key;
+                } else if (__builtin_amdgcn_inverse_ballot_w64(m)) {
+                    list_at(list, 0u, m) = key;
                 }
-                // ---- Step 3: Hamming distance H* of the kk-th candidate from the index table
-                uint32_t below;
-                uint32_t ties;  // candidates at Hamming distance H*
-                const uint32_t hs = hist_select<!EPI>(hist, kk, lane, &below, &ties);
-                const uint32_t need = kk - below;
-                if (ties == need) {
-                    tkey = ((hs + 1u) << 16) - 1u;
-                } else if (!EPI && in_regs && need <= kMinRounds) {
-                    // few ties needed: the need-th smallest key at or above
-                    // H* << 16, by rounds of a wave minimum over the keys at
-                    // or above a bound (keys below it, and the ~0u of empty
-                    // slots, wrap to values above every key in range); keys
-                    // are distinct, and the first `ties` keys at or above
-                    // the bound are the ties, so each round finds the next
-                    uint32_t bnd = hs << 16, cur = 0;
-                    for (uint32_t rd = 0; rd < need; ++rd) {
-                        uint32_t m = ~0u;
-#pragma unroll
-                        for (int u = 0; u < NS; ++u)
-                            if (!kSkipEmpty || (uint32_t)u < n_slots) m = min(m, kr[u] - bnd);
-                        cur = bnd + wave_min(m);
-                        bnd = cur + 1u;
-                    }
-                    tkey = cur;
-                } else if (ties <= 64) {
-                    // few ties: gather their indices (the index table is no longer
-                    // needed) and rank each one against the others
-                    const uint32_t lo = hs << 16, hi = lo + 0x10000u;
-                    uint32_t nt = 0;
-                    if (in_regs) {
-#pragma unroll
-                        for (int u = 0; u < NS; ++u) {
-                            if (kSkipEmpty && (uint32_t)u >= n_slots) break;
-                            const bool tie = kr[u] >= lo && kr[u] < hi;
-                            const uint64_t mk = __ballot(tie);
-                            // the index table counted exactly these keys: nt < ties <= 64
-                            // (the band kernels keep a guard; their code schedules better with it)
-                            const uint32_t slot = nt + mbcnt64(mk);
-                            if (tie && (!EPI || slot < 256u)) hist[slot] = kr[u] & 0xFFFFu;
-                            nt += (uint32_t)__popcll(mk);
+            } else {
+                do {
+                    n_pass = n_union = 0;
+                    auto add = [&](uint64_t ok, uint32_t key) {
+                        n_union += (uint32_t)__popcll(ok);
+                        const uint64_t m = ok & __builtin_amdgcn_ballot_w64(key <= th.K);
+                        if (__builtin_amdgcn_inverse_ballot_w64(m)) list_at(list, n_pass, m) = key;
+                        n_pass += (uint32_t)__popcll(m);
+                    };
+                    if (n_surv <= (uint32_t)kBandCap) {
+                        for (uint32_t base = 0; base < n_surv && n_pass <= (uint32_t)kListKeys - 64u; base += 64) {
+                            const uint32_t i = base + (uint32_t)lane;
+                            const uint32_t e = i < n_surv ? place[i] : 0u;
+                            uint32_t key;
+                            const uint64_t ok =
+                                entry(e >> 24, e & 0xFFFFFFu, __builtin_amdgcn_ballot_w64(i < n_surv), key);
+                            add(ok, key);
                         }
                     } else {
-                        for (uint32_t base = 0; base < span; base += 64) {
-                            const uint32_t e = base + lane;
-                            const uint32_t key = in_list ? (e < n_valid ? list[e] : ~0u)
-                                                         : key_at<EPI, kMask, FILT>(e, tv, runs_keyed(), prm.tau, dd, dummy);
-                            const bool tie = key >= lo && key < hi;
-                            const uint64_t mk = __ballot(tie);
-                            const uint32_t slot = nt + mbcnt64(mk);
-                            if (tie && slot < 256u) hist[slot] = key & 0xFFFFu;
-                            nt += (uint32_t)__popcll(mk);
+                        // more inside the band than the places held: every
+                        // entry is tested and read again
+                        for (int t = 0; t < kTables; ++t) {
+                            const uint2 run = *reinterpret_cast<const uint2*>(qrow + 2 * t);
+                            const uint32_t b = uniform(run.x), n = uniform(run.y);
+                            for (uint32_t i0 = 0; i0 < n && n_pass <= (uint32_t)kListKeys - 64u; i0 += 64) {
+                                const uint32_t pos = b + i0 + (uint32_t)lane;
+                                const uint64_t live = __builtin_amdgcn_ballot_w64(in_band(kp_at(pos))) &
+                                                      __builtin_amdgcn_ballot_w64(i0 + (uint32_t)lane < n);
+                                uint32_t key;
+                                const uint64_t ok = entry(8u * (uint32_t)t, pos, live, key);
+                                add(ok, key);
+                            }
                         }
                     }
-                    wave_sync();
-                    const uint32_t jl = (uint32_t)lane < ties ? hist[lane] : ~0u;
-                    uint32_t rank = 0;
-                    for (uint32_t m = 0; m < ties; ++m) rank += hist[m] < jl ? 1u : 0u;
-                    const uint64_t pick = __ballot((uint32_t)lane < ties && rank == need - 1u);
-                    tkey = lo | readlane(jl, __ffsll((unsigned long long)pick) - 1);
-                } else {
-                    // many ties: the need-th smallest index among them, by counting
-                    // with ballots over a binary search of the index bits
-                    const uint32_t lo = hs << 16;
-                    uint32_t J = 0;
-                    for (int b = (int)jbits - 1; b >= 0; --b) {
-                        const uint32_t J2 = J | (1u << b);
-                        uint32_t cnt;
-                        COUNT_RANGE(lo, lo | J2, cnt);
-                        if (cnt < need) J = J2;
-                    }
-                    tkey = lo | J;
-                }
-            }
-            // compaction of the kept candidates into the tile list
-            if (in_regs) {
-#pragma unroll
-                for (int u = 0; u < NS; ++u) {
-                    if (kSkipEmpty && (uint32_t)u >= n_slots) break;
-                    // exactly kk <= k keys are kept per query and the host sizes
-                    // tiles so that nq * k <= kSC: the slot is in range
-                    const bool keep = kr[u] <= tkey;
-                    const uint64_t mk = __ballot(keep);
-                    const uint32_t slot = sel_n + mbcnt64(mk);
-                    if (keep && (!EPI || slot < (uint32_t)kSC)) sel[slot] = ((uint32_t)qi << 16) | (kr[u] & 0xFFFFu);
-                    sel_n += (uint32_t)__popcll(mk);
-                }
-            } else {
-                for (uint32_t base = 0; base < span; base += 64) {
-                    const uint32_t e = base + lane;
-                    const uint32_t key = in_list ? (e < n_valid ? list[e] : ~0u)
-                                                 : key_at<EPI, kMask, FILT>(e, tv, runs_keyed(), prm.tau, dd, dummy);
-                    const bool keep = key <= tkey;
-                    const uint64_t mk = __ballot(keep);
-                    const uint32_t slot = sel_n + mbcnt64(mk);
-                    if (keep && slot < (uint32_t)kSC) sel[slot] = ((uint32_t)qi << 16) | (key & 0xFFFFu);
-                    sel_n += (uint32_t)__popcll(mk);
-                }
+                } while (!th.settled(n_pass, (uint32_t)prm.k, tauK));
             }
             wave_sync();
+            t_union += n_union;
+            const uint32_t kk = min(n_pass, (uint32_t)prm.k);
+            v_kept = lane == qi ? kk | (sel_n << 16) : v_kept;
+            if (n_surv <= 64u && n_pass <= (uint32_t)prm.k)
+                sel_n += n_pass;  // in sel already
+            else if (kk == 0)
+                continue;
+            else if (n_pass <= 64u)
+                select_64(list, hist, n_pass, th.K, kk, lane, sel, sel_n, hG);
+            else
+                select_keys<kPassSlots>(list, n_pass, th.K, kk, lane, sel, sel_n, hG);
+            wave_sync();
         }
-#undef COUNT_RANGE
-        if (sel_n > (uint32_t)kSC) sel_n = kSC;  // cannot happen when nq * k <= kSC
-
-        // ---- Step 4: squared distances of all kept pairs of the tile, 4 lanes per pair
-        for (uint32_t p0 = 0; p0 < sel_n; p0 += 32) {
-            uint32_t dpv[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const uint32_t p = p0 + 16u * h + (uint32_t)(lane >> 2);
-                const bool act = p < sel_n;
-                const uint32_t e = act ? sel[p] : 0u;
-                const uint32_t qi = e >> 16;
-                const uint32_t j = min(e & 0xFFFFu, (uint32_t)(tv.n - 1));
-                const uint4* ap = reinterpret_cast<const uint4*>(Q.desc + (int64_t)(q0 + (int)qi) * kDim + part * 32);
-                const uint4* bp = reinterpret_cast<const uint4*>(T.desc + (int64_t)j * kDim + part * 32);
-                const uint4 a0 = gload(ap), a1 = gload(ap + 1), b0 = gload(bp), b1 = gload(bp + 1);
-                const uint32_t av[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-                const uint32_t bv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-                uint32_t aa = 0, ab = 0, bb = 0;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    aa = __builtin_amdgcn_udot4(av[i], av[i], aa, false);
-                    ab = __builtin_amdgcn_udot4(av[i], bv[i], ab, false);
-                    bb = __builtin_amdgcn_udot4(bv[i], bv[i], bb, false);
-                }
-                dpv[h] = aa + bb - 2u * ab;  // sum over this lane's 32 components of (a - b)^2
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t d = dpv[h] + dpp<0xB1, 0xf>(dpv[h]);  // quad_perm [1,0,3,2]
-                d += dpp<0x4E, 0xf>(d);                        // quad_perm [2,3,0,1]
-                const uint32_t p = p0 + 16u * h + (uint32_t)(lane >> 2);
-                if (part == 0 && p < sel_n) list[p] = d;
-            }
-        }
-        wave_sync();
-
-        // ---- nearest, second nearest and ratio test, one lane per query
-        if (lane < nq) {
-            const uint32_t kw = qtab[kQS * lane + 7];
-            const uint32_t my_kk = kw & 0xFFFFu, my_off = kw >> 16;
-            uint64_t best = ~0ull;
-            uint32_t sec = ~0u;
-            for (uint32_t s = 0; s < my_kk; ++s) {
-                const uint32_t d = list[my_off + s];
-                const uint32_t j = sel[my_off + s] & 0xFFFFu;
-                const uint64_t c = ((uint64_t)d << 32) | j;
-                if (c < best) {
-                    sec = min(sec, (uint32_t)(best >> 32));
-                    best = c;
-                } else {
-                    sec = min(sec, d);
-                }
-            }
-            int32_t r_idx = -1, r_d1 = -1, r_d2 = -1;
-            if (my_kk >= 1) r_d1 = (int32_t)(best >> 32);
-            if (my_kk >= 2) {
-                r_d2 = (int32_t)sec;
-                if (s_rare.den2 * (int64_t)r_d1 < s_rare.num2 * (int64_t)r_d2) r_idx = (int32_t)(uint32_t)best;
-            }
-            const int64_t o = pr.out + q0 + lane;
-            gstore(s_rare.o_idx + o, r_idx);
-            gstore(s_rare.o_d1 + o, r_d1);
-            gstore(s_rare.o_d2 + o, r_d2);
-        }
-        wave_sync();
+        if (lane < nq) st_ranked += v_kept & 0xFFFFu;
+        st_union += t_union;
+        finish_tile(lane, nq, q0, Q.desc, T.desc, pr.out, v_kept, sel, s_rare);
         if (!persistent) break;
     }
-    // statistics: bucket entries and ranked counts (uniform), union sizes (per lane)
-    uint64_t u64 = st_union;
-    for (int d = 32; d >= 1; d >>= 1) u64 += __shfl_xor(u64, d);
-    u64 += st_valid;
-    if (lane == 0 && s_rare.stats) {
-        atomicAdd(&s_rare.stats[0], (unsigned long long)st_bucket);
-        atomicAdd(&s_rare.stats[1], (unsigned long long)u64);
-        atomicAdd(&s_rare.stats[2], (unsigned long long)st_ranked);
+    for (int d = 32; d >= 1; d >>= 1) {
+        st_bucket += __shfl_xor(st_bucket, d);
+        st_ranked += __shfl_xor(st_ranked, d);
     }
+    if (lane == 0) s_rare.add_stats(st_bucket, st_union, st_ranked);
 }
 
 // ------------------------------------------------------------------ launcher
 hipError_t launch_match(hipStream_t s, bool epi, int ns, int grid, const ImgDev* imgs, const PairDev* pairs,
-                        const Item* items, int32_t n_items, uint32_t* counter, const MatchParams& prm, int32_t* o_idx,
-                        int32_t* o_d1, int32_t* o_d2, unsigned long long* stats) {
+                        const Item* items, int32_t n_items, uint32_t* ctl, const MatchParams& prm, int32_t* o_idx,
+                        int32_t* o_d1, int32_t* o_d2) {
     if (n_items <= 0 || grid <= 0) return hipSuccess;
     const dim3 g(grid), b(64 * kWavesPerBlock);
-    const bool filt = prm.tau < kCodeBits;  // a Hamming filter is set
-#define CH_MATCH(E, N, F) \
-    CH_LAUNCH((match_kernel<E, N, F>), g, b, 0, s, imgs, pairs, items, n_items, counter, prm, o_idx, o_d1, o_d2, stats)
     if (epi)
-        CH_MATCH(true, 4, true);  // the band pass keeps only its survivors in the slots
-    else if (ns > 6 && filt)
-        CH_MATCH(false, 8, true);
-    else if (ns > 6)
-        CH_MATCH(false, 8, false);
-    else if (ns > 4 && filt)
-        CH_MATCH(false, 6, true);
+        CH_LAUNCH(band_match_kernel, g, b, 0, s, imgs, pairs, items, n_items, ctl, prm, o_idx, o_d1, o_d2);
     else if (ns > 4)
-        CH_MATCH(false, 6, false);
-    else if (filt)
-        CH_MATCH(false, 4, true);
+        CH_LAUNCH(plain_match_kernel<8>, g, b, 0, s, imgs, pairs, items, n_items, ctl, prm, o_idx, o_d1, o_d2);
     else
-        CH_MATCH(false, 4, false);
-#undef CH_MATCH
+        CH_LAUNCH(plain_match_kernel<4>, g, b, 0, s, imgs, pairs, items, n_items, ctl, prm, o_idx, o_d1, o_d2);
     return hipSuccess;
 }
 

@@ -221,3 +221,82 @@ def test_band_pass_addressing():
             assert N_TABLES * n + 64 < 2**24
     # the keypoint byte offset (pos << 3) of the largest image fits 32 bits
     assert ((N_TABLES * 65535 + 64) << 3) < 2**32
+
+
+# ------------------------------------------------------------------ plain matcher, run words and chunk masks
+
+RUN_WORDS = 12
+
+
+def setup_masks(lens, b, n, nc):
+    """The plain matcher's per-query LDS row (run words by ordinal of the
+    non-empty runs, start masks of the first nc chunks), the counts of starts
+    at or below each chunk boundary (3 bits each) and the run starts."""
+    row = [0] * (RUN_WORDS + 2 * nc)
+    acc = cnt = pre = 0
+    P = []
+    for t in range(N_TABLES):
+        inner = lens[t] != 0 and cnt != 0
+        if t > 0:
+            P.append(acc if inner else 0xFFFFFFFF)
+        if lens[t] != 0:
+            row[2 * cnt] = ((t * n + b[t] - acc) << 4) & 0xFFFFFFFF
+            row[2 * cnt + 1] = t
+        if inner and acc <= 64 * nc:
+            row[RUN_WORDS + ((acc - 1) >> 5)] |= 1 << ((acc - 1) & 31)
+        for u in range(1, nc):
+            pre += int(inner and acc <= 64 * u) << (3 * u)
+        cnt += lens[t] != 0
+        acc += lens[t]
+    assert pre < 1 << 24  # key 4 of the query sits above
+    return row, pre, P, acc
+
+
+@pytest.mark.parametrize("nc", [4, 8])
+def test_run_words_and_masks(nc):
+    """Every live lane of every chunk finds its entry and table: by the masks
+    in the first nc chunks, by compares with the run starts in all of them
+    (the starts kept in 16 bits for nc = 4)."""
+    rng = np.random.default_rng(100 + nc)
+    for n in (300, 9000) if nc == 4 else (9001, 20000, 65535):
+        for lens in layouts(rng, n, 64 * nc + 200):
+            if max(lens) > n or sum(lens) == 0:
+                continue
+            b = runs_of(lens, n, rng)
+            pos, tab = truth(lens, b, n)
+            row, pre, P, total = setup_masks(lens, b, n, nc)
+            if nc == 4:
+                assert all(p == 0xFFFFFFFF or p < 0xFFFF for p in P)
+                P = [p & 0xFFFF for p in P]
+            for e in range(total):
+                u, lane = divmod(e, 64)
+                orders = [sum(int(e >= p) for p in P)]
+                if u < nc:
+                    sm = row[RUN_WORDS + 2 * u] | (row[RUN_WORDS + 2 * u + 1] << 32)
+                    orders.append(mbcnt(sm, lane, (pre >> (3 * u)) & 7))
+                for o in orders:
+                    assert row[2 * o] + 16 * e == 16 * pos[e] and row[2 * o + 1] == tab[e], (nc, n, lens, b, e)
+
+
+def test_entry_words():
+    """The matcher's union test on an entry's word (earlier tables' keys, 0 in
+    the other bytes, key 4 only in table 5's entries) against the query's (0xFF
+    in the bytes from its table on): a repeat exactly when an earlier table's
+    key is shared."""
+    rng = np.random.default_rng(12)
+    for _ in range(4000):
+        q = rng.integers(0, 256, 6)
+        c = rng.integers(0, 256, 6)
+        same = rng.random(6) < 0.3
+        c[same] = q[same]
+        if rng.random() < 0.3:
+            q[rng.integers(0, 6)] = rng.choice([0, 255])
+        for t in range(N_TABLES):
+            k03 = sum(int(c[i]) << (8 * i) for i in range(4))
+            lo = k03 if t >= 4 else k03 & ~(0xFFFFFFFF << (8 * t)) & 0xFFFFFFFF
+            hi = int(c[4]) if t == 5 else 0x100
+            q03 = sum(int(q[i]) << (8 * i) for i in range(4))
+            qlo = q03 | ((0xFFFFFFFF << (8 * t)) & 0xFFFFFFFF) if t < 4 else q03
+            y = lo ^ qlo
+            zero = ((y - 0x01010101) & ~y & 0x80808080) & 0xFFFFFFFF
+            assert (zero != 0 or hi == int(q[4])) == any(c[i] == q[i] for i in range(t)), (t, q, c)

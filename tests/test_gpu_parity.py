@@ -549,3 +549,53 @@ def test_inputs_written_by_queued_torch_work(mats):
         a.copy_(b)
     got, _ = m.match_pairs(dst, c2, k2, w.pairs)
     _assert_match(got, exp, "matches after queued writes")
+
+
+# ------------------------------------------------------------------ edges of the plain matcher's threshold
+
+@pytest.mark.parametrize("k,tau", [(1, 128), (10, 128), (64, 128), (10, 60), (64, 52)])
+def test_candidate_counts_around_chunk_and_list_sizes(mats, k, tau):
+    """Zero bucket rows make every train point a candidate in each table: 6 n
+    bucket entries and n candidates per query, n around the sizes where the
+    64-entry chunks, the masked chunks (256 and 512 entries), the pass list
+    (192 keys) and the one-register selection (64) end; with real code rows and
+    with four distinct codes (hundreds of candidates at one Hamming distance)."""
+    rng = np.random.default_rng(31)
+    sizes = [1, 10, 11, 21, 22, 42, 43, 64, 65, 85, 86, 171, 193, 257, 700]
+    ims = [synth.desc(rng, n) for n in sizes]
+    q = len(ims)
+    ims.append(np.concatenate([synth.noisy(rng, im[:7]) for im in ims]))
+    pairs = np.array([(q, t) for t in range(q)] + [(9, 14)], np.int32)
+    rc, rb = mats
+    coarse = np.zeros_like(rc)
+    coarse[[5, 77]] = rc[[5, 77]]
+    for rows in (rc, coarse):
+        _say(f"candidate counts k={k} tau={tau} rows={'real' if rows is rc else 'coarse'}")
+        m = binding.Matcher(rows, np.zeros_like(rb), k=k, max_hamming=tau)
+        oc, ok = oracle.build_codes(ims, rows, np.zeros_like(rb))
+        dimgs, codes, keys, _ = _gpu_codes(m, ims)
+        got, st = m.match_pairs(dimgs, codes, keys, pairs)
+        exp = _oracle_all(ims, oc, ok, pairs, k=k, tau=tau)
+        _assert_match(got, exp, f"k={k} tau={tau}")
+        # the band form, with a band wider than the images
+        kp = [torch.rand(len(im), 2, device="cuda") * 1000 for im in ims]
+        F = np.tile(np.array([0.0, 0, 0, 0, 0, -1, 0, 1, 0]), (len(pairs), 1))
+        band, _ = m.match_pairs_epipolar(dimgs, codes, keys, kp, pairs, F, 1e5)
+        _assert_match(band, exp, f"band k={k} tau={tau}")
+        assert st["union_size"] == sum(len(ims[a]) * len(ims[b]) for a, b in pairs)
+
+
+@pytest.mark.parametrize("ratio", [(4, 5), (3, 2)])
+def test_equal_nearest_distances(mats, ratio):
+    """Duplicated train points: the two smallest distances are equal, and with a
+    ratio above 1 the match is reported, at the smaller index."""
+    rng = np.random.default_rng(32)
+    a = synth.desc(rng, 150)
+    b = np.concatenate([a[:100], synth.desc(rng, 40), a[:100]])[rng.permutation(240)]
+    ims = [a, np.ascontiguousarray(b)]
+    pairs = np.array([[0, 1], [1, 0]], np.int32)
+    m = binding.Matcher(*mats, ratio=ratio)
+    oc, ok = oracle.build_codes(ims, *mats)
+    dimgs, codes, keys, _ = _gpu_codes(m, ims)
+    got, _ = m.match_pairs(dimgs, codes, keys, pairs)
+    _assert_match(got, _oracle_all(ims, oc, ok, pairs, k=10, ratio=ratio), f"ratio {ratio}")
