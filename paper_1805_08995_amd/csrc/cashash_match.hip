@@ -116,7 +116,7 @@ struct Grab {
             for (int sx = 0; sx < kSegments; ++sx) {
                 const uint32_t x = (blockIdx.x + (uint32_t)sx) & (kSegments - 1);
                 const int32_t s0 = rare.seg[x], s1 = rare.seg[x + 1];
-                if (s0 >= s1 || (*(volatile uint32_t*)&rare.empty >> x & 1u)) continue;
+                if (s0 >= s1 || ((rare.empty >> x) & 1u)) continue;
                 uint32_t v = 0;
                 const int32_t n = rare.grab;
                 if (lane == 0) v = atomicAdd(rare.counter(x), (uint32_t)n);
