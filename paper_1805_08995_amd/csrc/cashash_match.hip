@@ -254,7 +254,7 @@ constexpr int kRunWords = 12;
 constexpr int kPassCap = 192;
 constexpr int kPassSlots = kPassCap / 64;
 // Keys the list in LDS holds, in front of select_64's histogram.
-constexpr int kListKeys = 320;
+constexpr int kListKeys = 256;
 
 // Entry word `kw` (see bucket_kernel) against the query's: the lanes whose
 // candidate shares no key of an earlier table with the query (one that does
@@ -305,9 +305,9 @@ struct Chunks {
         const char* kb = kid + 512 * u0;
         // the last chunk's lanes inside the runs; only they load (the empty asm
         // keeps every case's mask from being computed ahead of the switch)
-        int over = 64 * (u0 + C) - (int)total;
-        asm volatile("" : "+s"(over));
-        const uint64_t live = ~0ull >> max(over, 0);
+        int tot = (int)total;
+        asm volatile("" : "+s"(tot));
+        const uint64_t live = ~0ull >> max(64 * (u0 + C) - tot, 0);
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             if (c + 1 < C || __builtin_amdgcn_inverse_ballot_w64(live)) {
@@ -475,7 +475,7 @@ __device__ __forceinline__ void select_64(const uint32_t* list, uint32_t* hist, 
         }
         hG = base + L;
         const uint32_t at = (uint32_t)hG << 16;
-        tkey = min(K, at | 0xFFFFu);
+        tkey = at | 0xFFFFu;
         if (readlane(incl, L) > kk) {
             // more at H* than needed: the one with exactly kk keys up to it
             uint64_t m = __builtin_amdgcn_ballot_w64(r >= at) & __builtin_amdgcn_ballot_w64(r <= tkey);
@@ -521,16 +521,18 @@ __device__ __forceinline__ void run_starts(uint32_t (&P)[5], const uint32_t (&v)
     }
 }
 
-// A query's threshold on its candidates' keys.  settled(): the number that
-// passed is right (at least k, or all, and no more than the selection takes);
-// else the threshold moves, by steps until both sides are known and then by
-// halves.  Keys are distinct, so some threshold settles (the last line only
-// ends the search if the buffers change under the kernel).
+// Whether the number of keys that passed is right: at least k, or all, and no
+// more than the selection takes.
+__device__ __forceinline__ bool settled(uint32_t n_pass, uint32_t k, uint32_t K, uint32_t tauK) {
+    return n_pass >= k ? n_pass <= (uint32_t)kPassCap : K == tauK;
+}
+// The search for a threshold K that settles: by steps until both sides are
+// known, then by halves.  Keys are distinct, so one settles; move() returns
+// false when none is left, which only happens if the buffers change under the
+// kernel.
 struct Threshold {
-    uint32_t K;
     int32_t klo = -1, khi = INT32_MAX;  // too few pass klo, too many khi
-    __device__ __forceinline__ bool settled(uint32_t n_pass, uint32_t k, uint32_t tauK) {
-        if (n_pass >= k ? n_pass <= (uint32_t)kPassCap : K == tauK) return true;
+    __device__ __forceinline__ bool move(uint32_t& K, uint32_t n_pass, uint32_t k, uint32_t tauK) {
         if (n_pass < k) {
             klo = (int32_t)K;
             K = khi != INT32_MAX ? (uint32_t)(klo + ((khi - klo) >> 1)) : min(tauK, K + (6u << 16));
@@ -538,7 +540,7 @@ struct Threshold {
             khi = (int32_t)K;
             K = klo >= 0 || khi < (4 << 16) ? (uint32_t)(klo + ((khi - klo) >> 1)) : K - (4u << 16);
         }
-        return khi - klo <= 1;
+        return khi - klo > 1;
     }
 };
 
@@ -551,13 +553,13 @@ struct Threshold {
 // limit, and the ranking works on one register per lane instead of one per
 // chunk.  NC: chunks with start masks.
 //
-// What bounds it (100 x 8000 points, rocprofv3): issue, vector and scalar alike,
-// and L2 next to it.  Per query 149 VALU and 147 SALU instructions (213 and 132
-// when every candidate was kept in registers, ranked by an index table over all
-// of them and compacted from them) at about 0.73 of either pipe's rate, and 60
-// L2 lines, 0.75 of what a plain read of such runs gets from L2 here (29 TB/s).
-// Against that form: 100 x 8000 points 15.5 -> 13.3 ms, 16 x 20000 3.65 -> 1.7 ms
-// (half of its queries had more candidates than its eight registers).
+// What bounds it (100 x 8000 points, rocprofv3): issue.  Per query 157 VALU and
+// 132 SALU instructions (213 and 132 when every candidate was kept in registers,
+// ranked by an index table over all of them and compacted from them), 0.86 and
+// 0.72 of the pipes' rates, and 61 L2 lines, 26 of the 29 TB/s that a plain read
+// of such runs gets from L2 here.  Against that form: 100 x 8000 points 15.4 ->
+// 11.9 ms, 16 x 20000 3.65 -> 1.65 ms (half of its queries had more candidates
+// than its eight registers).
 template <int NC>
 __global__ __launch_bounds__(256, match_blocks_per_cu(false, NC)) void plain_match_kernel(
     const ImgDev* __restrict__ imgs, const PairDev* __restrict__ pairs, const Item* __restrict__ items,
@@ -581,7 +583,8 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(false, NC)) void plain_mat
     uint64_t st_bucket = 0, st_ranked = 0;  // per lane
     uint64_t st_union = 0;                   // uniform
     const uint32_t tauK = ((uint32_t)prm.tau << 16) | 0xFFFFu;
-    int32_t hT = 56, hG = 52;  // threshold for the next query; the last query's H*
+    uint32_t hK = min(tauK, (56u << 16) | 0xFFFFu);  // threshold for the next query
+    int32_t hG = 52;                                  // the last query's H*
 
     Grab grab;
     int32_t it = (int32_t)(blockIdx.x * kWavesPerBlock + wv);
@@ -656,61 +659,67 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(false, NC)) void plain_mat
                                     readlane(v_code.w, qi)};
             const uint32_t total = readlane(v_total, qi), preq = readlane(v_preq, qi);
             const uint32_t* qrow = qtab + kQS * qi;
-            const int nch = (int)((total + 63u) >> 6);
-            Threshold th{nch > 1 ? min(tauK, ((uint32_t)hT << 16) | 0xFFFFu) : tauK};
-            uint32_t n_pass, n_union;
-            for (;;) {
-                n_pass = n_union = 0;
-                const uint32_t noP[5] = {0, 0, 0, 0, 0};
-#define SCAN(C, ORD, U, P) scan_chunks<C, ORD>(lane, code, kid, qrow, U, preq, P, total, qc, th.K, list, n_pass, n_union)
-                switch (min(nch, 4)) {
-                    case 0: break;
-                    case 1: SCAN(1, true, 0, noP); break;
-                    case 2: SCAN(2, true, 0, noP); break;
-                    case 3: SCAN(3, true, 0, noP); break;
-                    default: SCAN(4, true, 0, noP); break;
-                }
-                // further chunks, four or two at a time while the list has
-                // room for all their candidates
-#pragma unroll 1
-                for (int u0 = 4; u0 < nch;) {
-                    if (n_pass > (uint32_t)kPassCap) break;  // too many already
-                    const int c = min(nch - u0, n_pass <= (uint32_t)kListKeys - 256u ? 4 : 2);
-                    if (NC > 4 && u0 + c <= NC) {
-                        switch (c) {
-                            case 1: SCAN(1, true, u0, noP); break;
-                            case 2: SCAN(2, true, u0, noP); break;
-                            case 3: SCAN(3, true, u0, noP); break;
-                            default: SCAN(4, true, u0, noP); break;
-                        }
-                        u0 += c;
-                    } else {
-                        uint32_t P[5];
-                        run_starts(P, v_P, qi);
-                        if (c >= 2) {
-                            SCAN(2, false, u0, P);
-                            u0 += 2;
-                        } else {
-                            SCAN(1, false, u0, P);
-                            u0 += 1;
-                        }
-                    }
-                }
-#undef SCAN
-                if (th.settled(n_pass, (uint32_t)prm.k, tauK)) break;
-                hT = (int32_t)(th.K >> 16);
+            uint32_t K = total > 64u ? hK : tauK;  // a single chunk fits the list whole
+            uint32_t n_pass = 0, n_union = 0;
+            const uint32_t noP[5] = {0, 0, 0, 0, 0};
+#define SCAN(C, ORD, U, P) scan_chunks<C, ORD>(lane, code, kid, qrow, U, preq, P, total, qc, K, list, n_pass, n_union)
+            if (total > 128u) {
+                if (total > 192u)
+                    SCAN(4, true, 0, noP);
+                else
+                    SCAN(3, true, 0, noP);
+            } else if (total > 64u) {
+                SCAN(2, true, 0, noP);
+            } else if (total != 0u) {
+                SCAN(1, true, 0, noP);
             }
+            // Further chunks, two or one at a time while the list has room for
+            // all their candidates; and, when the number that passed is not
+            // right, all chunks again with another threshold
+            if (total > 256u || !settled(n_pass, (uint32_t)prm.k, K, tauK)) {
+                const int nch = (int)((total + 63u) >> 6);
+                Threshold th;
+                int u0 = 4;
+                for (;;) {
+#pragma unroll 1
+                    while (u0 < nch && n_pass <= (uint32_t)kPassCap) {
+                        const bool two = nch - u0 >= 2 && n_pass <= (uint32_t)kListKeys - 128u;
+                        if (u0 + 2 <= NC) {
+                            if (two)
+                                SCAN(2, true, u0, noP);
+                            else
+                                SCAN(1, true, u0, noP);
+                        } else {
+                            uint32_t P[5];
+                            run_starts(P, v_P, qi);
+                            if (two)
+                                SCAN(2, false, u0, P);
+                            else
+                                SCAN(1, false, u0, P);
+                        }
+                        u0 += two ? 2 : 1;
+                    }
+                    if (settled(n_pass, (uint32_t)prm.k, K, tauK) || !th.move(K, n_pass, (uint32_t)prm.k, tauK)) break;
+                    hK = min(K | 0xFFFFu, tauK);
+                    n_pass = n_union = 0;
+                    u0 = 0;
+                }
+                n_pass = min(n_pass, (uint32_t)kPassCap);
+            }
+#undef SCAN
             wave_sync();
             t_union += n_union;
             const uint32_t kk = min(n_pass, (uint32_t)prm.k);
-            v_kept = lane == qi ? kk | (sel_n << 16) : v_kept;
-            if (kk == 0) continue;
-            if (n_pass <= 64u) {
-                select_64(list, hist, n_pass, th.K, kk, lane, sel, sel_n, hG);
-            } else {
-                select_keys<kPassSlots>(list, n_pass, th.K, kk, lane, sel, sel_n, hG);
-                hT = max(hT - 1, 4);
+            const uint32_t at = sel_n;
+            if (kk != 0) {
+                if (n_pass <= 64u) {
+                    select_64(list, hist, n_pass, K, kk, lane, sel, sel_n, hG);
+                } else {
+                    select_keys<kPassSlots>(list, n_pass, K, kk, lane, sel, sel_n, hG);
+                    hK = max(hK, 5u << 16) - 0x10000u;
+                }
             }
+            v_kept = lane == qi ? (sel_n - at) | (at << 16) : v_kept;
             wave_sync();
         }
         if (lane < nq) {
@@ -903,8 +912,7 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(true, 4)) void band_match_
                 key = __builtin_amdgcn_alignbyte(h, kw.y, 2);
                 return first_seen(kw, qlo | (uint32_t)(0xFFFFFFFFull << t8), q4) & live;
             };
-            uint32_t n_pass = 0, n_union = 0;
-            Threshold th{tauK};
+            uint32_t n_pass = 0, n_union = 0, K = tauK;
             if (n_surv <= 64u) {
                 const uint64_t live = ~0ull >> (64u - n_surv);
                 const uint32_t e = (uint32_t)lane < n_surv ? place[lane] : 0u;
@@ -920,16 +928,17 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(true, 4)) void band_match_
                     list_at(list, 0u, m) = key;
                 }
             } else {
+                Threshold th;
                 do {
                     n_pass = n_union = 0;
                     auto add = [&](uint64_t ok, uint32_t key) {
                         n_union += (uint32_t)__popcll(ok);
-                        const uint64_t m = ok & __builtin_amdgcn_ballot_w64(key <= th.K);
+                        const uint64_t m = ok & __builtin_amdgcn_ballot_w64(key <= K);
                         if (__builtin_amdgcn_inverse_ballot_w64(m)) list_at(list, n_pass, m) = key;
                         n_pass += (uint32_t)__popcll(m);
                     };
                     if (n_surv <= (uint32_t)kBandCap) {
-                        for (uint32_t base = 0; base < n_surv && n_pass <= (uint32_t)kListKeys - 64u; base += 64) {
+                        for (uint32_t base = 0; base < n_surv && n_pass <= (uint32_t)kPassCap; base += 64) {
                             const uint32_t i = base + (uint32_t)lane;
                             const uint32_t e = i < n_surv ? place[i] : 0u;
                             uint32_t key;
@@ -943,7 +952,7 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(true, 4)) void band_match_
                         for (int t = 0; t < kTables; ++t) {
                             const uint2 run = *reinterpret_cast<const uint2*>(qrow + 2 * t);
                             const uint32_t b = uniform(run.x), n = uniform(run.y);
-                            for (uint32_t i0 = 0; i0 < n && n_pass <= (uint32_t)kListKeys - 64u; i0 += 64) {
+                            for (uint32_t i0 = 0; i0 < n && n_pass <= (uint32_t)kPassCap; i0 += 64) {
                                 const uint32_t pos = b + i0 + (uint32_t)lane;
                                 const uint64_t live = __builtin_amdgcn_ballot_w64(in_band(kp_at(pos))) &
                                                       __builtin_amdgcn_ballot_w64(i0 + (uint32_t)lane < n);
@@ -953,20 +962,20 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(true, 4)) void band_match_
                             }
                         }
                     }
-                } while (!th.settled(n_pass, (uint32_t)prm.k, tauK));
+                } while (!settled(n_pass, (uint32_t)prm.k, K, tauK) && th.move(K, n_pass, (uint32_t)prm.k, tauK));
+                n_pass = min(n_pass, (uint32_t)kPassCap);
             }
             wave_sync();
             t_union += n_union;
             const uint32_t kk = min(n_pass, (uint32_t)prm.k);
-            v_kept = lane == qi ? kk | (sel_n << 16) : v_kept;
+            const uint32_t at = sel_n;
             if (n_surv <= 64u && n_pass <= (uint32_t)prm.k)
                 sel_n += n_pass;  // in sel already
-            else if (kk == 0)
-                continue;
-            else if (n_pass <= 64u)
-                select_64(list, hist, n_pass, th.K, kk, lane, sel, sel_n, hG);
-            else
-                select_keys<kPassSlots>(list, n_pass, th.K, kk, lane, sel, sel_n, hG);
+            else if (kk != 0 && n_pass <= 64u)
+                select_64(list, hist, n_pass, K, kk, lane, sel, sel_n, hG);
+            else if (kk != 0)
+                select_keys<kPassSlots>(list, n_pass, K, kk, lane, sel, sel_n, hG);
+            v_kept = lane == qi ? (sel_n - at) | (at << 16) : v_kept;
             wave_sync();
         }
         if (lane < nq) st_ranked += v_kept & 0xFFFFu;
