@@ -175,7 +175,7 @@ struct cashash_ctx {
     HostPinned pin[2];        // host-memory mode upload staging
     hipEvent_t pin_ev[2] = {nullptr, nullptr};
     int pin_turn = 0;
-    HostPinned pin_out[2], pin_small;
+    HostPinned pin_out[2], pin_small, pin_geo;
     hipEvent_t slot_load_ev[3] = {nullptr, nullptr, nullptr};
     hipEvent_t slot_free_ev[3] = {nullptr, nullptr, nullptr};
     // per match job in flight (host-memory mode keeps two): kernel start and
@@ -324,7 +324,7 @@ static void destroy_ctx(cashash_ctx* c) {
     for (DevBuf* b : dev_bufs(c)) b->release();
     for (HostPinned* h : {&c->meta_host[0][0], &c->meta_host[0][1], &c->meta_host[1][0], &c->meta_host[1][1],
                           &c->meta_host[2][0], &c->meta_host[2][1], &c->pin[0], &c->pin[1], &c->pin_out[0], &c->pin_out[1],
-                          &c->pin_small})
+                          &c->pin_small, &c->pin_geo})
         h->release();
     for (hipEvent_t e : {c->meta_ev[0][0], c->meta_ev[0][1], c->meta_ev[1][0], c->meta_ev[1][1],
                          c->meta_ev[2][0], c->meta_ev[2][1], c->geo_ev[0], c->geo_ev[1], c->geo_ev[2], c->geo_ev[3],
@@ -419,7 +419,7 @@ extern "C" int cashash_create(cashash_ctx** out, const double* r_code, const dou
     for (DevBuf* b : dev_bufs(c)) b->owner = c;
     for (HostPinned* h : {&c->meta_host[0][0], &c->meta_host[0][1], &c->meta_host[1][0], &c->meta_host[1][1],
                           &c->meta_host[2][0], &c->meta_host[2][1], &c->pin[0], &c->pin[1], &c->pin_out[0],
-                          &c->pin_out[1], &c->pin_small})
+                          &c->pin_out[1], &c->pin_small, &c->pin_geo})
         h->owner = c;
     auto bail = [&](int code) {
         std::string keep = g_err;
@@ -1975,7 +1975,8 @@ static int run_fundamental(cashash_ctx* c, int32_t n_images, const int32_t* n_fe
     if (cap > kGeoMaxMatches)
         return fail(CASHASH_E_LIMIT, "a query image has %d points; at most %d per image here", cap, kGeoMaxMatches);
     const size_t P = (size_t)n_pairs;
-    RETCHK(c->geo_pair.ensure(P * 9 * 8 + 4 * P * 4 + 256));
+    const size_t fit_at = al256(P * 9 * 8 + 4 * P * 4);  // the estimator's own area
+    RETCHK(c->geo_pair.ensure(fit_at + P * sizeof(GeoFit)));
     GeoOut go;
     go.F = c->geo_pair.as<double>();
     go.n_matches = reinterpret_cast<int32_t*>(go.F + 9 * P);
@@ -1991,7 +1992,8 @@ static int run_fundamental(cashash_ctx* c, int32_t n_images, const int32_t* n_fe
     RETCHK(upload_meta(c, up, d, kMetaGeo));
     GeoParams prm{n_hyp, min_matches, thr, cap, 0};
     HIPCHK(launch_fundamental(c->stream, (const GeoImg*)d[0], (const GeoPair*)d[1], n_pairs, match_idx,
-                              (const uint32_t*)d[2], prm, go, c->geo_err.as<unsigned>()));
+                              (const uint32_t*)d[2], prm, go, reinterpret_cast<GeoFit*>(c->geo_pair.as<uint8_t>() + fit_at),
+                              c->geo_err.as<unsigned>()));
     return CASHASH_OK;
 }
 
@@ -2003,20 +2005,20 @@ static int check_geo_args(int32_t n_hyp, const uint32_t* rand8, double thr, int3
     return CASHASH_OK;
 }
 
+// The per-pair results and the error word in one download through pinned memory.
 static int copy_pair_results(cashash_ctx* c, int64_t n_pairs, double* F_out, int32_t* n_matches, int32_t* n_inliers,
                              int32_t* best_hyp, int32_t* status) {
-    const size_t P = (size_t)n_pairs;
-    const double* F = c->geo_pair.as<double>();
+    const size_t P = (size_t)n_pairs, bytes = P * (9 * 8 + 4 * 4);
+    RETCHK(c->pin_geo.ensure(bytes));
+    HIPCHK(hipMemcpyAsync(c->pin_geo.p, c->geo_pair.p, bytes, hipMemcpyDeviceToHost, c->stream));
+    RETCHK(read_geo_err(c));  // waits
+    const double* F = static_cast<const double*>(c->pin_geo.p);
     const int32_t* nm = reinterpret_cast<const int32_t*>(F + 9 * P);
-    struct Piece {
-        void* dst;
-        const void* src;
-        size_t bytes;
-    };
-    for (const Piece& pc : {Piece{F_out, F, P * 72}, Piece{n_matches, nm, P * 4}, Piece{n_inliers, nm + P, P * 4},
-                            Piece{best_hyp, nm + 2 * P, P * 4}, Piece{status, nm + 3 * P, P * 4}})
-        if (pc.dst) HIPCHK(hipMemcpyAsync(pc.dst, pc.src, pc.bytes, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
+    std::memcpy(F_out, F, P * 72);
+    std::memcpy(n_matches, nm, P * 4);
+    std::memcpy(n_inliers, nm + P, P * 4);
+    if (best_hyp) std::memcpy(best_hyp, nm + 2 * P, P * 4);
+    std::memcpy(status, nm + 3 * P, P * 4);
     return CASHASH_OK;
 }
 
@@ -2056,7 +2058,6 @@ extern "C" int cashash_estimate_fundamental(cashash_ctx* c, int32_t n_images, co
     RETCHK(clear_geo_err(c));
     RETCHK(run_fundamental(c, n_images, n_feat, kp_xy, n_pairs, pairs, out, match_idx, rand8, n_hyp, thr_px,
                            min_matches));
-    RETCHK(read_geo_err(c));
     return copy_pair_results(c, n_pairs, F_out, n_matches, n_inliers, best_hyp, status);
 }
 
@@ -2154,7 +2155,6 @@ extern "C" int cashash_match_pairs_geometric(cashash_ctx* c, const cashash_image
     RETCHK(run_fundamental(c, n_img, ms.data(), const_cast<const float* const*>(skp.data()), n_pairs, pairs, out1, m1,
                            g->rand8, g->n_hyp, g->ransac_px, g->min_matches));
     HIPCHK(hipEventRecord(c->geo_ev[3], c->stream));
-    RETCHK(read_geo_err(c));
     RETCHK(copy_pair_results(c, n_pairs, F_out, n_matches, n_inliers, nullptr, status));
     // stage 2: guided matching of the accepted pairs; the others get -1
     std::vector<int32_t> acc_pairs;

@@ -351,26 +351,55 @@ __device__ __forceinline__ bool null8(double (&A)[8][9], double (&f)[9]) {
 
 }  // namespace
 
+// The estimator runs as three kernels: the fit of the best hypothesis up to the
+// refit's normal matrix (a block per pair), the refit's eigenvector (27 lanes per
+// pair) and the inlier count of its matrix (a block per pair).  The 360 rotations of the 9 x 9 Jacobi are one long chain of
+// dependent divisions and square roots; in one kernel they kept a 256-thread
+// block of 253 registers waiting, two blocks per CU, and everything sequential in
+// match order ran in one thread: 667 us for 600 pairs of 400 matches (256
+// hypotheses each), now 161 + 154 + 4 us.  What is left is the binary64 work of
+// the hypotheses (19 thousand VALU instructions per wavefront of the fit; four
+// tests at a time or a third block per CU with its spills changed nothing) and
+// the rotations' chain.
+
+// Sequential sum of v over the first n lanes of consecutive 64-lane chunks,
+// s = ((s + v_0) + v_1) + .. : the lanes hold a chunk's values, the sum is
+// uniform.
+__device__ __forceinline__ double add_lanes(double s, double v, int n) {
+    auto lane_value = [&](int i) {
+        const uint64_t u = (uint64_t)__double_as_longlong(v);
+        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, i), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), i);
+        return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
+    };
+    if (n == 64) {
+#pragma unroll
+        for (int i = 0; i < 64; ++i) s = s + lane_value(i);
+    } else {
+        for (int i = 0; i < n; ++i) s = s + lane_value(i);
+    }
+    return s;
+}
+
 // One block of 256 threads per pair.  The pair's stage-1 matches are
-// compacted (ascending query order) into LDS as (x, y, x', y'); thread 0
-// computes the two normalisations; each thread runs hypotheses h = tid,
-// tid + 256, ... entirely in registers and counts their inliers against the
-// LDS list; the block picks the best; 45 threads accumulate the upper
-// triangle of A^T A over its inliers, each sequentially in match order;
-// wave 0 runs the 9 x 9 Jacobi with one lane per row / column of each
-// rotation; thread 0 finishes the refit and the block counts its inliers.
-__global__ __launch_bounds__(256) void fundamental_kernel(const GeoImg* __restrict__ imgs,
-                                                          const GeoPair* __restrict__ pairs,
-                                                          const int32_t* __restrict__ match_idx,
-                                                          const uint32_t* __restrict__ rnd, GeoParams prm,
-                                                          GeoOut out, unsigned* __restrict__ err) {
+// compacted (ascending query order) into LDS as (x, y, x', y'); the four waves
+// take one coordinate's sum each, then two the distance sums (values by lane,
+// sums in match order); each thread runs hypotheses h = tid, tid + 256, ...
+// entirely in registers and counts their inliers against the LDS list; the
+// block picks the best; its inliers' design rows are laid out 256 at a time
+// (zeros for outliers: a sum that starts at 0 is unchanged by adding 0) and 45
+// lanes accumulate the upper triangle of A^T A, each sequentially in match order.
+__global__ __launch_bounds__(256) void fundamental_fit_kernel(const GeoImg* __restrict__ imgs,
+                                                              const GeoPair* __restrict__ pairs,
+                                                              const int32_t* __restrict__ match_idx,
+                                                              const uint32_t* __restrict__ rnd, GeoParams prm,
+                                                              GeoOut out, GeoFit* __restrict__ fits,
+                                                              unsigned* __restrict__ err) {
     extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
-    float4* pts = reinterpret_cast<float4*>(dyn);
-    uint8_t* flag = dyn + (size_t)16 * prm.cap;
-    __shared__ double sA[81], sV[81], sF[9], s_norm[6];
+    double* rows = reinterpret_cast<double*>(dyn);                            // [256][9]
+    float4* pts = reinterpret_cast<float4*>(dyn + kGeoRowBytes);              // [cap]
+    __shared__ double sF[9], s_sum[6];
     __shared__ uint32_t wtot[4];
     __shared__ unsigned long long s_best[4];
-    __shared__ int32_t s_ok;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t p = blockIdx.x;
     const GeoPair pr = pairs[p];
@@ -391,62 +420,63 @@ __global__ __launch_bounds__(256) void fundamental_kernel(const GeoImg* __restri
             pts[pos] = make_float4(Q.kp[2 * q], Q.kp[2 * q + 1], T.kp[2 * m], T.kp[2 * m + 1]);
         n += tot;
     }
-    auto finish = [&](int st, int ni, int bh) {
-        out.n_matches[p] = (int32_t)n;
-        out.n_inliers[p] = ni;
-        out.best_h[p] = bh;
-        out.status[p] = st;
+    // a pair that ends here: no matrix, nothing for the kernels that follow
+    auto finish = [&](int st, int bh) {
+        if (tid < 9) out.F[9 * p + tid] = 0.0;
+        if (tid == 0) {
+            out.n_matches[p] = (int32_t)n;
+            out.n_inliers[p] = 0;
+            out.best_h[p] = bh;
+            out.status[p] = st;
+            fits[p].refit = 0;
+        }
     };
     if (n > (uint32_t)prm.cap) {
-        if (tid == 0) {
-            atomicOr(err, 4u);
-            for (int i = 0; i < 9; ++i) out.F[9 * p + i] = 0.0;
-            finish(kDegenerate, 0, -1);
-        }
+        if (tid == 0) atomicOr(err, 4u);
+        finish(kDegenerate, -1);
         return;
     }
     if ((int)n < prm.min_matches || n < 8) {
-        if (tid < 9) out.F[9 * p + tid] = 0.0;
-        if (tid == 0) finish(kFewMatches, 0, -1);
+        finish(kFewMatches, -1);
         return;
     }
     __syncthreads();
 
     // Hartley normalisation of both point sets (sequential sums)
-    if (tid == 0) {
-        double sx = 0.0, sy = 0.0, su = 0.0, sv = 0.0;
-        for (uint32_t i = 0; i < n; ++i) {
-            const float4 m = pts[i];
-            sx = sx + (double)m.x;
-            sy = sy + (double)m.y;
-            su = su + (double)m.z;
-            sv = sv + (double)m.w;
+    const double dn = (double)n;
+    {
+        const float* co = reinterpret_cast<const float*>(pts) + wv;  // this wave's coordinate
+        double s = 0.0;
+        for (uint32_t c0 = 0; c0 < n; c0 += 64) {
+            const uint32_t i = c0 + (uint32_t)lane;
+            s = add_lanes(s, i < n ? (double)co[4 * i] : 0.0, (int)min(64u, n - c0));
         }
-        const double dn = (double)n;
-        const double cx = sx / dn, cy = sy / dn, cu = su / dn, cv = sv / dn;
-        double dq = 0.0, dt = 0.0;
-        for (uint32_t i = 0; i < n; ++i) {
-            const float4 m = pts[i];
-            const double dx = (double)m.x - cx, dy = (double)m.y - cy;
-            const double du = (double)m.z - cu, dv = (double)m.w - cv;
-            dq = dq + sqrt(dx * dx + dy * dy);
-            dt = dt + sqrt(du * du + dv * dv);
-        }
-        s_ok = (dq > 0.0) && (dt > 0.0);
-        s_norm[0] = kSqrt2 / (dq / dn);
-        s_norm[1] = cx;
-        s_norm[2] = cy;
-        s_norm[3] = kSqrt2 / (dt / dn);
-        s_norm[4] = cu;
-        s_norm[5] = cv;
+        if (lane == 0) s_sum[wv] = s;
     }
     __syncthreads();
-    if (!s_ok) {
-        if (tid < 9) out.F[9 * p + tid] = 0.0;
-        if (tid == 0) finish(kDegenerate, 0, -1);
+    const double cx = s_sum[0] / dn, cy = s_sum[1] / dn, cu = s_sum[2] / dn, cv = s_sum[3] / dn;
+    if (wv < 2) {
+        const double c0x = wv == 0 ? cx : cu, c0y = wv == 0 ? cy : cv;
+        double s = 0.0;
+        for (uint32_t c0 = 0; c0 < n; c0 += 64) {
+            const uint32_t i = c0 + (uint32_t)lane;
+            double v = 0.0;
+            if (i < n) {
+                const float4 m = pts[i];
+                const double dx = (double)(wv == 0 ? m.x : m.z) - c0x, dy = (double)(wv == 0 ? m.y : m.w) - c0y;
+                v = sqrt(dx * dx + dy * dy);
+            }
+            s = add_lanes(s, v, (int)min(64u, n - c0));
+        }
+        if (lane == 0) s_sum[4 + wv] = s;
+    }
+    __syncthreads();
+    const double dq = s_sum[4], dt = s_sum[5];
+    if (!(dq > 0.0 && dt > 0.0)) {
+        finish(kDegenerate, -1);
         return;
     }
-    const Norm2 NQ{s_norm[0], s_norm[1], s_norm[2]}, NT{s_norm[3], s_norm[4], s_norm[5]};
+    const Norm2 NQ{kSqrt2 / (dq / dn), cx, cy}, NT{kSqrt2 / (dt / dn), cu, cv};
     const double dd = prm.thr * prm.thr;
 
     // hypotheses: pixel-space matrix of hypothesis h, false if unsolvable
@@ -497,8 +527,7 @@ __global__ __launch_bounds__(256) void fundamental_kernel(const GeoImg* __restri
     const int bc = (int)(top >> 32) - 1;
     const int bh = 0x7FFFFFFF - (int)(uint32_t)(top & 0xFFFFFFFFull);
     if (bc < 8) {
-        if (tid < 9) out.F[9 * p + tid] = 0.0;
-        if (tid == 0) finish(kDegenerate, 0, bc >= 0 ? bh : -1);
+        finish(kDegenerate, bc >= 0 ? bh : -1);
         return;
     }
     if (best_h == bh) {
@@ -509,92 +538,174 @@ __global__ __launch_bounds__(256) void fundamental_kernel(const GeoImg* __restri
     }
     __syncthreads();
 
-    // refit: inlier flags of the best hypothesis, then A^T A (upper triangle,
-    // one thread per entry, sequential over matches)
-    {
-        double F[9];
-#pragma unroll
-        for (int i = 0; i < 9; ++i) F[i] = sF[i];
-        for (uint32_t i = tid; i < n; i += 256) flag[i] = inlier(F, pts[i], dd) ? 1 : 0;
-    }
-    __syncthreads();
-    if (tid < 45) {
-        int r = 0, k = tid;
-        while (k >= 9 - r) {
-            k -= 9 - r;
-            ++r;
-        }
-        const int c = r + k;
-        double acc = 0.0;
-        for (uint32_t i = 0; i < n; ++i) {
-            if (!flag[i]) continue;
-            const float4 m = pts[i];
-            double a[9];
-            design_row(nx(NQ, m.x), ny(NQ, m.y), nx(NT, m.z), ny(NT, m.w), a);
-            double ar = a[0], ac = a[0];
-#pragma unroll
-            for (int j = 1; j < 9; ++j) {
-                ar = r == j ? a[j] : ar;
-                ac = c == j ? a[j] : ac;
-            }
-            acc = acc + ar * ac;
-        }
-        sA[r * 9 + c] = acc;
-        sA[c * 9 + r] = acc;
-    }
-    if (tid < 81) sV[tid] = (tid % 10 == 0) ? 1.0 : 0.0;
-    __syncthreads();
-    if (wv == 0) {
-        const int k = lane < 9 ? lane : 0;
-        for (int sw = 0; sw < kJacobiSweeps9; ++sw)
-            for (int pp = 0; pp < 8; ++pp)
-                for (int qq = pp + 1; qq < 9; ++qq) {
-                    const double apq = sA[pp * 9 + qq];
-                    if (apq == 0.0) continue;
-                    double c, s;
-                    schur(sA[pp * 9 + pp], sA[qq * 9 + qq], apq, c, s);
-                    if (lane < 9) {
-                        const double akp = sA[k * 9 + pp], akq = sA[k * 9 + qq];
-                        sA[k * 9 + pp] = c * akp - s * akq;
-                        sA[k * 9 + qq] = s * akp + c * akq;
-                    }
-                    wave_sync();
-                    if (lane < 9) {
-                        const double apk = sA[pp * 9 + k], aqk = sA[qq * 9 + k];
-                        sA[pp * 9 + k] = c * apk - s * aqk;
-                        sA[qq * 9 + k] = s * apk + c * aqk;
-                        const double vkp = sV[k * 9 + pp], vkq = sV[k * 9 + qq];
-                        sV[k * 9 + pp] = c * vkp - s * vkq;
-                        sV[k * 9 + qq] = s * vkp + c * vkq;
-                    }
-                    wave_sync();
-                }
-        if (lane == 0) {
-            int m = 0;
-            for (int i = 1; i < 9; ++i)
-                if (sA[i * 9 + i] < sA[m * 9 + m]) m = i;
-            double f[9], F[9];
-#pragma unroll
-            for (int i = 0; i < 9; ++i) f[i] = sV[i * 9 + m];
-            rank2(f);
-            to_pixels(f, NQ, NT, F);
-#pragma unroll
-            for (int i = 0; i < 9; ++i) sF[i] = F[i];
-        }
-    }
-    __syncthreads();
+    // refit: A^T A (upper triangle) over the best hypothesis's inliers
     double F[9];
 #pragma unroll
     for (int i = 0; i < 9; ++i) F[i] = sF[i];
+    int r = 0, k = min(tid, 44);
+    while (k >= 9 - r) {
+        k -= 9 - r;
+        ++r;
+    }
+    const int c = r + k;
+    double acc = 0.0;
+    for (uint32_t c0 = 0; c0 < n; c0 += 256) {
+        const uint32_t i = c0 + (uint32_t)tid;
+        double a[9];
+#pragma unroll
+        for (int j = 0; j < 9; ++j) a[j] = 0.0;
+        if (i < n) {
+            const float4 m = pts[i];
+            if (inlier(F, m, dd)) design_row(nx(NQ, m.x), ny(NQ, m.y), nx(NT, m.z), ny(NT, m.w), a);
+        }
+        __syncthreads();  // the last chunk's rows are read
+#pragma unroll
+        for (int j = 0; j < 9; ++j) rows[9 * tid + j] = a[j];
+        __syncthreads();
+        if (tid < 45) {
+            const int cnt = (int)min(256u, n - c0);
+#pragma unroll 8
+            for (int i2 = 0; i2 < cnt; ++i2) acc = acc + rows[9 * i2 + r] * rows[9 * i2 + c];
+        }
+    }
+    GeoFit& fit = fits[p];
+    if (tid < 45) {
+        fit.A[r * 9 + c] = acc;
+        fit.A[c * 9 + r] = acc;
+    }
+    if (tid == 0) {
+        fit.norm[0] = NQ.s;
+        fit.norm[1] = NQ.cx;
+        fit.norm[2] = NQ.cy;
+        fit.norm[3] = NT.s;
+        fit.norm[4] = NT.cx;
+        fit.norm[5] = NT.cy;
+        fit.refit = 1;
+        out.n_matches[p] = (int32_t)n;
+        out.best_h[p] = bh;
+    }
+}
+
+// The smallest eigenvector of each pair's A^T A, made rank 2 and mapped to
+// pixels.  27 lanes work on a pair, two pairs per wavefront: lane k on row k of
+// A (the column step of a rotation), lane 9 + k on row k of V, lane 18 + k on
+// column k of A (the row step); A and V lie in LDS.  The time is that of 360
+// rotations one after another in a single wavefront: its instructions, of which
+// the two square roots and three divisions of c and s are 95.  So the rest is
+// kept short: a lane reads and writes two elements, the row step takes the
+// block's column step in registers, the next rotation's c and s start from
+// entries computed here and not from the LDS, and q is unrolled so that places
+// are offsets: 124 instructions per rotation, 154 us at up to about 2000 pairs
+// (nine lanes per pair, each doing a row's, V's and a column's work, 270
+// instructions: 205 us).
+constexpr int kRefitPairs = 2;
+__global__ __launch_bounds__(64) void fundamental_refit_kernel(const GeoFit* __restrict__ fits, int64_t n_pairs,
+                                                               GeoOut out) {
+    __shared__ double s_M[kRefitPairs][2][81];  // A, then V
+    const int lane = threadIdx.x;
+    const int g = min(lane / 27, kRefitPairs - 1), kind = lane % 27 / 9, k = lane % 9;
+    const int64_t p = (int64_t)blockIdx.x * kRefitPairs + g;
+    const bool live = lane < 27 * kRefitPairs && p < n_pairs && fits[p].refit != 0;
+    if (__ballot(live) == 0) return;
+    double* A = s_M[g][0];
+    double* V = s_M[g][1];
+    if (live && kind < 2)
+        for (int j = 0; j < 9; ++j) (kind == 0 ? A : V)[9 * k + j] = kind == 0 ? fits[p].A[9 * k + j] : j == k ? 1.0 : 0.0;
+    wave_sync();
+    // this lane's elements of a rotation (p, q): own[p * step], own[q * step]
+    double* own = kind == 0 ? A + 9 * k : kind == 1 ? V + 9 * k : A + k;
+    const int step = kind == 2 ? 9 : 1;
+    // c and s of the rotation at hand; on: it is one (its entry is not 0)
+    double c, s;
+    bool on = live && A[1] != 0.0;
+    schur(A[0], A[10], A[1], c, s);
+    for (int sw = 0; sw < kJacobiSweeps9; ++sw)
+#pragma unroll 1
+        for (int pp = 0; pp < 8; ++pp) {
+            const double* Arow = A + 9 * pp;  // A[pp][..]
+            const double* Acol = A + pp;      // A[..][pp]
+            double* mine = own + step * pp;
+#pragma unroll
+            for (int q = 1; q < 9; ++q) {
+                if (q <= pp) continue;
+                const double app = Arow[pp], apq = Arow[q], aqp = Acol[9 * q], aqq = A[10 * q];
+                double u = *mine, v = own[step * q];
+                // the next rotation's plane: (pp, q + 1), or (pp + 1, pp + 2)
+                const int np = pp < 7 ? pp + 1 : 0;
+                double n_pp = q < 8 ? 0.0 : A[10 * np], n_qq = q < 8 ? A[10 * q + 10] : A[10 * np + 10];
+                double n_pq = q < 8 ? Arow[q + 1] : A[10 * np + 1];
+                const double e = q < 8 ? A[10 * q + 1] : A[9 * np + pp];
+                // the block after the column step
+                const double bpp = c * app - s * apq, bpq = s * app + c * apq;
+                const double bqp = c * aqp - s * aqq, bqq = s * aqp + c * aqq;
+                if (q < 8) {
+                    n_pp = on ? c * bpp - s * bqp : app;
+                    const double w = c * n_pq - s * e;
+                    n_pq = on ? w : n_pq;
+                } else if (pp == 6) {  // (7, 8) follows (6, 8)
+                    const double w = s * e + c * n_pq, z = s * bpq + c * bqq;
+                    n_qq = on ? z : n_qq;
+                    n_pq = on ? w : n_pq;
+                }
+                double c1, s1;
+                schur(n_pp, n_qq, n_pq, c1, s1);
+                const bool at_p = k == pp, at_q = k == q, row = kind == 2;
+                u = row && at_p ? bpp : row && at_q ? bpq : u;
+                v = row && at_p ? bqp : row && at_q ? bqq : v;
+                const double nu = c * u - s * v, nv = s * u + c * v;
+                if (on && (kind != 0 || (!at_p && !at_q))) {
+                    *mine = nu;
+                    own[step * q] = nv;
+                }
+                on = live && n_pq != 0.0;
+                c = c1;
+                s = s1;
+                wave_sync();
+            }
+        }
+    if (live && lane % 27 == 0) {
+        int m = 0;
+        for (int i = 1; i < 9; ++i)
+            if (A[i * 9 + i] < A[m * 9 + m]) m = i;
+        double f[9], F[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) f[i] = V[i * 9 + m];
+        rank2(f);
+        const double* N = fits[p].norm;
+        to_pixels(f, Norm2{N[0], N[1], N[2]}, Norm2{N[3], N[4], N[5]}, F);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) out.F[9 * p + i] = F[i];
+    }
+}
+
+// Inliers of the refit matrices and the pairs' status.
+__global__ __launch_bounds__(256) void fundamental_count_kernel(const GeoImg* __restrict__ imgs,
+                                                                const GeoPair* __restrict__ pairs,
+                                                                const int32_t* __restrict__ match_idx, double thr,
+                                                                const GeoFit* __restrict__ fits, GeoOut out) {
+    __shared__ uint32_t wtot[4];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int64_t p = blockIdx.x;
+    if (fits[p].refit == 0) return;
+    const GeoPair pr = pairs[p];
+    const GeoImg Q = imgs[pr.qi], T = imgs[pr.ti];
+    const double dd = thr * thr;
+    double F[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) F[i] = out.F[9 * p + i];
     uint32_t cnt = 0;
-    for (uint32_t i = tid; i < n; i += 256) cnt += inlier(F, pts[i], dd) ? 1u : 0u;
+    for (int q = tid; q < Q.n; q += 256) {
+        const int32_t m = match_idx[pr.out + q];
+        if (m >= 0 && m < T.n)
+            cnt += inlier(F, make_float4(Q.kp[2 * q], Q.kp[2 * q + 1], T.kp[2 * m], T.kp[2 * m + 1]), dd) ? 1u : 0u;
+    }
     for (int d = 32; d >= 1; d >>= 1) cnt += __shfl_xor(cnt, d);
     if (lane == 0) wtot[wv] = cnt;
     __syncthreads();
-    if (tid < 9) out.F[9 * p + tid] = sF[tid];
     if (tid == 0) {
         const int ni = (int)(wtot[0] + wtot[1] + wtot[2] + wtot[3]);
-        finish(3ll * ni >= 2ll * (long long)n ? kAccept : kFewInliers, ni, bh);
+        out.n_inliers[p] = ni;
+        out.status[p] = 3ll * ni >= 2ll * (long long)out.n_matches[p] ? kAccept : kFewInliers;
     }
 }
 
@@ -612,22 +723,26 @@ hipError_t launch_gather_rows(hipStream_t s, const GatherImg* imgs, const RowChu
     return hipGetLastError();
 }
 
-size_t fundamental_lds_bytes(int cap) { return (size_t)cap * 17; }
+size_t fundamental_lds_bytes(int cap) { return kGeoRowBytes + (size_t)cap * 16; }
 
 hipError_t launch_fundamental(hipStream_t s, const GeoImg* imgs, const GeoPair* pairs, int64_t n_pairs,
                               const int32_t* match_idx, const uint32_t* rnd, const GeoParams& prm, const GeoOut& out,
-                              unsigned* err) {
+                              GeoFit* fits, unsigned* err) {
     if (n_pairs <= 0) return hipSuccess;
     const size_t lds = (fundamental_lds_bytes(prm.cap) + 15) & ~size_t(15);
     if (lds > 65536) {
         // dynamic LDS beyond 64 KB has to be allowed explicitly
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&fundamental_kernel),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&fundamental_fit_kernel),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(fundamental_kernel, dim3((unsigned)n_pairs), dim3(256), lds, s, imgs, pairs, match_idx, rnd,
-                       prm, out, err);
-    return hipGetLastError();
+    CH_LAUNCH(fundamental_fit_kernel, dim3((unsigned)n_pairs), dim3(256), lds, s, imgs, pairs, match_idx, rnd, prm, out,
+              fits, err);
+    CH_LAUNCH(fundamental_refit_kernel, dim3((unsigned)((n_pairs + kRefitPairs - 1) / kRefitPairs)), dim3(64), 0, s, fits,
+              n_pairs, out);
+    CH_LAUNCH(fundamental_count_kernel, dim3((unsigned)n_pairs), dim3(256), 0, s, imgs, pairs, match_idx, prm.thr, fits,
+              out);
+    return hipSuccess;
 }
 
 }  // namespace cashash

@@ -193,6 +193,17 @@ struct GeoOut {
     int32_t* status;      // [P]
 };
 
+// What the fit of a pair leaves for its refit: A^T A of the best hypothesis's
+// inliers and the two normalisations (query s, cx, cy, then train); refit == 0
+// if the pair's outputs are final already.
+struct GeoFit {
+    double A[81];
+    double norm[6];
+    int32_t refit;
+    int32_t pad;
+};
+constexpr size_t kGeoRowBytes = 256 * 9 * sizeof(double);  // LDS of one chunk's design rows
+
 constexpr int kGeoMaxMatches = 8192;  // LDS list of one pair's stage-1 matches (16 B each)
 constexpr int kJacobiSweeps3 = 6;
 constexpr int kJacobiSweeps9 = 10;

@@ -45,5 +45,5 @@ hipError_t launch_gather_rows(hipStream_t s, const GatherImg* imgs, const RowChu
 size_t fundamental_lds_bytes(int cap);
 hipError_t launch_fundamental(hipStream_t s, const GeoImg* imgs, const GeoPair* pairs, int64_t n_pairs,
                               const int32_t* match_idx, const uint32_t* rnd, const GeoParams& prm, const GeoOut& out,
-                              unsigned* err);
+                              GeoFit* fits, unsigned* err);
 }  // namespace cashash

@@ -167,6 +167,24 @@ def test_fundamental_parity(m, n_hyp):
         assert {G.ACCEPT, G.FEW_MATCHES, G.DEGENERATE, G.FEW_INLIERS} <= statuses
 
 
+@pytest.mark.parametrize("n_pairs", [1, 2, 3])
+def test_fundamental_match_counts_around_chunks(m, n_pairs):
+    """Matches around the sums' 64-lane chunks and the refit's 256-row chunks,
+    pairs around the two that a refit wavefront takes (one of them refused)."""
+    rng = np.random.default_rng(40 + n_pairs)
+    rand = _rand(64, seed=3)
+    for n in (8, 9, 63, 64, 65, 255, 256, 257, 513):
+        out = n // 8
+        specs = [(n - out, out, 5, 9, 0.2), (4, 0, 3, 3, 0.0), (n - out, out, 0, 0, 0.4)][:n_pairs]
+        kps, pairs, flat = _fundamental_case(rng, specs)
+        got = m.estimate_fundamental([len(k) for k in kps], _cuda(kps), pairs, torch.from_numpy(flat).cuda(), rand,
+                                     thr=2.0, min_matches=8)
+        exp = _oracle_fundamental(kps, pairs, flat, rand, 2.0, 8)
+        for p, (st, F, ni, bh, nm) in enumerate(exp):
+            assert (got["n_matches"][p], got["status"][p], got["best_h"][p], got["n_inliers"][p]) == (nm, st, bh, ni), (n, p)
+            assert np.array_equal(got["F"][p], F), (n, p)
+
+
 def test_fundamental_many_matches_uses_large_lds(m):
     # 5000 matches per pair needs an 85 KB LDS list
     rng = np.random.default_rng(14)
