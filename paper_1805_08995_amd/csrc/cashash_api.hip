@@ -154,7 +154,11 @@ struct cashash_ctx {
     hipStream_t d2h_stream = nullptr;
     int n_cu = 256;
     std::vector<double> R64;  // [176][128]
-    DevBuf dR64, dR32, dFrag, dBias, dS, dCount;
+    DevBuf dR64, dRt, dR32, dFrag, dBias, dS, dCount;  // dRt: R transposed
+    // the two sets of column sums in dS take turns: each whole-set launch clears
+    // the other one; clean: known to be zero
+    int sum_turn = 0;
+    bool sum_clean[2] = {false, false};
     // uploaded tables (images, pairs, tiles ...): one double-buffered area for
     // the code builder and one for the matcher, so that the matcher's table
     // addresses (baked into captured launches) do not move between calls
@@ -164,9 +168,9 @@ struct cashash_ctx {
     int meta_turn[3] = {0, 0, 0};
     std::vector<uint8_t> meta_last[3][2];  // bytes each meta buffer holds (empty: unknown)
     const void* meta_last_at[3][2] = {};   // ... at this device address
-    DevBuf near, tables;      // near-margin masks; bucket tables
+    DevBuf near, tables;      // near list; bucket tables
     // device-resident row chunks of the last image-size list seen by the
-    // device-memory code builder (column sums: 2048 rows, projection: 16
+    // device-memory code builder (column sums: up to 2048 rows, projection: 16
     // rows), reused while the sizes repeat
     std::vector<int32_t> chunk_key;
     DevBuf chunk_dev;
@@ -225,7 +229,7 @@ static void quiesce(const cashash_ctx* c) {
 }
 
 static std::vector<DevBuf*> dev_bufs(cashash_ctx* c) {
-    return {&c->dR64, &c->dR32, &c->dFrag, &c->dBias, &c->dS, &c->dCount, &c->meta[0][0], &c->meta[0][1],
+    return {&c->dR64, &c->dRt, &c->dR32, &c->dFrag, &c->dBias, &c->dS, &c->dCount, &c->meta[0][0], &c->meta[0][1],
             &c->meta[1][0], &c->meta[1][1], &c->meta[2][0], &c->meta[2][1], &c->near, &c->tables, &c->stage,
             &c->outbuf[0], &c->outbuf[1], &c->items, &c->counters, &c->geo_sub, &c->geo_m1, &c->geo_pair, &c->geo_err, &c->chunk_dev};
 }
@@ -460,15 +464,19 @@ extern "C" int cashash_create(cashash_ctx** out, const double* r_code, const dou
                           &c->slot_free_ev[2], &c->caller_ev, &c->part_ev[0], &c->part_ev[1]})
         if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess)
             return bail(fail(CASHASH_E_DEVICE, "event creation failed"));
-    if ((r = c->pin_small.ensure(1024 + 2 * kCtlWords * 4))) return bail(r);
+    if ((r = c->pin_small.ensure(1024 + 2 * kCtlWords * 4 + kCountWords * 8))) return bail(r);
     std::vector<float> R32(c->R64.size());
     for (size_t i = 0; i < R32.size(); ++i) R32[i] = (float)c->R64[i];
+    std::vector<double> Rt(c->R64.size());
+    for (int j = 0; j < kRows; ++j)
+        for (int i = 0; i < kDim; ++i) Rt[(size_t)i * kRows + j] = c->R64[(size_t)j * kDim + i];
     std::vector<uint16_t> frag = make_frag(c->R64);
     if ((r = c->dR64.ensure(c->R64.size() * 8)) || (r = c->dR32.ensure(R32.size() * 4)) ||
-        (r = c->dFrag.ensure(frag.size() * 2)) || (r = c->dBias.ensure(kRows * 4)) || (r = c->dS.ensure(kDim * 8)) ||
-        (r = c->dCount.ensure(64 * 8)) || (r = c->counters.ensure(kCtlWords * 4)))
+        (r = c->dFrag.ensure(frag.size() * 2)) || (r = c->dBias.ensure(kRows * 4)) || (r = c->dS.ensure(2 * kSumWords * 8)) ||
+        (r = c->dRt.ensure(Rt.size() * 8)) || (r = c->dCount.ensure(kCountWords * 8)) || (r = c->counters.ensure(kCtlWords * 4)))
         return bail(r);
     if (hipMemcpy(c->dR64.p, c->R64.data(), c->R64.size() * 8, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(c->dRt.p, Rt.data(), Rt.size() * 8, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->dR32.p, R32.data(), R32.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->dFrag.p, frag.data(), frag.size() * 2, hipMemcpyHostToDevice) != hipSuccess)
         return bail(fail(CASHASH_E_DEVICE, "upload of projection matrices failed"));
@@ -569,8 +577,16 @@ static int cached_chunks(cashash_ctx* c, const std::vector<ImgDev>& imgs) {
     bool same = c->chunk_key.size() == imgs.size();
     for (size_t m = 0; same && m < imgs.size(); ++m) same = c->chunk_key[m] == imgs[m].n;
     if (same) return CASHASH_OK;
+    // column sums: two blocks per compute unit, of 64 to 2048 rows.  More
+    // blocks add more often to the same words, fewer leave units idle: 800k
+    // descriptors 24.9 us (three per unit 28.7, four 30.1, eight 41), 2 x 2000
+    // descriptors 7.9 us (in blocks of 2048 rows 12.9, and 5.8 for the bias)
+    int64_t rows = 0;
+    for (const ImgDev& im : imgs) rows += im.n;
+    const int64_t blocks = 2 * (int64_t)c->n_cu;
+    const int per = (int)std::min<int64_t>(2048, std::max<int64_t>(64, ((rows + blocks - 1) / blocks + 31) / 32 * 32));
     std::vector<RowChunk> v;
-    row_chunks(imgs, 2048, v);
+    row_chunks(imgs, per, v);
     const int ncol = (int)v.size();
     row_chunks(imgs, 16, v);
     c->chunk_key.clear();
@@ -607,35 +623,35 @@ static int run_colsum(cashash_ctx* c, const std::vector<ImgDev>& imgs, const Row
     return CASHASH_OK;
 }
 
-// Projection + binary64 fix-up of `imgs` into `outs`, given c->dBias and c->dS.
+// Clears the first set of column sums (of launches that add up over several
+// calls) and the recompute counts.
+static int clear_sums(cashash_ctx* c) {
+    c->sum_turn = 0;
+    c->sum_clean[0] = false;
+    HIPCHK(launch_fill_u64(c->stream, c->dS.as<unsigned long long>(), kDim, 0ull));
+    HIPCHK(launch_fill_u64(c->stream, c->dCount.as<unsigned long long>(), kCountWords, 0ull));
+    return CASHASH_OK;
+}
+
+// Recomputes counted so far, from a copy of the counters.
+static int64_t near_total(const unsigned long long* counts) {
+    int64_t n = 0;
+    for (int i = 0; i < kCountSlots; ++i) n += (int64_t)counts[i * kCountStride];
+    return n;
+}
+
+// Projection + binary64 recompute of `imgs` into `outs`, given c->dBias and the
+// sums S.
 // dI, dO: the image and output tables already on the device (with dtiles), or nullptr.
 static int run_project(cashash_ctx* c, const std::vector<ImgDev>& imgs, std::vector<CodeOut> outs, double n_tot,
-                       const RowChunk* dtiles = nullptr, int n_tiles = 0, const ImgDev* dIp = nullptr,
-                       const CodeOut* dOp = nullptr) {
+                       const unsigned long long* S, const RowChunk* dtiles = nullptr, int n_tiles = 0,
+                       const ImgDev* dIp = nullptr, const CodeOut* dOp = nullptr) {
     std::vector<RowChunk> tiles;
     if (!dtiles) {
         row_chunks(imgs, 16, tiles);
         n_tiles = (int)tiles.size();
     }
     if (n_tiles == 0) return CASHASH_OK;
-    const int nt = n_tiles;
-    const bool mfma = c->cfg.mode == CASHASH_MODE_BATCHED_BF16X2;
-    // near list: one segment per projection wavefront, each large enough for
-    // every descriptor that wavefront handles; per-segment counts in front
-    // (MFMA form: a wavefront takes groups of kProjTB tiles, kProjTB * 16 descriptors)
-    const int groups = (nt + kProjTB - 1) / kProjTB;
-    const int grid = mfma ? std::max(1, std::min((groups + 3) / 4, c->n_cu * 8)) : (int)(((int64_t)nt * 16 + 255) / 256);
-    const uint32_t n_seg = (uint32_t)grid * 4;
-    const uint32_t seg_cap = mfma ? (uint32_t)((groups + n_seg - 1) / n_seg) * kProjTB * 16 : 64;
-    const uint64_t n_cap = (uint64_t)n_seg * seg_cap;
-    if (n_cap >= ((uint64_t)1 << 32)) return fail(CASHASH_E_LIMIT, "more than 2^32 near-list places");
-    // segment counts, near list, recompute work area
-    const size_t count_bytes = al256((size_t)n_seg * 4);
-    const size_t list_bytes = al256((size_t)n_cap * sizeof(NearEntry));
-    RETCHK(c->near.ensure(count_bytes + list_bytes + near_work_bytes(n_cap)));
-    uint32_t* seg_count = c->near.as<uint32_t>();
-    NearEntry* near = reinterpret_cast<NearEntry*>(c->near.as<uint8_t>() + count_bytes);
-    void* work = c->near.as<uint8_t>() + count_bytes + list_bytes;
     const ImgDev* dI = dIp;
     const CodeOut* dO = dOp;
     const RowChunk* dT = dtiles;
@@ -651,18 +667,15 @@ static int run_project(cashash_ctx* c, const std::vector<ImgDev>& imgs, std::vec
         if (!dtiles) dT = (const RowChunk*)d[2];
     }
     const float coef = (float)c->cfg.margin_coef;
-    if (mfma) {
-        HIPCHK(launch_proj_mfma(c->stream, grid, dI, dO, dT, nt, c->dFrag.as<uint4>(), c->dBias.as<float>(), coef,
-                                near, seg_count, seg_cap, work));
-    } else {
-        HIPCHK(launch_proj_fp32(c->stream, dI, dO, dT, nt, c->dR32.as<float>(), c->dBias.as<float>(), coef, near,
-                                seg_count, work));
-    }
-    // the recompute: as many wavefronts as the near list has segments, at
-    // most 16 per compute unit
-    const int fix_grid = (int)std::max<int64_t>(1, std::min<int64_t>((n_seg + 3) / 4, (int64_t)c->n_cu * 4));
-    HIPCHK(launch_near_recompute(c->stream, fix_grid, dI, dO, near, seg_count, seg_cap, n_seg, c->dR64.as<double>(),
-                        c->dS.as<unsigned long long>(), n_tot, work, c->dCount.as<unsigned long long>()));
+    unsigned long long* counts = c->dCount.as<unsigned long long>();
+    if (c->cfg.mode == CASHASH_MODE_BATCHED_BF16X2) {
+        const ProjPlan pl = proj_plan(n_tiles, c->n_cu);
+        if (pl.near_bytes()) RETCHK(c->near.ensure(pl.near_bytes()));
+        HIPCHK(launch_proj_mfma(c->stream, dI, dO, dT, n_tiles, c->dFrag.as<uint4>(), c->dBias.as<float>(), coef,
+                                c->dR64.as<double>(), S, n_tot, counts, pl, c->near.p));
+    } else
+        HIPCHK(launch_proj_fp32(c->stream, dI, dO, dT, n_tiles, c->dR32.as<float>(), c->dBias.as<float>(), coef,
+                                c->dR64.as<double>(), S, n_tot, counts));
     return CASHASH_OK;
 }
 
@@ -693,17 +706,23 @@ static int build_codes_device(cashash_ctx* c, const cashash_images* im, uint64_t
     up.add(outs);
     std::vector<const void*> d;
     RETCHK(upload_meta(c, up, d, kMetaCodes));
-    HIPCHK(launch_fill_u64(c->stream, c->dS.as<unsigned long long>(), kDim, 0ull));
-    HIPCHK(launch_fill_u64(c->stream, c->dCount.as<unsigned long long>(), 8, 0ull));
-    RETCHK(run_colsum(c, imgs, dch, c->chunk_ncol, (const ImgDev*)d[0]));
-    HIPCHK(launch_bias(c->stream, c->dR64.as<double>(), c->dS.as<unsigned long long>(), n_tot, c->dBias.as<float>()));
-    RETCHK(run_project(c, imgs, outs, n_tot, dch + c->chunk_ncol, c->chunk_ntile, (const ImgDev*)d[0],
+    const int turn = c->sum_turn;
+    unsigned long long* S = c->dS.as<unsigned long long>() + turn * kSumWords;
+    unsigned long long* next_S = c->dS.as<unsigned long long>() + (turn ^ 1) * kSumWords;
+    if (!c->sum_clean[turn]) HIPCHK(launch_fill_u64(c->stream, S, kSumClear, 0ull));
+    c->sum_clean[0] = c->sum_clean[1] = false;
+    HIPCHK(launch_colsum_bias(c->stream, (const ImgDev*)d[0], dch, c->chunk_ncol, S, c->dRt.as<double>(), n_tot,
+                              c->dBias.as<float>(), next_S, c->dCount.as<unsigned long long>()));
+    RETCHK(run_project(c, imgs, outs, n_tot, S + kSumTotal, dch + c->chunk_ncol, c->chunk_ntile, (const ImgDev*)d[0],
                        (const CodeOut*)d[1]));
-    // the recompute count through pinned memory (offset 128 of pin_small)
-    unsigned long long* pc = reinterpret_cast<unsigned long long*>(static_cast<uint8_t*>(c->pin_small.p) + 128);
-    HIPCHK(hipMemcpyAsync(pc, c->dCount.p, 8, hipMemcpyDeviceToHost, c->stream));
+    // the recompute counts through pinned memory, after the matcher's control words
+    unsigned long long* pc = reinterpret_cast<unsigned long long*>(static_cast<uint8_t*>(c->pin_small.p) + 1024 +
+                                                                   2 * kCtlWords * 4);
+    HIPCHK(hipMemcpyAsync(pc, c->dCount.p, kCountWords * 8, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
-    *near_count = (int64_t)*pc;
+    c->sum_turn = turn ^ 1;
+    c->sum_clean[turn ^ 1] = true;  // by the finished launch
+    *near_count = near_total(pc);
     return CASHASH_OK;
 }
 
@@ -1364,10 +1383,7 @@ static int build_codes_host(cashash_ctx* c, const cashash_images* im, uint64_t* 
     };
     std::vector<ImgDev> iv;
     std::vector<CodeOut> ov;
-    if (both) {
-        HIPCHK(launch_fill_u64(c->stream, c->dS.as<unsigned long long>(), kDim, 0ull));
-        HIPCHK(launch_fill_u64(c->stream, c->dCount.as<unsigned long long>(), 8, 0ull));
-    }
+    if (both) RETCHK(clear_sums(c));
     if (passes & kPassSums) {
         for (int b = 0; b < nb; ++b) {
             const int s = b & 1;
@@ -1380,7 +1396,7 @@ static int build_codes_host(cashash_ctx* c, const cashash_images* im, uint64_t* 
         }
     }
     if (both)
-        HIPCHK(launch_bias(c->stream, c->dR64.as<double>(), c->dS.as<unsigned long long>(), n_tot,
+        HIPCHK(launch_bias(c->stream, c->dRt.as<double>(), c->dS.as<unsigned long long>(), n_tot,
                            c->dBias.as<float>()));
     for (int b = nb - 1; (passes & kPassCodes) && b >= 0; --b) {
         int s = resident[0] == b ? 0 : resident[1] == b ? 1 : (b & 1);
@@ -1391,7 +1407,7 @@ static int build_codes_host(cashash_ctx* c, const cashash_images* im, uint64_t* 
         RETCHK(c->outbuf[0].ensure(std::max<size_t>(out_bytes, 16)));
         RETCHK(c->pin_out[0].ensure(std::max<size_t>(out_bytes, 16)));
         views(b, iv, &ov, c->outbuf[0].as<uint8_t>());
-        RETCHK(run_project(c, iv, ov, both ? n_tot : n_tot_set));
+        RETCHK(run_project(c, iv, ov, both ? n_tot : n_tot_set, c->dS.as<unsigned long long>()));
         HIPCHK(hipEventRecord(c->slot_free_ev[s], c->stream));
         HIPCHK(hipMemcpyAsync(c->pin_out[0].p, c->outbuf[0].p, out_bytes, hipMemcpyDeviceToHost, c->stream));
         HIPCHK(hipStreamSynchronize(c->stream));
@@ -1405,10 +1421,10 @@ static int build_codes_host(cashash_ctx* c, const cashash_images* im, uint64_t* 
         });
         for (int m = first[b]; m < first[b + 1]; ++m) d2h += (int64_t)im->n_feat[m] * 22;
     }
-    unsigned long long cnt = 0;
+    unsigned long long counts[kCountWords];
     HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipMemcpy(&cnt, c->dCount.p, 8, hipMemcpyDeviceToHost));
-    *near_count = (int64_t)cnt;
+    HIPCHK(hipMemcpy(counts, c->dCount.p, sizeof counts, hipMemcpyDeviceToHost));
+    *near_count = near_total(counts);
     if (stats) {
         stats->h2d_bytes += h2d;
         stats->d2h_bytes += d2h;
@@ -2382,8 +2398,7 @@ extern "C" int cashash_build_codes_disk(cashash_ctx* c, const char* set_path, co
     if (!write_at(out.fd, kCodMagic, 8, 0) || !write_at(out.fd, hdr, 16, 8) ||
         ::ftruncate(out.fd, (off_t)(kFileHeader + N * 22)) != 0)
         return fail(CASHASH_E_IO, "write to %s failed", codes_path);
-    HIPCHK(launch_fill_u64(c->stream, c->dS.as<unsigned long long>(), kDim, 0ull));
-    HIPCHK(launch_fill_u64(c->stream, c->dCount.as<unsigned long long>(), 8, 0ull));
+    RETCHK(clear_sums(c));
     int64_t near = 0;
     for (int pass = 0; pass < 2; ++pass) {
         // first line: the group in progress; second line: the next group read ahead
@@ -2422,7 +2437,7 @@ extern "C" int cashash_build_codes_disk(cashash_ctx* c, const char* set_path, co
             group_loads += g + 1 < ng;
         }
         if (pass == 0 && N > 0)
-            HIPCHK(launch_bias(c->stream, c->dR64.as<double>(), c->dS.as<unsigned long long>(), (double)N,
+            HIPCHK(launch_bias(c->stream, c->dRt.as<double>(), c->dS.as<unsigned long long>(), (double)N,
                                c->dBias.as<float>()));
     }
     if (::fdatasync(out.fd) != 0) return fail(CASHASH_E_IO, "sync of %s failed", codes_path);

@@ -16,10 +16,6 @@ namespace cashash {
 
 // ------------------------------------------------------------------ utilities
 
-// Control words of the binary64 recompute (jobs per row, overflow flag),
-// cleared by block 0 of the projection kernel (256 threads) before use.
-constexpr int kNearCtlWords = 256;
-
 __global__ void fill_u64_kernel(unsigned long long* p, int64_t n, unsigned long long v) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -52,21 +48,51 @@ __global__ void make_items_kernel(const PairTiles* __restrict__ pt, int32_t n_pt
 }
 
 // ------------------------------------------------------------------ column sums
-// One block per chunk of <= 2048 rows.  Thread t reads the 16-byte column
-// group t % 8 of rows t / 8, t / 8 + 32, ...; partial column totals meet in
-// LDS and each column is added to the int64 sums with one atomic.
+// bias_j = (r_j . S) / N in binary64, rounded once to fp32 for the fast path.
+// One block of at least kRows threads; Rt is R transposed ([128][kRows]: a
+// component's values side by side), s_S the sums in LDS.
+__device__ __forceinline__ void bias_block(const double* __restrict__ Rt, const double* s_S, double n_tot,
+                                           float* __restrict__ bias) {
+    const int j = threadIdx.x;
+    if (j >= kRows) return;
+    double acc = 0.0;
+#pragma unroll 32
+    for (int i = 0; i < kDim; ++i) acc = fma(Rt[i * kRows + j], s_S[i], acc);
+    bias[j] = (float)(acc / n_tot);
+}
+
+// One block per chunk of rows.  Thread t reads the 16-byte column group t % 8
+// of rows t / 8, t / 8 + 32, ...; partial column totals meet in LDS and each
+// column is added to the int64 sums with one atomic.
+// WHOLE: the grid covers the whole set.  The blocks add to one of kSumSlots
+// copies of the sums (one copy's 128 addresses would queue every block's
+// atomics); the last block to finish (a ticket after its sums) adds the copies
+// up, sets the bias, and clears the copies that the next call will use and the
+// recompute counts, so that none of it needs a launch.  An atomic's returned
+// value is the proof that it took place, which is all that the ticket must
+// follow: a fence here would write the caches back once per wavefront (800k
+// descriptors: 56 us with it).
+// Bound by the read and by the adds at its end: 800k descriptors 24.9 us, 4.1
+// TB/s (29 + 7 us with the bias a launch of its own).
+template <bool WHOLE>
 __global__ __launch_bounds__(256) void colsum_kernel(const ImgDev* __restrict__ imgs,
                                                      const RowChunk* __restrict__ chunks,
-                                                     unsigned long long* __restrict__ S) {
+                                                     unsigned long long* __restrict__ S, const double* __restrict__ Rt,
+                                                     double n_tot, float* __restrict__ bias,
+                                                     unsigned long long* __restrict__ next_S,
+                                                     unsigned long long* __restrict__ counts) {
     __shared__ uint32_t part[32][kDim + 1];
+    __shared__ double s_S[kDim];
+    __shared__ uint32_t s_last;
     const RowChunk ch = chunks[blockIdx.x];
     const uint8_t* base = imgs[ch.img].desc + (int64_t)ch.r0 * kDim;
     const int g = threadIdx.x & 7, rl = threadIdx.x >> 3;
     uint32_t s[16];
 #pragma unroll
     for (int c = 0; c < 16; ++c) s[c] = 0;
+#pragma unroll 8
     for (int r = rl; r < ch.nr; r += 32) {
-        const uint4 w = *reinterpret_cast<const uint4*>(base + (int64_t)r * kDim + g * 16);
+        const uint4 w = gload(reinterpret_cast<const uint4*>(base + (int64_t)r * kDim + g * 16));
         const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
         for (int a = 0; a < 4; ++a)
@@ -76,21 +102,43 @@ __global__ __launch_bounds__(256) void colsum_kernel(const ImgDev* __restrict__ 
 #pragma unroll
     for (int c = 0; c < 16; ++c) part[rl][g * 16 + c] = s[c];
     __syncthreads();
+    unsigned long long* to = S + (WHOLE ? (blockIdx.x % kSumSlots) * kDim : 0);
     if (threadIdx.x < kDim) {
         uint32_t tot = 0;
         for (int r = 0; r < 32; ++r) tot += part[r][threadIdx.x];
-        atomicAdd(&S[threadIdx.x], (unsigned long long)tot);
+        const unsigned long long old = atomicAdd(&to[threadIdx.x], (unsigned long long)tot);
+        if constexpr (WHOLE) asm volatile("" ::"v"(old) : "memory");
+    }
+    if constexpr (WHOLE) {
+        __syncthreads();
+        unsigned long long* ticket = S + kSumSlots * kDim;
+        if (threadIdx.x == 0) s_last = atomicAdd(ticket, 1ull) + 1ull == (unsigned long long)gridDim.x;
+        __syncthreads();
+        if (!s_last) return;
+        if (threadIdx.x < kDim) {
+            unsigned long long tot = 0, v[kSumSlots];
+#pragma unroll
+            for (int q = 0; q < kSumSlots; ++q) v[q] = atomicAdd(&S[q * kDim + threadIdx.x], 0ull);
+#pragma unroll
+            for (int q = 0; q < kSumSlots; ++q) tot += v[q];
+            S[kSumTotal + threadIdx.x] = tot;
+            s_S[threadIdx.x] = (double)tot;
+        }
+        for (int i = threadIdx.x; i <= kSumSlots * kDim; i += 256) next_S[i] = 0ull;
+        for (int i = threadIdx.x; i < kCountWords; i += 256) counts[i] = 0ull;
+        __syncthreads();
+        bias_block(Rt, s_S, n_tot, bias);
     }
 }
 
-// bias_j = (r_j . S) / N in binary64, rounded once to fp32 for the fast path.
-__global__ void bias_kernel(const double* __restrict__ R, const unsigned long long* __restrict__ S,
-                            double n_tot, float* __restrict__ bias) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= kRows) return;
-    double acc = 0.0;
-    for (int i = 0; i < kDim; ++i) acc = fma(R[j * kDim + i], (double)S[i], acc);
-    bias[j] = (float)(acc / n_tot);
+// The bias alone, of sums added up over several launches.
+__global__ __launch_bounds__(256) void bias_kernel(const double* __restrict__ Rt,
+                                                   const unsigned long long* __restrict__ S, double n_tot,
+                                                   float* __restrict__ bias) {
+    __shared__ double s_S[kDim];
+    if (threadIdx.x < kDim) s_S[threadIdx.x] = (double)S[threadIdx.x];
+    __syncthreads();
+    bias_block(Rt, s_S, n_tot, bias);
 }
 
 // ------------------------------------------------------------------ projection
@@ -118,142 +166,488 @@ __device__ __forceinline__ bf16x8 load_frag(const uint4* __restrict__ frag, int 
     return cv.v;
 }
 
-// Writes the fast bits of one descriptor (near-margin bits are 0 until the
-// binary64 recompute) and, if any row is flagged, appends it to the
-// wavefront's own segment of the near list (seg[cnt ..]); cnt is the
-// wave-uniform fill of that segment.  No atomics: each wave owns its segment.
-__device__ __forceinline__ void store_code(const CodeOut& o, int img, int row, bool live, uint64_t w0, uint64_t w1,
-                                           uint64_t w2, uint64_t m0, uint64_t m1, uint64_t m2,
-                                           NearEntry* __restrict__ seg, uint32_t& cnt) {
-    if (live) {
-        gstore(reinterpret_cast<ulonglong2*>(o.codes) + row, make_ulonglong2(w0, w1));
-        uint16_t* kp = reinterpret_cast<uint16_t*>(o.keys + 6 * (int64_t)row);
-        gstore(kp, (uint16_t)(w2 & 0xFFFFu));
-        gstore(kp + 1, (uint16_t)((w2 >> 16) & 0xFFFFu));
-        gstore(kp + 2, (uint16_t)((w2 >> 32) & 0xFFFFu));
+// ---- binary64 recompute
+// Near-margin projections are recomputed with the same fused multiply-add
+// chain over components 0..127 of r_j . (N x - S) that defines the codes
+// (N x_i - S_i is an exact integer in binary64), row rp per lane (vector loads,
+// 16 components at a time).
+// Each group of 16 is loaded while the one before it is multiplied.
+__device__ __forceinline__ double near_chain(const uint8_t* x, const double* rp, const double* s_S, double n_tot) {
+    const uint4* xp = reinterpret_cast<const uint4*>(x);
+    const double2* rr = reinterpret_cast<const double2*>(rp);
+    double2 rv[2][8];
+    uint4 xv[2];
+    auto fetch = [&](int h, int q) {
+        xv[h] = gload(xp + q);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) rv[h][i] = rr[8 * q + i];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    double p = 0.0;
+    auto chain = [&](int h, int q) {
+        const uint32_t xw[4] = {xv[h].x, xv[h].y, xv[h].z, xv[h].w};
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const double c = n_tot * (double)((xw[i >> 2] >> (8 * (i & 3))) & 0xFFu) - s_S[16 * q + i];
+            p = fma((i & 1) ? rv[h][i >> 1].y : rv[h][i >> 1].x, c, p);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    fetch(0, 0);
+#pragma unroll 1
+    for (int q = 0; q < 8; q += 2) {
+        fetch(1, q + 1);
+        chain(0, q);
+        fetch(0, min(q + 2, 7));
+        chain(1, q + 1);
     }
-    const bool flagged = live && (m0 | m1 | m2) != 0;
-    const uint64_t fm = __ballot(flagged);
-    if (fm == 0) return;
-    if (flagged) {
-        NearEntry& e = seg[cnt + mbcnt64(fm)];
-        e.img = img;
-        e.row = row;
-        e.mask[0] = m0;
-        e.mask[1] = m1;
-        e.mask[2] = m2;
-    }
-    cnt += (uint32_t)__popcll(fm);
+    return p;
 }
 
-// BF16 hi+lo split on MFMA.  One wave per group of kProjTB tiles of 16
-// descriptors: for each of the 11 row tiles, D[16 rows][16 desc] = sum over
-// 4 k-steps of (R_hi + R_lo)[rows][32 k] x X^T[32 k][desc] with
-// v_mfma_f32_16x16x32_bf16.  Each fragment of R is loaded once per group and
-// applied to every tile of it.  Lane l holds descriptor l % 16 of each tile
-// and rows 4 (l / 16) .. +3 of each row tile.
-__global__ __launch_bounds__(256) void proj_mfma_kernel(const ImgDev* __restrict__ imgs,
-                                                        const CodeOut* __restrict__ outs,
-                                                        const RowChunk* __restrict__ tiles, int n_tiles,
-                                                        const uint4* __restrict__ frag,
-                                                        const float* __restrict__ bias, float margin_coef,
-                                                        NearEntry* __restrict__ near,
-                                                        uint32_t* __restrict__ seg_count, uint32_t seg_cap,
-                                                        uint32_t* __restrict__ near_ctl) {
-    if (blockIdx.x == 0) near_ctl[threadIdx.x] = 0u;  // the recompute's control words (kNearCtlWords)
-    constexpr int TB = kProjTB;
-    const int lane = threadIdx.x & 63;
-    const int n = lane & 15, g = lane >> 4;
-    const int n_waves = (gridDim.x * blockDim.x) >> 6;
-    const int wave = (int)uniform((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-    NearEntry* seg = near + (size_t)wave * seg_cap;
-    uint32_t cnt = 0;
-    for (int t0 = wave * TB; t0 < n_tiles; t0 += n_waves * TB) {
-        RowChunk tc[TB];
-        bool live[TB];
-        bf16x8 xb[TB][4];
-        float base_margin[TB];
+// What a block of projections shares: DESC descriptors' bits and the bits of
+// the projections inside the margin, 176 in six words each.
+template <int DESC>
+struct ProjBlock {
+    uint32_t bits[DESC][6], near[DESC][6];
+    const uint8_t* x[DESC];
+    uint32_t pre[DESC];  // inclusive prefix of the recomputes per descriptor
+    double S[kDim];
+
+    // The flagged projections of the block (their bits are 0 so far), one per
+    // thread whichever descriptor and row they belong to; positive values set
+    // their bit.  A flagged projection of 64 descriptors is one of about 15, so
+    // a block's chains run side by side, beside other blocks' products.
+    // Returns after a barrier.  counts: kCountSlots counters a line apart (one
+    // address for every block's atomic would queue them).
+    __device__ __forceinline__ void recompute(const double* __restrict__ R, double n_tot,
+                                              unsigned long long* __restrict__ counts) {
+        const int tid = threadIdx.x;
+        if (tid < 64) {
+            uint32_t carry = 0;
+            for (int d0 = 0; d0 < DESC; d0 += 64) {
+                uint32_t c = 0;
 #pragma unroll
-        for (int b = 0; b < TB; ++b) {
-            const bool in = t0 + b < n_tiles;
-            tc[b] = tiles[in ? t0 + b : t0];
-            live[b] = in && n < tc[b].nr;
-            const uint8_t* x = imgs[tc[b].img].desc + (int64_t)(tc[b].r0 + (live[b] ? n : 0)) * kDim;
+                for (int w = 0; w < 6; ++w) c += (uint32_t)__popc(near[d0 + tid][w]);
+                const uint32_t incl = carry + wave_incl_scan(c, tid);
+                pre[d0 + tid] = incl;
+                carry = (uint32_t)__shfl((int)incl, 63);
+            }
+        }
+        __syncthreads();
+        const uint32_t total = pre[DESC - 1];
+        for (uint32_t j = tid; j < total; j += 256) {
+            // owner: the first descriptor whose prefix exceeds j
+            uint32_t L = 0;
+#pragma unroll
+            for (uint32_t step = DESC / 2; step >= 1; step >>= 1)
+                if (pre[L + step - 1] <= j) L += step;
+            uint32_t kth = j - (L ? pre[L - 1] : 0u);
+            int w = 0;
+            uint32_t m = near[L][0];
+            for (uint32_t c = (uint32_t)__popc(m); kth >= c; c = (uint32_t)__popc(m)) {
+                kth -= c;
+                m = near[L][++w];
+            }
+            for (uint32_t t = 0; t < kth; ++t) m &= m - 1;
+            const int bit = __ffs(m) - 1;
+            if (near_chain(x[L], R + (size_t)(32 * w + bit) * kDim, S, n_tot) > 0.0) atomicOr(&bits[L][w], 1u << bit);
+        }
+        if (tid == 0 && total) atomicAdd(counts + (blockIdx.x % kCountSlots) * kCountStride, (unsigned long long)total);
+        __syncthreads();
+    }
+};
+
+// Code and keys of one descriptor, from its 176 bits in six words.
+__device__ __forceinline__ void store_code(const CodeOut& o, int row, const uint32_t* b) {
+    gstore(reinterpret_cast<ulonglong2*>(o.codes) + row,
+           make_ulonglong2((uint64_t)b[0] | ((uint64_t)b[1] << 32), (uint64_t)b[2] | ((uint64_t)b[3] << 32)));
+    uint16_t* kp = reinterpret_cast<uint16_t*>(o.keys + 6 * (int64_t)row);
+    gstore(kp, (uint16_t)b[4]);
+    gstore(kp + 1, (uint16_t)(b[4] >> 16));
+    gstore(kp + 2, (uint16_t)b[5]);
+}
+
+// BF16 hi+lo split on MFMA: D[16 rows][16 desc] = sum over 4 k-steps of
+// (R_hi + R_lo)[rows][32 k] x X^T[32 k][desc] with v_mfma_f32_16x16x32_bf16.
+// A block keeps all of R in registers, wavefront w the row tiles w, w + 4 and
+// w + 8 of 11, and takes groups of tpg <= 4 tiles of 16 descriptors, n_groups
+// in all, a grid apart: wavefront w widens tile w's descriptors (loaded during
+// the group before) to bf16 fragments in LDS, every wavefront multiplies every
+// tile by its rows, and wavefront k < 3 stores word k of codes and keys.
+// (With R read from L2 for each group of 64 descriptors that was 1.1 GB at
+// 800k descriptors.)  Where a tile's rows lie and go is worked out for
+// kTileRun groups at once: the dependent loads behind it would not fit between
+// two groups.
+// Lane l holds descriptor l % 16 of a tile and rows 4 (l / 16) .. +3 of each
+// row tile.  A value v is positive where its sign bit is clear, inside the
+// margin M where that of M - |v| is (the difference of two fp32 numbers has
+// the exact sign), so both tests are one shift each into a word of 12 bits.
+// FUSED: a block takes one group, and recomputes what lies inside the margin
+// itself; otherwise words with such bits go into the block's three segments
+// of the near list (seg_cap entries each) for near_kernel.
+// 800k descriptors: 89 us (123 with R from L2 for each wavefront and the bits
+// unpacked in every lane), of which the products alone are 31 and the vector
+// instructions around them 41; leaving out loads or stores changes nothing.
+// 4000 descriptors: 10 us with the recompute (17.5 + 29 as four launches).
+template <bool FUSED>
+__global__ __launch_bounds__(256, 2) void proj_mfma_kernel(const ImgDev* __restrict__ imgs,
+                                                           const CodeOut* __restrict__ outs,
+                                                           const RowChunk* __restrict__ tiles, int n_tiles, int tpg,
+                                                           int n_groups, const uint4* __restrict__ frag,
+                                                           const float* __restrict__ bias, float margin_coef,
+                                                           const double* __restrict__ R,
+                                                           const unsigned long long* __restrict__ S, double n_tot,
+                                                           unsigned long long* __restrict__ counts,
+                                                           NearEntry* __restrict__ near,
+                                                           uint32_t* __restrict__ seg_count, uint32_t seg_cap) {
+    constexpr int DESC = 16 * kProjTB;
+    constexpr int kTileRun = FUSED ? 1 : 16;
+    static_assert(kProjTB == 4, "a wavefront per tile");
+    struct Tile {
+        const uint8_t* x;
+        uint64_t* codes;
+        uint8_t* keys;
+        int32_t img, row, nr, pad;
+    };
+    __shared__ __attribute__((aligned(16))) uint4 s_x[kProjTB][4][64];  // bf16 fragments [tile][k step][lane]
+    __shared__ float s_margin[DESC];
+    // [descriptor][4 wavefront + row group]: signs, margin hits << 16
+    __shared__ __attribute__((aligned(16))) uint32_t s_out[DESC][20];
+    __shared__ Tile s_tile[kTileRun][kProjTB];
+    __shared__ ProjBlock<FUSED ? DESC : 1> blk;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = (int)uniform((uint32_t)tid >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const bool third = wv + 8 < kRowTiles;
+    const int step = (int)gridDim.x;
+    // tiles of the kTileRun groups from grp on (nr 0: none there)
+    auto set_tiles = [&](int grp) {
+        if (tid < kTileRun * kProjTB) {
+            const int b = tid % kProjTB;
+            const int gi = grp + (tid / kProjTB) * step;
+            const int t = gi * tpg + b;
+            Tile r{};
+            if (gi < n_groups && b < tpg && t < n_tiles) {
+                const RowChunk tc = tiles[t];
+                const CodeOut o = outs[tc.img];
+                r.x = imgs[tc.img].desc + (int64_t)tc.r0 * kDim;
+                r.codes = o.codes + 2 * (int64_t)tc.r0;
+                r.keys = o.keys + 6 * (int64_t)tc.r0;
+                r.img = tc.img;
+                r.row = tc.r0;
+                r.nr = tc.nr;
+            }
+            s_tile[tid / kProjTB][b] = r;
+        }
+    };
+    int grp = blockIdx.x;
+    set_tiles(grp);
+    if constexpr (FUSED)
+        if (tid < kDim) blk.S[tid] = (double)S[tid];
+    bf16x8 fr[3][4][2];
+    float bv[3][4], mb[3][4];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int rt = k < 2 || third ? wv + 4 * k : wv;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            fr[k][ks][0] = load_frag(frag, ((0 * kRowTiles + rt) * 4 + ks) * 64 + lane);
+            fr[k][ks][1] = load_frag(frag, ((1 * kRowTiles + rt) * 4 + ks) * 64 + lane);
+        }
+        const float4 bq = reinterpret_cast<const float4*>(bias)[rt * 4 + g];
+        bv[k][0] = bq.x, bv[k][1] = bq.y, bv[k][2] = bq.z, bv[k][3] = bq.w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mb[k][i] = 0x1p-20f * fabsf(bv[k][i]);
+    }
+    __syncthreads();
+    // this lane's 8-byte pieces of its descriptor of this wavefront's tile of
+    // group `slot` of the run
+    uint2 w[4];
+    bool live = false;
+    auto fetch = [&](int slot) {
+        const Tile& t = s_tile[slot][wv];
+        live = n < t.nr;
+        const uint8_t* x = t.x + n * kDim + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            w[ks] = live ? gload(reinterpret_cast<const uint2*>(x + 32 * ks)) : make_uint2(0u, 0u);
+    };
+    fetch(0);
+    uint32_t cnt = 0;  // near-list entries so far (wavefronts 0 to 2)
+    int slot = 0;
+    for (; grp < n_groups; grp += step) {
+        {
             uint32_t sq = 0;
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
-                const uint2 w = live[b] ? gload(reinterpret_cast<const uint2*>(x + 32 * ks + 8 * g)) : make_uint2(0u, 0u);
-                sq = __builtin_amdgcn_udot4(w.x, w.x, sq, false);
-                sq = __builtin_amdgcn_udot4(w.y, w.y, sq, false);
-                xb[b][ks] = bytes_to_bf16x8(w);
+                sq = __builtin_amdgcn_udot4(w[ks].x, w[ks].x, sq, false);
+                sq = __builtin_amdgcn_udot4(w[ks].y, w[ks].y, sq, false);
+                s_x[wv][ks][lane] = make_uint4(bf16_pair(w[ks].x, 0), bf16_pair(w[ks].x, 16), bf16_pair(w[ks].y, 0),
+                                               bf16_pair(w[ks].y, 16));
             }
             sq += __shfl_xor(sq, 16);
             sq += __shfl_xor(sq, 32);
-            base_margin[b] = margin_coef * sqrtf((float)sq) + 0x1p-26f;
+            if (g == 0) {
+                // (rows past a tile's end are never inside the margin)
+                s_margin[16 * wv + n] = live ? margin_coef * sqrtf((float)sq) + 0x1p-26f : -__builtin_inff();
+                if constexpr (FUSED) blk.x[16 * wv + n] = s_tile[0][wv].x + (live ? n * kDim : 0);
+            }
         }
-        // this lane's bits, packed: row 16 rw + 4 g + i of row block k at bit
-        // 16 (k & 1) + 4 rw + i of word k >> 1 (its own g only)
-        uint32_t pw[TB][2], pm[TB][2];
+        __syncthreads();
+        const bool more = slot + 1 < kTileRun;
+        if (more) fetch(slot + 1);
+        // the fragments of a tile are read while the tile before it is multiplied
+        struct Frags {
+            bf16x8 x[4];
+            float base;
+        };
+        auto frags = [&](int b) {
+            Frags f;
 #pragma unroll
-        for (int b = 0; b < TB; ++b) pw[b][0] = pw[b][1] = pm[b][0] = pm[b][1] = 0u;
+            for (int ks = 0; ks < 4; ++ks) {
+                union {
+                    uint4 u;
+                    bf16x8 v;
+                } cv;
+                cv.u = s_x[b][ks][lane];
+                f.x[ks] = cv.v;
+            }
+            f.base = s_margin[16 * b + n];
+            return f;
+        };
+        auto tile = [&](int b, auto nrt, const Frags& f) {
+            constexpr int NRT = decltype(nrt)::value;
+            f32x4 acc[NRT];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const int n_rt = k < 2 ? 4 : kRowTiles - 8;
-#pragma unroll 1
-            for (int rw = 0; rw < n_rt; ++rw) {
-                const int rt = 4 * k + rw;
-                f32x4 acc[TB];
+            for (int k = 0; k < NRT; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int b = 0; b < TB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    const bf16x8 fh = load_frag(frag, ((0 * kRowTiles + rt) * 4 + ks) * 64 + lane);
-                    const bf16x8 fl = load_frag(frag, ((1 * kRowTiles + rt) * 4 + ks) * 64 + lane);
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int b = 0; b < TB; ++b) {
-                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh, xb[b][ks], acc[b], 0, 0, 0);
-                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl, xb[b][ks], acc[b], 0, 0, 0);
+                    for (int k = 0; k < NRT; ++k)
+                        acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[k][ks][h], f.x[ks], acc[k], 0, 0, 0);
+            uint32_t neg = 0, far = 0;
+#pragma unroll
+            for (int k = NRT - 1; k >= 0; --k)
+#pragma unroll
+                for (int i = 3; i >= 0; --i) {
+                    const float v = acc[k][i] - bv[k][i];
+                    const float d = (f.base + mb[k][i]) - fabsf(v);
+                    neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(v), 31);
+                    far = __builtin_amdgcn_alignbit(far, __float_as_uint(d), 31);
+                }
+            constexpr uint32_t kAll = (1u << (4 * NRT)) - 1u;
+            s_out[16 * b + n][4 * wv + g] = (far & (neg ^ kAll)) | ((far ^ kAll) << 16);
+        };
+        auto product = [&](auto nrt) {
+            Frags f[2];
+            f[0] = frags(0);
+            if constexpr (FUSED) {
+                for (int b = 0; b < tpg; ++b) {
+                    f[1] = frags(min(b + 1, tpg - 1));
+                    __builtin_amdgcn_sched_barrier(0);
+                    tile(b, nrt, f[0]);
+                    f[0] = f[1];
+                }
+            } else {
+#pragma unroll
+                for (int b = 0; b < kProjTB; ++b) {
+                    if (b + 1 < kProjTB) f[(b + 1) & 1] = frags(b + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    tile(b, nrt, f[b & 1]);
+                }
+            }
+        };
+        if (third)
+            product(std::integral_constant<int, 3>{});
+        else
+            product(std::integral_constant<int, 2>{});
+        __syncthreads();
+        if (third) {
+            // word wv of descriptor `lane` of the group: row tiles 4 wv .. + 3
+            const Tile& t = s_tile[slot][g];
+            const bool in = n < t.nr;
+            uint32_t bits[2] = {0u, 0u}, nr[2] = {0u, 0u};
+#pragma unroll
+            for (int w4 = 0; w4 < 4; ++w4) {
+                const uint4 q = *reinterpret_cast<const uint4*>(&s_out[lane][4 * w4]);
+                const uint32_t v[4] = {q.x >> (4 * wv), q.y >> (4 * wv), q.z >> (4 * wv), q.w >> (4 * wv)};
+#pragma unroll
+                for (int gg = 0; gg < 4; ++gg) {
+                    bits[w4 >> 1] |= (v[gg] & 0xFu) << (16 * (w4 & 1) + 4 * gg);
+                    nr[w4 >> 1] |= ((v[gg] >> 16) & 0xFu) << (16 * (w4 & 1) + 4 * gg);
+                }
+            }
+            if (!in) nr[0] = nr[1] = 0u;
+            if constexpr (FUSED) {
+                blk.bits[lane][2 * wv] = bits[0];
+                blk.bits[lane][2 * wv + 1] = bits[1];
+                blk.near[lane][2 * wv] = nr[0];
+                blk.near[lane][2 * wv + 1] = nr[1];
+            } else {
+                if (in) {
+                    if (wv < 2) {
+                        gstore(t.codes + 2 * n + wv, (uint64_t)bits[0] | ((uint64_t)bits[1] << 32));
+                    } else {
+                        uint16_t* kp = reinterpret_cast<uint16_t*>(t.keys + 6 * n);
+                        gstore(kp, (uint16_t)bits[0]);
+                        gstore(kp + 1, (uint16_t)(bits[0] >> 16));
+                        gstore(kp + 2, (uint16_t)bits[1]);
                     }
                 }
-                const float4 bq = reinterpret_cast<const float4*>(bias)[rt * 4 + g];
-                const float bv[4] = {bq.x, bq.y, bq.z, bq.w};
-#pragma unroll
-                for (int b = 0; b < TB; ++b)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float v = acc[b][i] - bv[i];
-                        const float M = base_margin[b] + 0x1p-20f * fabsf(bv[i]);
-                        const bool nr = !(fabsf(v) > M);
-                        const bool bit = !nr && v > 0.f;
-                        const int pos = 16 * (k & 1) + 4 * rw + i;
-                        pw[b][k >> 1] |= (uint32_t)bit << pos;
-                        pm[b][k >> 1] |= (uint32_t)nr << pos;
-                    }
+                const bool flagged = (nr[0] | nr[1]) != 0;
+                const uint64_t fm = __ballot(flagged);
+                if (flagged)
+                    gstore(reinterpret_cast<uint4*>(near + (size_t)(3 * blockIdx.x + wv) * seg_cap + cnt + mbcnt64(fm)),
+                           make_uint4((uint32_t)t.img, (uint32_t)(t.row + n), nr[0], nr[1]));
+                cnt += (uint32_t)__popcll(fm);
             }
         }
-        // unpack to rows 16 rw + 4 g + i (g: this lane's row group)
-        auto unpack = [&](uint32_t p16) {
-            uint64_t r = 0;
-#pragma unroll
-            for (int rw = 0; rw < 4; ++rw) r |= (uint64_t)((p16 >> (4 * rw)) & 0xFu) << (16 * rw + 4 * g);
-            return r;
-        };
-#pragma unroll
-        for (int b = 0; b < TB; ++b) {
-            uint64_t w[3] = {unpack(pw[b][0] & 0xFFFFu), unpack(pw[b][0] >> 16), unpack(pw[b][1])};
-            uint64_t m[3] = {unpack(pm[b][0] & 0xFFFFu), unpack(pm[b][0] >> 16), unpack(pm[b][1])};
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                w[k] |= __shfl_xor(w[k], 16);
-                w[k] |= __shfl_xor(w[k], 32);
-                m[k] |= __shfl_xor(m[k], 16);
-                m[k] |= __shfl_xor(m[k], 32);
+        if constexpr (FUSED) {
+            __syncthreads();
+            blk.recompute(R, n_tot, counts);
+            if (tid < DESC) {
+                const Tile& t = s_tile[0][tid >> 4];
+                if (n < t.nr) store_code(CodeOut{t.codes, t.keys, 0}, n, blk.bits[tid]);
             }
-            store_code(outs[tc[b].img], tc[b].img, tc[b].r0 + n, g == 0 && live[b], w[0], w[1], w[2], m[0], m[1],
-                       m[2], seg, cnt);
+        } else if (more) {
+            ++slot;
+        } else {
+            __syncthreads();
+            set_tiles(grp + step);
+            __syncthreads();
+            slot = 0;
+            fetch(0);
         }
     }
-    if (lane == 0) seg_count[wave] = cnt;
+    if constexpr (!FUSED)
+        if (third && lane == 0) seg_count[3 * blockIdx.x + wv] = cnt;
+}
+
+// The recompute of the near list: a block takes word `word` of the near
+// lists of kNearSegs projection blocks, a thread an entry and then a flagged
+// projection.  Every lane needs another row of R, so half of the columns of R
+// at a time are in LDS (16 bytes per lane from memory are a cache line per
+// lane: 94.7 us at 800k descriptors and 190k projections), rows two doubles
+// longer than that so that equal columns of different rows lie in all banks.
+// 800k descriptors, 190k projections: 17.5 us (38 for a sort by row, a
+// wavefront per 64 projections of one row, and a pass to store the results).
+__global__ __launch_bounds__(kNearThreads) void near_kernel(const ImgDev* __restrict__ imgs,
+                                                            const CodeOut* __restrict__ outs,
+                                                            const NearEntry* __restrict__ near,
+                                                            const uint32_t* __restrict__ seg_count, uint32_t seg_cap,
+                                                            uint32_t n_lists, const double* __restrict__ R,
+                                                            const unsigned long long* __restrict__ S, double n_tot,
+                                                            unsigned long long* __restrict__ counts) {
+    constexpr int kHalf = kDim / 2, kStride = kHalf + 2;
+    constexpr int kWaves = kNearThreads / 64;
+    __shared__ __attribute__((aligned(16))) double s_R[64 * kStride];  // 64 rows of one word
+    __shared__ double s_S[kDim];
+    __shared__ uint32_t s_pre[kNearThreads], s_wave[kWaves];
+    __shared__ uint32_t s_mask[kNearThreads][2], s_bits[kNearThreads][2];
+    __shared__ const uint8_t* s_xp[kNearThreads];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const uint32_t word = blockIdx.x % 3, l0 = blockIdx.x / 3 * kNearSegs;
+    const int rows = word < 2 ? 64 : kRows - 128;
+    uint32_t n_seg[kNearSegs], n = 0;
+#pragma unroll
+    for (int i = 0; i < kNearSegs; ++i) {
+        n_seg[i] = l0 + i < n_lists ? uniform(seg_count[3 * (l0 + i) + word]) : 0u;
+        n += n_seg[i];
+    }
+    if (n == 0) return;
+    if (tid < kDim) s_S[tid] = (double)S[tid];
+    uint32_t n_jobs = 0;
+    for (uint32_t e0 = 0; e0 < n; e0 += kNearThreads) {
+        uint32_t at = e0 + tid, li = 0;
+        const bool has = at < n;
+#pragma unroll
+        for (int i = 0; i + 1 < kNearSegs; ++i)
+            if (li == (uint32_t)i && at >= n_seg[i]) at -= n_seg[i], ++li;
+        uint4 e = make_uint4(0u, 0u, 0u, 0u);
+        if (has) e = gload(reinterpret_cast<const uint4*>(near + (size_t)(3 * (l0 + li) + word) * seg_cap + at));
+        s_xp[tid] = imgs[e.x].desc + (int64_t)(int32_t)e.y * kDim;
+        s_mask[tid][0] = e.z;
+        s_mask[tid][1] = e.w;
+        s_bits[tid][0] = s_bits[tid][1] = 0u;
+        uint32_t incl = wave_incl_scan((uint32_t)(__popc(e.z) + __popc(e.w)), lane);
+        if (lane == 63) s_wave[wv] = incl;
+        __syncthreads();
+        uint32_t total = 0;
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) {
+            if (i == wv) incl += total;
+            total += s_wave[i];
+        }
+        s_pre[tid] = incl;
+        n_jobs += total;
+        for (uint32_t j0 = 0; j0 < total; j0 += kNearThreads) {
+            __syncthreads();  // s_pre is there; the other half of R is read
+            const uint32_t j = j0 + tid;
+            const bool act = j < total;
+            // owner: the first entry whose prefix exceeds j; its kth set bit
+            uint32_t L = 0;
+#pragma unroll
+            for (uint32_t st = kNearThreads / 2; st >= 1; st >>= 1)
+                if (act && s_pre[L + st - 1] <= j) L += st;
+            uint32_t kth = act ? j - (L ? s_pre[L - 1] : 0u) : 0u;
+            uint32_t m = s_mask[L][0];
+            const uint32_t c0 = (uint32_t)__popc(m);
+            const bool up = kth >= c0;
+            if (up) {
+                kth -= c0;
+                m = s_mask[L][1];
+            }
+            for (uint32_t t = 0; t < kth; ++t) m &= m - 1;
+            const int bit = act ? __ffs(m) - 1 : 0;
+            const uint4* xp = reinterpret_cast<const uint4*>(s_xp[L]);
+            const double* rp = s_R + (act ? (up ? 32 : 0) + bit : 0) * kStride;
+            double p = 0.0;
+            for (int half = 0; half < 2; ++half) {
+                if (half) __syncthreads();
+                for (int i = tid; i < rows * (kHalf / 2); i += kNearThreads) {
+                    const int r = i / (kHalf / 2), c = i % (kHalf / 2);
+                    *reinterpret_cast<double2*>(s_R + r * kStride + 2 * c) =
+                        *reinterpret_cast<const double2*>(R + (size_t)(64 * word + r) * kDim + half * kHalf + 2 * c);
+                }
+                uint4 xv[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) xv[q] = gload(xp + 4 * half + q);
+                __syncthreads();
+                if (act) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const uint32_t xw[4] = {xv[q].x, xv[q].y, xv[q].z, xv[q].w};
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) {
+                            const double c = n_tot * (double)((xw[i >> 2] >> (8 * (i & 3))) & 0xFFu) -
+                                             s_S[half * kHalf + 16 * q + i];
+                            p = fma(rp[16 * q + i], c, p);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+            if (act && p > 0.0) atomicOr(&s_bits[L][up ? 1 : 0], 1u << bit);
+        }
+        __syncthreads();
+        const uint32_t b0 = s_bits[tid][0], b1 = s_bits[tid][1];
+        if (has && (b0 | b1)) {
+            const CodeOut o = outs[e.x];
+            const int64_t row = (int32_t)e.y;
+            if (word < 2) {
+                o.codes[2 * row + word] |= (uint64_t)b0 | ((uint64_t)b1 << 32);
+            } else {
+                uint16_t* kp = reinterpret_cast<uint16_t*>(o.keys + 6 * row);
+                kp[0] |= (uint16_t)b0;
+                kp[1] |= (uint16_t)(b0 >> 16);
+                kp[2] |= (uint16_t)b1;
+            }
+        }
+        __syncthreads();
+    }
+    if (tid == 0) atomicAdd(counts + (blockIdx.x % kCountSlots) * kCountStride, (unsigned long long)n_jobs);
 }
 
 // Plain FP32 form: one thread per descriptor, 176 fp32 FMA chains over the
@@ -263,15 +657,18 @@ __global__ __launch_bounds__(256) void proj_fp32_kernel(const ImgDev* __restrict
                                                         const RowChunk* __restrict__ tiles, int n_tiles,
                                                         const float* __restrict__ R32,
                                                         const float* __restrict__ bias, float margin_coef,
-                                                        NearEntry* __restrict__ near,
-                                                        uint32_t* __restrict__ seg_count,
-                                                        uint32_t* __restrict__ near_ctl) {
-    if (blockIdx.x == 0) near_ctl[threadIdx.x] = 0u;  // the recompute's control words (kNearCtlWords)
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+                                                        const double* __restrict__ R,
+                                                        const unsigned long long* __restrict__ S, double n_tot,
+                                                        unsigned long long* __restrict__ counts) {
+    __shared__ ProjBlock<256> blk;
+    const int tid = threadIdx.x;
+    if (tid < kDim) blk.S[tid] = (double)S[tid];
+    const int t = blockIdx.x * blockDim.x + tid;
     const int tile = min(t >> 4, n_tiles - 1), n = t & 15;
     const RowChunk tc = tiles[tile];
     const bool live = (t >> 4) < n_tiles && n < tc.nr;
-    const uint4* xp = reinterpret_cast<const uint4*>(imgs[tc.img].desc + (int64_t)(tc.r0 + (live ? n : 0)) * kDim);
+    const uint8_t* x = imgs[tc.img].desc + (int64_t)(tc.r0 + (live ? n : 0)) * kDim;
+    const uint4* xp = reinterpret_cast<const uint4*>(x);
     float xf[kDim];
     uint32_t sq = 0;
 #pragma unroll
@@ -285,13 +682,13 @@ __global__ __launch_bounds__(256) void proj_fp32_kernel(const ImgDev* __restrict
             for (int b = 0; b < 4; ++b) xf[c * 16 + a * 4 + b] = (float)((ws[a] >> (8 * b)) & 0xFFu);
         }
     }
-    const float base_margin = margin_coef * sqrtf((float)sq) + 0x1p-26f;
-    uint64_t w[3] = {0, 0, 0}, m[3] = {0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int rows = k < 2 ? 64 : kRows - 128;
+    const float base_margin = live ? margin_coef * sqrtf((float)sq) + 0x1p-26f : -__builtin_inff();
+    blk.x[tid] = x;
+    for (int wd = 0; wd < 6; ++wd) {
+        uint32_t w = 0, m = 0;
+        const int rows = wd < 5 ? 32 : kRows - 160;
         for (int rr = 0; rr < rows; ++rr) {
-            const int r = 64 * k + rr;
+            const int r = 32 * wd + rr;
             const float* rp = R32 + r * kDim;
             float acc = 0.f;
 #pragma unroll
@@ -300,350 +697,15 @@ __global__ __launch_bounds__(256) void proj_fp32_kernel(const ImgDev* __restrict
             const float v = acc - bv;
             const float M = base_margin + 0x1p-20f * fabsf(bv);
             const bool nr = !(fabsf(v) > M);
-            const bool bit = !nr && v > 0.f;
-            w[k] |= (uint64_t)bit << rr;
-            m[k] |= (uint64_t)nr << rr;
+            w |= (uint32_t)(!nr && v > 0.f) << rr;
+            m |= (uint32_t)nr << rr;
         }
-    }
-    // one 64-entry segment per wavefront
-    const int wave = t >> 6;
-    uint32_t cnt = 0;
-    store_code(outs[tc.img], tc.img, tc.r0 + n, live, w[0], w[1], w[2], m[0], m[1], m[2], near + (size_t)wave * 64,
-               cnt);
-    if ((t & 63) == 0) seg_count[wave] = cnt;
-}
-
-// ------------------------------------------------------------------ binary64 recompute
-// Near-margin projections are recomputed with the same fused multiply-add
-// chain over components 0..127 of r_j . (N x - S) that defines the codes
-// (N x_i - S_i is an exact integer in binary64).  A recompute is a job
-// (near-list entry, row j).  The jobs are grouped by row first, so that the
-// wavefront evaluating 64 of them reads one row of R, with wave-uniform
-// (scalar) loads, and only the descriptors differ per lane:
-//   near_sort  : per block of kSortSegs near-list segments, count the jobs
-//                of each row, reserve their places in the row's region of
-//                the job list (one atomic per block and row), place them;
-//                clear the result bits of the entries;
-//   near_eval  : one wavefront per 64 jobs of one row; a positive value ORs
-//                the row's bit into the entry's result bits;
-//   near_apply : the result bits ORed into each entry's code and keys (one
-//                thread per entry, the only writer of that descriptor).
-// A row region holds cap_r jobs.  If some row has more, near_eval takes its
-// spread form instead: the jobs of each segment are spread over the lanes
-// as they come (any row per lane, rows read with vector loads); the results
-// are the same.  Block sizes measured on 800k descriptors (190k jobs):
-// 32 segments per near_sort block (fewer blocks: longer passes; more: more
-// row reservations), 8 per near_apply block (about one entry per thread).
-constexpr int kSortSegs = 32;
-constexpr int kApplySegs = 8;
-
-struct NearJob {
-    uint32_t entry;       // near-list index sg * seg_cap + i
-    uint32_t pad;
-    const uint8_t* x;     // the descriptor
-};
-
-constexpr int kNearOverflow = kRows;  // control word: some row has more jobs than its region
-
-// The near-list entries of a block's SEGS segments from s0 on, flattened:
-// s_pre[j] is the number of entries in segments s0 .. s0 + j - 1.
-template <int SEGS>
-__device__ __forceinline__ uint32_t near_entry_of(const uint32_t* s_pre, uint32_t i, uint32_t s0, uint32_t seg_cap) {
-    uint32_t j = 0;
-#pragma unroll
-    for (uint32_t step = SEGS / 2; step >= 1; step >>= 1)
-        if (s_pre[j + step] <= i) j += step;
-    return (s0 + j) * seg_cap + (i - s_pre[j]);
-}
-
-template <int SEGS>
-__device__ __forceinline__ void near_block_prefix(uint32_t* s_pre, const uint32_t* seg_count, uint32_t s0,
-                                                  uint32_t n_seg) {
-    static_assert(SEGS >= 2 && SEGS <= 64 && (SEGS & (SEGS - 1)) == 0, "SEGS: a power of two up to 64");
-    if (threadIdx.x < 64) {
-        const uint32_t t = threadIdx.x;
-        const uint32_t c = (t < SEGS && s0 + t < n_seg) ? seg_count[s0 + t] : 0u;
-        const uint32_t incl = wave_incl_scan(c, (int)t);
-        if (t < SEGS) s_pre[t + 1] = incl;
-        if (t == 0) s_pre[0] = 0;
-    }
-}
-
-__global__ __launch_bounds__(256) void near_sort_kernel(const ImgDev* __restrict__ imgs,
-                                                        const NearEntry* __restrict__ near,
-                                                        const uint32_t* __restrict__ seg_count, uint32_t seg_cap,
-                                                        uint32_t n_seg, unsigned long long* __restrict__ res,
-                                                        uint32_t* __restrict__ ctl, NearJob* __restrict__ jobs,
-                                                        uint32_t cap_r, unsigned long long* __restrict__ counter) {
-    __shared__ uint32_t s_pre[kSortSegs + 1];
-    __shared__ uint32_t s_hist[kRows];
-    __shared__ uint32_t s_tot[4];
-    const uint32_t s0 = blockIdx.x * kSortSegs;
-    near_block_prefix<kSortSegs>(s_pre, seg_count, s0, n_seg);
-    for (int r = threadIdx.x; r < kRows; r += blockDim.x) s_hist[r] = 0;
-    __syncthreads();
-    const uint32_t n_ent = s_pre[kSortSegs];
-    // pass 1: jobs per row; result bits cleared
-    uint32_t tot = 0;
-    for (uint32_t i = threadIdx.x; i < n_ent; i += blockDim.x) {
-        const uint32_t e = near_entry_of<kSortSegs>(s_pre, i, s0, seg_cap);
-        const NearEntry ne = near[e];
-#pragma unroll
-        for (int w = 0; w < 3; ++w) {
-            res[3 * (size_t)e + w] = 0ull;
-            for (uint64_t m = ne.mask[w]; m; m &= m - 1) {
-                atomicAdd(&s_hist[64 * w + __ffsll((unsigned long long)m) - 1], 1u);
-                ++tot;
-            }
-        }
-    }
-    tot += __shfl_xor(tot, 1);
-    tot += __shfl_xor(tot, 2);
-    tot += __shfl_xor(tot, 4);
-    tot += __shfl_xor(tot, 8);
-    tot += __shfl_xor(tot, 16);
-    tot += __shfl_xor(tot, 32);
-    if ((threadIdx.x & 63) == 0) s_tot[threadIdx.x >> 6] = tot;
-    __syncthreads();
-    // reserve each row's places (s_hist becomes the row's next free place)
-    for (int r = threadIdx.x; r < kRows; r += blockDim.x) {
-        const uint32_t h = s_hist[r];
-        uint32_t b = 0;
-        if (h) {
-            b = atomicAdd(&ctl[r], h);
-            if (b + h > cap_r) ctl[kNearOverflow] = 1u;
-        }
-        s_hist[r] = b;
-    }
-    if (threadIdx.x == 0) {
-        const uint32_t t = s_tot[0] + s_tot[1] + s_tot[2] + s_tot[3];
-        if (t) atomicAdd(counter, (unsigned long long)t);
+        blk.bits[tid][wd] = w;
+        blk.near[tid][wd] = m;
     }
     __syncthreads();
-    // pass 2: place the jobs
-    for (uint32_t i = threadIdx.x; i < n_ent; i += blockDim.x) {
-        const uint32_t e = near_entry_of<kSortSegs>(s_pre, i, s0, seg_cap);
-        const NearEntry ne = near[e];
-        const uint8_t* x = imgs[ne.img].desc + (int64_t)ne.row * kDim;
-#pragma unroll
-        for (int w = 0; w < 3; ++w)
-            for (uint64_t m = ne.mask[w]; m; m &= m - 1) {
-                const int r = 64 * w + __ffsll((unsigned long long)m) - 1;
-                const uint32_t pos = atomicAdd(&s_hist[r], 1u);
-                if (pos < cap_r) jobs[(size_t)r * cap_r + pos] = NearJob{e, 0u, x};
-            }
-    }
-}
-
-// The binary64 chain of one descriptor x (per lane) against row rp: c_i =
-// N x_i - S_i exactly, then p = fma(r_i, c_i, p) for i = 0 .. 127.
-__device__ __forceinline__ double near_chain_q(double p, uint4 xv, const double rv[16], const double* s_S, int q,
-                                               double n_tot) {
-    const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w};
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int bb = 0; bb < 4; ++bb) {
-            const int ci = 16 * q + 4 * a + bb;
-            const double c = n_tot * (double)((xw[a] >> (8 * bb)) & 0xFFu) - s_S[ci];
-            p = fma(rv[4 * a + bb], c, p);
-        }
-    return p;
-}
-
-// Row rp the same for the whole wavefront (scalar loads).  The descriptor is
-// loaded whole; the scheduling barriers keep the conversions of each group
-// of 16 components next to their multiply-adds (hoisting all 128 would need
-// 256 registers).
-__device__ __forceinline__ double near_chain_uniform(const uint8_t* x, const double* __restrict__ rp,
-                                                     const double* s_S, double n_tot) {
-    const uint4* xp = reinterpret_cast<const uint4*>(x);
-    uint4 xv[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) xv[q] = gload(xp + q);
-    double p = 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        double rv[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) rv[i] = rp[16 * q + i];
-        p = near_chain_q(p, xv[q], rv, s_S, q, n_tot);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    return p;
-}
-
-// Row rp per lane (vector loads, 16 components at a time).
-__device__ __forceinline__ double near_chain_lane(const uint8_t* x, const double* rp, const double* s_S,
-                                                  double n_tot) {
-    const uint4* xp = reinterpret_cast<const uint4*>(x);
-    const double2* rr = reinterpret_cast<const double2*>(rp);
-    double p = 0.0;
-#pragma unroll 1
-    for (int q = 0; q < 8; ++q) {
-        double rv[16];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const double2 v = rr[8 * q + i];
-            rv[2 * i] = v.x;
-            rv[2 * i + 1] = v.y;
-        }
-        p = near_chain_q(p, gload(xp + q), rv, s_S, q, n_tot);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    return p;
-}
-
-// The spread form of the recompute, used when some row has more jobs than
-// its region holds: per segment, the (entry, row) jobs of up to 64 entries
-// are spread over the lanes 64 at a time, whichever entry they belong to.
-__device__ __forceinline__ void near_eval_spread(const ImgDev* __restrict__ imgs, const NearEntry* __restrict__ near,
-                                                 const uint32_t* __restrict__ seg_count, uint32_t seg_cap,
-                                                 uint32_t n_seg, const double* __restrict__ R, const double* s_S,
-                                                 double n_tot, unsigned long long* __restrict__ res, uint32_t* s_fb,
-                                                 int lane, uint32_t wave, uint32_t n_waves) {
-    for (uint32_t sg = wave; sg < n_seg; sg += n_waves) {
-        const uint32_t ns = uniform(seg_count[sg]);
-        for (uint32_t base = 0; base < ns; base += 64) {
-            const uint32_t i = base + (uint32_t)lane;
-            const bool has = i < ns;
-            NearEntry e{};
-            if (has) e = near[(size_t)sg * seg_cap + i];
-            const uint32_t pc = has ? (uint32_t)(__popcll(e.mask[0]) + __popcll(e.mask[1]) + __popcll(e.mask[2])) : 0u;
-            const uint32_t incl = wave_incl_scan(pc, lane);
-            const uint32_t total = uniform(__shfl(incl, 63));
-            s_fb[lane] = incl;
-            wave_sync();
-            for (uint32_t j0 = 0; j0 < total; j0 += 64) {
-                const uint32_t j = j0 + (uint32_t)lane;
-                const bool act = j < total;
-                // owner: the first entry whose inclusive prefix exceeds j
-                uint32_t L = 0;
-#pragma unroll
-                for (uint32_t step = 32; step >= 1; step >>= 1)
-                    if (s_fb[L + step - 1] <= j) L += step;
-                L = act ? L : 0u;
-                const uint32_t start = L ? s_fb[L - 1] : 0u;
-                uint32_t kth = act ? j - start : 0u;
-                const uint64_t m0 = __shfl(e.mask[0], (int)L), m1 = __shfl(e.mask[1], (int)L),
-                               m2 = __shfl(e.mask[2], (int)L);
-                const int img = __shfl(e.img, (int)L), row = __shfl(e.row, (int)L);
-                // the kth set bit of the owner's 176-bit mask
-                int word = 0;
-                uint64_t w = m0;
-                const uint32_t c0 = (uint32_t)__popcll(m0), c1 = (uint32_t)__popcll(m1);
-                if (kth >= c0) {
-                    kth -= c0;
-                    word = 1;
-                    w = m1;
-                    if (kth >= c1) {
-                        kth -= c1;
-                        word = 2;
-                        w = m2;
-                    }
-                }
-                for (uint32_t t = 0; t < kth; ++t) w &= w - 1;
-                const int bitpos = w ? __ffsll((unsigned long long)w) - 1 : 0;
-                if (act) {
-                    const int r = 64 * word + bitpos;
-                    const double p =
-                        near_chain_lane(imgs[img].desc + (int64_t)row * kDim, R + (size_t)r * kDim, s_S, n_tot);
-                    if (p > 0.0)
-                        atomicOr(&res[3 * ((size_t)sg * seg_cap + base + L) + word], 1ull << bitpos);
-                }
-            }
-            wave_sync();  // s_fb is rewritten by the next batch
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void near_eval_kernel(const NearJob* __restrict__ jobs, uint32_t cap_r,
-                                                        const uint32_t* __restrict__ ctl,
-                                                        const double* __restrict__ R,
-                                                        const unsigned long long* __restrict__ S, double n_tot,
-                                                        unsigned long long* __restrict__ res,
-                                                        const ImgDev* __restrict__ imgs,
-                                                        const NearEntry* __restrict__ near,
-                                                        const uint32_t* __restrict__ seg_count, uint32_t seg_cap,
-                                                        uint32_t n_seg) {
-    __shared__ double s_S[kDim];
-    __shared__ uint32_t s_pre[kRows + 1];  // first 64-job chunk of each row
-    __shared__ uint32_t s_n[kRows];        // jobs of each row
-    __shared__ uint32_t s_fb[4][64];       // spread form: per wave, inclusive prefix of jobs per entry
-    for (int i = threadIdx.x; i < kDim; i += blockDim.x) s_S[i] = (double)S[i];
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    const uint32_t n_waves = (gridDim.x * blockDim.x) >> 6;
-    const uint32_t wave = uniform((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-    const bool overflow = uniform(ctl[kNearOverflow]) != 0u;
-    if (!overflow && threadIdx.x < 64) {
-        // lane l: rows 3l .. 3l + 2
-        uint32_t c[3], sum = 0;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int r = 3 * lane + a;
-            const uint32_t n = r < kRows ? min(ctl[r], cap_r) : 0u;
-            if (r < kRows) s_n[r] = n;
-            c[a] = (n + 63) >> 6;
-            sum += c[a];
-        }
-        const uint32_t incl = wave_incl_scan(sum, lane);
-        uint32_t run = incl - sum;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int r = 3 * lane + a;
-            if (r < kRows) s_pre[r] = run;
-            run += c[a];
-        }
-        if (lane == 63) s_pre[kRows] = incl;
-    }
-    __syncthreads();
-    if (overflow) {
-        near_eval_spread(imgs, near, seg_count, seg_cap, n_seg, R, s_S, n_tot, res, s_fb[wv], lane, wave, n_waves);
-        return;
-    }
-    const uint32_t n_chunks = uniform(s_pre[kRows]);
-    for (uint32_t ch = wave; ch < n_chunks; ch += n_waves) {
-        // the row: the last one whose first chunk is <= ch
-        uint32_t r = 0;
-#pragma unroll
-        for (uint32_t step = 128; step >= 1; step >>= 1)
-            if (r + step < kRows && s_pre[r + step] <= ch) r += step;
-        r = uniform(r);
-        const uint32_t j = 64 * (ch - s_pre[r]) + (uint32_t)lane;
-        if (j < s_n[r]) {
-            const NearJob jb = jobs[(size_t)r * cap_r + j];
-            const double p = near_chain_uniform(jb.x, R + (size_t)r * kDim, s_S, n_tot);
-            if (p > 0.0) atomicOr(&res[3 * (size_t)jb.entry + (r >> 6)], 1ull << (r & 63));
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void near_apply_kernel(const CodeOut* __restrict__ outs,
-                                                         const NearEntry* __restrict__ near,
-                                                         const uint32_t* __restrict__ seg_count, uint32_t seg_cap,
-                                                         uint32_t n_seg, const unsigned long long* __restrict__ res) {
-    __shared__ uint32_t s_pre[kApplySegs + 1];
-    const uint32_t s0 = blockIdx.x * kApplySegs;
-    near_block_prefix<kApplySegs>(s_pre, seg_count, s0, n_seg);
-    __syncthreads();
-    const uint32_t n_ent = s_pre[kApplySegs];
-    for (uint32_t i = threadIdx.x; i < n_ent; i += blockDim.x) {
-        const uint32_t e = near_entry_of<kApplySegs>(s_pre, i, s0, seg_cap);
-        const uint64_t b0 = res[3 * (size_t)e], b1 = res[3 * (size_t)e + 1], b2 = res[3 * (size_t)e + 2];
-        if (!(b0 | b1 | b2)) continue;
-        const NearEntry ne = near[e];
-        const CodeOut o = outs[ne.img];
-        const int64_t row = ne.row;
-        if (b0 | b1) {
-            o.codes[2 * row] |= b0;
-            o.codes[2 * row + 1] |= b1;
-        }
-        if (b2) {
-            uint8_t* kb = o.keys + 6 * row;
-            for (int tb = 0; tb < kTables; ++tb) kb[tb] = (uint8_t)(kb[tb] | ((b2 >> (8 * tb)) & 0xFFu));
-        }
-    }
+    blk.recompute(R, n_tot, counts);
+    if (live) store_code(outs[tc.img], tc.r0 + n, blk.bits[tid]);
 }
 
 // ------------------------------------------------------------------ bucket tables
@@ -770,62 +832,50 @@ hipError_t launch_make_items(hipStream_t s, const PairTiles* pt, int32_t n_pt, c
 hipError_t launch_colsum(hipStream_t s, const ImgDev* imgs, const RowChunk* chunks, int n_chunks,
                          unsigned long long* S) {
     if (n_chunks <= 0) return hipSuccess;
-    CH_LAUNCH(colsum_kernel, dim3(n_chunks), dim3(256), 0, s, imgs, chunks, S);
+    CH_LAUNCH(colsum_kernel<false>, dim3(n_chunks), dim3(256), 0, s, imgs, chunks, S, (const double*)nullptr, 0.0,
+              (float*)nullptr, (unsigned long long*)nullptr, (unsigned long long*)nullptr);
     return hipSuccess;
 }
 
-hipError_t launch_bias(hipStream_t s, const double* R, const unsigned long long* S, double n_tot, float* bias) {
-    CH_LAUNCH(bias_kernel, dim3(1), dim3(192), 0, s, R, S, n_tot, bias);
+hipError_t launch_colsum_bias(hipStream_t s, const ImgDev* imgs, const RowChunk* chunks, int n_chunks,
+                              unsigned long long* S, const double* Rt, double n_tot, float* bias,
+                              unsigned long long* next_S, unsigned long long* counts) {
+    if (n_chunks <= 0) return hipSuccess;
+    CH_LAUNCH(colsum_kernel<true>, dim3(n_chunks), dim3(256), 0, s, imgs, chunks, S, Rt, n_tot, bias, next_S, counts);
     return hipSuccess;
 }
 
-hipError_t launch_proj_mfma(hipStream_t s, int grid, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles,
-                            int n_tiles, const uint4* frag, const float* bias, float margin, NearEntry* near,
-                            uint32_t* seg_count, uint32_t seg_cap, void* near_work) {
+hipError_t launch_bias(hipStream_t s, const double* Rt, const unsigned long long* S, double n_tot, float* bias) {
+    CH_LAUNCH(bias_kernel, dim3(1), dim3(256), 0, s, Rt, S, n_tot, bias);
+    return hipSuccess;
+}
+
+hipError_t launch_proj_mfma(hipStream_t s, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles, int n_tiles,
+                            const uint4* frag, const float* bias, float margin, const double* R,
+                            const unsigned long long* S, double n_tot, unsigned long long* counts, const ProjPlan& pl,
+                            void* near) {
     if (n_tiles <= 0) return hipSuccess;
-    CH_LAUNCH(proj_mfma_kernel, dim3(grid), dim3(256), 0, s, imgs, outs, tiles, n_tiles, frag, bias, margin, near,
-              seg_count, seg_cap, static_cast<uint32_t*>(near_work));
+    if (pl.fused) {
+        CH_LAUNCH(proj_mfma_kernel<true>, dim3((unsigned)pl.grid), dim3(256), 0, s, imgs, outs, tiles, n_tiles, pl.tpg,
+                  pl.groups, frag, bias, margin, R, S, n_tot, counts, (NearEntry*)nullptr, (uint32_t*)nullptr, 0u);
+        return hipSuccess;
+    }
+    uint32_t* seg_count = static_cast<uint32_t*>(near);
+    NearEntry* list = reinterpret_cast<NearEntry*>(static_cast<uint8_t*>(near) + pl.count_bytes());
+    CH_LAUNCH(proj_mfma_kernel<false>, dim3((unsigned)pl.grid), dim3(256), 0, s, imgs, outs, tiles, n_tiles, pl.tpg,
+              pl.groups, frag, bias, margin, R, S, n_tot, counts, list, seg_count, pl.seg_cap());
+    CH_LAUNCH(near_kernel, dim3((unsigned)((pl.grid + kNearSegs - 1) / kNearSegs * 3)), dim3(kNearThreads), 0, s, imgs,
+              outs, (const NearEntry*)list, (const uint32_t*)seg_count, pl.seg_cap(), (uint32_t)pl.grid, R, S, n_tot,
+              counts);
     return hipSuccess;
 }
 
-hipError_t launch_proj_fp32(hipStream_t s, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles,
-                            int n_tiles, const float* R32, const float* bias, float margin, NearEntry* near,
-                            uint32_t* seg_count, void* near_work) {
+hipError_t launch_proj_fp32(hipStream_t s, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles, int n_tiles,
+                            const float* R32, const float* bias, float margin, const double* R,
+                            const unsigned long long* S, double n_tot, unsigned long long* counts) {
     if (n_tiles <= 0) return hipSuccess;
-    const int64_t threads = (int64_t)n_tiles * 16;
-    CH_LAUNCH(proj_fp32_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, imgs, outs, tiles, n_tiles,
-              R32, bias, margin, near, seg_count, static_cast<uint32_t*>(near_work));
-    return hipSuccess;
-}
-
-uint32_t near_row_cap(uint64_t n_cap) {
-    const uint64_t c = std::max<uint64_t>(64, (n_cap + kRows - 1) / kRows);
-    return (uint32_t)((c + 63) & ~uint64_t(63));
-}
-
-// Work area: control words, result bits (3 words per near-list place), jobs.
-size_t near_work_bytes(uint64_t n_cap) {
-    const size_t res = ((size_t)n_cap * 24 + 255) & ~size_t(255);
-    return (size_t)kNearCtlWords * 4 + res + (size_t)kRows * near_row_cap(n_cap) * sizeof(NearJob);
-}
-
-hipError_t launch_near_recompute(hipStream_t s, int eval_grid, const ImgDev* imgs, const CodeOut* outs, const NearEntry* near,
-                        const uint32_t* seg_count, uint32_t seg_cap, uint32_t n_seg, const double* R,
-                        const unsigned long long* S, double n_tot, void* work, unsigned long long* counter) {
-    if (n_seg == 0) return hipSuccess;
-    const uint64_t n_cap = (uint64_t)n_seg * seg_cap;
-    const uint32_t cap_r = near_row_cap(n_cap);
-    uint32_t* ctl = static_cast<uint32_t*>(work);
-    unsigned long long* res = reinterpret_cast<unsigned long long*>(ctl + kNearCtlWords);
-    NearJob* jobs = reinterpret_cast<NearJob*>(reinterpret_cast<uint8_t*>(res) +
-                                               (((size_t)n_cap * 24 + 255) & ~size_t(255)));
-    const unsigned blocks = (n_seg + kSortSegs - 1) / kSortSegs;
-    const unsigned ablocks = (n_seg + kApplySegs - 1) / kApplySegs;
-    CH_LAUNCH(near_sort_kernel, dim3(blocks), dim3(256), 0, s, imgs, near, seg_count, seg_cap, n_seg, res, ctl, jobs,
-              cap_r, counter);
-    CH_LAUNCH(near_eval_kernel, dim3(eval_grid), dim3(256), 0, s, jobs, cap_r, ctl, R, S, n_tot, res, imgs, near,
-              seg_count, seg_cap, n_seg);
-    CH_LAUNCH(near_apply_kernel, dim3(ablocks), dim3(256), 0, s, outs, near, seg_count, seg_cap, n_seg, res);
+    CH_LAUNCH(proj_fp32_kernel, dim3((unsigned)((n_tiles + 15) / 16)), dim3(256), 0, s, imgs, outs, tiles, n_tiles, R32,
+              bias, margin, R, S, n_tot, counts);
     return hipSuccess;
 }
 

@@ -10,26 +10,23 @@ hipError_t launch_make_items(hipStream_t s, const PairTiles* pt, int32_t n_pt, c
                              const ImgDev* imgs, int32_t qt, Item* items, int32_t n_items, uint32_t* ctl);
 hipError_t launch_colsum(hipStream_t s, const ImgDev* imgs, const RowChunk* chunks, int n_chunks,
                          unsigned long long* S);
-hipError_t launch_bias(hipStream_t s, const double* R, const unsigned long long* S, double n_tot, float* bias);
-// Projection: wavefront w appends its near-margin descriptors to
-// near[w * seg_cap ..] and writes their number to seg_count[w] (the fp32 form
-// has one 64-entry segment per wavefront of its grid).  near_work: the work
-// area of the recompute that follows (the projection clears its control
-// words).
-hipError_t launch_proj_mfma(hipStream_t s, int grid, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles,
-                            int n_tiles, const uint4* frag, const float* bias, float margin, NearEntry* near,
-                            uint32_t* seg_count, uint32_t seg_cap, void* near_work);
-hipError_t launch_proj_fp32(hipStream_t s, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles,
-                            int n_tiles, const float* R32, const float* bias, float margin, NearEntry* near,
-                            uint32_t* seg_count, void* near_work);
-// Binary64 recompute of the near list's flagged projections (three launches).
-// work: near_work_bytes(n_seg * seg_cap) bytes of device scratch, the one
-// given to the projection launch just before.
-uint32_t near_row_cap(uint64_t n_cap);
-size_t near_work_bytes(uint64_t n_cap);
-hipError_t launch_near_recompute(hipStream_t s, int eval_grid, const ImgDev* imgs, const CodeOut* outs, const NearEntry* near,
-                        const uint32_t* seg_count, uint32_t seg_cap, uint32_t n_seg, const double* R,
-                        const unsigned long long* S, double n_tot, void* work, unsigned long long* counter);
+// Column sums of a whole set in one launch, with what follows from them: the
+// bias.  S: kSumWords words, the first kSumClear zero, the totals from
+// kSumTotal on afterwards; next_S (cleared the same way for the next call) and
+// the recompute counts are cleared.
+hipError_t launch_colsum_bias(hipStream_t s, const ImgDev* imgs, const RowChunk* chunks, int n_chunks,
+                              unsigned long long* S, const double* Rt, double n_tot, float* bias,
+                              unsigned long long* next_S, unsigned long long* counts);
+hipError_t launch_bias(hipStream_t s, const double* Rt, const unsigned long long* S, double n_tot, float* bias);
+// Projection with the binary64 recompute of what falls inside the margin; the
+// number of recomputes is added to counts.  near: pl.near_bytes() bytes.
+hipError_t launch_proj_mfma(hipStream_t s, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles, int n_tiles,
+                            const uint4* frag, const float* bias, float margin, const double* R,
+                            const unsigned long long* S, double n_tot, unsigned long long* counts, const ProjPlan& pl,
+                            void* near);
+hipError_t launch_proj_fp32(hipStream_t s, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles, int n_tiles,
+                            const float* R32, const float* bias, float margin, const double* R,
+                            const unsigned long long* S, double n_tot, unsigned long long* counts);
 hipError_t launch_bucket(hipStream_t s, bool epi, const ImgDev* imgs, const TableOut* touts,
                          const int32_t* train_list, int n_train);
 hipError_t launch_match(hipStream_t s, bool epi, int ns, int grid, const ImgDev* imgs, const PairDev* pairs,

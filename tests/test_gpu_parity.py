@@ -163,6 +163,29 @@ def test_codes_one_context_changing_sizes(mats):
         _assert_codes(codes, keys, oc, ok, f"set {i}")
 
 
+@pytest.mark.parametrize("sizes,copies", [((17, 1, 31), 1), ((17, 1, 31), 64), ((17, 1, 31), 128), ((17, 1, 31), 256),
+                                          ((17, 1, 31), 512), ((1025,), 512)])
+def test_codes_projection_groups(mats, sizes, copies):
+    """Images repeated a power of two times: N x - S scales exactly, so every
+    copy has the codes of the one set, and as many projections inside the
+    margin, whichever way its tiles of 16 descriptors are grouped: one to four
+    tiles a block with the recompute in it, and, from more than four tiles for
+    each of two blocks per compute unit on, blocks taking several groups with
+    a near list (512 x 1025: more than the 16 groups whose places a block
+    works out at once)."""
+    _say(f"codes, {copies} copies of {sizes}")
+    rng = np.random.default_rng(31)
+    ims = [synth.desc(rng, n) for n in sizes]
+    oc, ok = oracle.build_codes(ims, *mats)
+    m = binding.Matcher(*mats, margin_coef=1e-2)
+    _, codes, keys, one = _gpu_codes(m, ims)
+    _assert_codes(codes, keys, oc, ok, "one set")
+    for again in range(2):
+        _, codes, keys, st = _gpu_codes(m, ims * copies)
+        _assert_codes(codes, keys, list(oc) * copies, list(ok) * copies, f"{copies} copies, call {again}")
+        assert st["near_margin_recomputes"] == copies * one["near_margin_recomputes"] > 0
+
+
 # ------------------------------------------------------------------ matching
 
 def _oracle_all(images, oc, ok, pairs, **kw):
