@@ -858,19 +858,21 @@ static int slots_for(const MatchJob& J, int64_t p) {
 
 // Generate the work items of shape qt on the device (into P.items, which
 // holds P.items_cap of them).
-static int make_items(cashash_ctx* c, const MatchPlan& P, int qt, const PairTiles* dPT, int32_t n_pt,
-                      int64_t n_items) {
+static int item_args(const MatchPlan& P, int qt, const PairTiles* dPT, int32_t n_pt, int64_t n_items, ItemArgs* a) {
     if (n_items > (int64_t)INT32_MAX) return fail(CASHASH_E_LIMIT, "too many query tiles in one call");
     if (n_items > P.items_cap) return fail(CASHASH_E_INVAL, "work item buffer too small");
-    HIPCHK(launch_make_items(c->stream, dPT, n_pt, P.dP, P.dI, qt, P.items, (int32_t)n_items, P.ctl));
+    *a = ItemArgs{dPT, P.dP, P.items, P.ctl, n_pt, qt, (int32_t)n_items, 0};
     return CASHASH_OK;
 }
+
+// Queries up to which a call's matcher is launched directly, not replayed.
+constexpr int64_t kDirectQueries = 8192;
 
 // The matcher over items [0, n_items) (batched: one persistent launch) or,
 // in the plain form, one launch per pair over its own items.
 static int enqueue_matcher(cashash_ctx* c, const MatchPlan& P, MatchJob& J, Shape sh, bool batched,
                            const std::vector<int64_t>& first_of, int64_t n_pairs_run, int64_t n_items,
-                           int64_t* launches, bool use_graph) {
+                           int64_t n_queries, int64_t* launches, bool use_graph) {
     uint32_t* ctl = P.ctl;
     const Item* items = P.items;
     if (batched) {
@@ -914,7 +916,10 @@ static int enqueue_matcher(cashash_ctx* c, const MatchPlan& P, MatchJob& J, Shap
             return hipSuccess;
         };
         c->last_replayed = false;
-        if (use_graph && c->use_graphs && !ls.empty()) {
+        // A replay costs about 12 us more than the one launch of a small call
+        // (2 x 2000 descriptors: 67.3 us per call, direct 55.3).  Events taken by
+        // the launch itself instead of recorded around it: 67.9.
+        if (use_graph && c->use_graphs && n_queries > kDirectQueries && !ls.empty()) {
             // the persistent launches as one captured graph, replayed while
             // the launch arguments are unchanged
             std::string key;
@@ -1049,7 +1054,13 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
     std::vector<PairTiles> pt;
     std::vector<int64_t> first;
     int64_t max_items = 1;
-    Uploader up2;  // pairs, then the tile table
+    // All tables go in one upload, and the work items are made beside the bucket
+    // tables: two launches per call.  (Planning the pairs behind the launch of the
+    // bucket tables, with an upload and a launch more, measured 57.7 us per call
+    // against 55.9 for one pair of 2000, 187.4 against 181.7 for 120 and 526.6
+    // against 526.1 for 1035.)
+    Uploader up;  // image views, table outputs, train list, pairs, tile table
+    std::vector<PairDev> pd;
     auto plan = [&]() {
         double sum_nt = 0, sum_nq = 0;
         for (int64_t p = 0; p < n_pairs; ++p) {
@@ -1081,22 +1092,15 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
         pt = pair_tiles(J, P.order, shape.qt, &first);
         max_items = std::max<int64_t>(1, first[n_pairs]);
         P.items_cap = max_items;
-        std::vector<PairDev> pd(n_pairs);
+        pd.resize(n_pairs);
         for (int64_t p = 0; p < n_pairs; ++p) {
             pd[p].qi = J.pair_q[p];
             pd[p].ti = J.pair_t[p];
             pd[p].out = J.pair_out[p];
             for (int i = 0; i < 9; ++i) pd[p].F[i] = J.epi ? J.F[9 * p + i] : 0.0;
         }
-        up2.add(pd);
-        up2.add(pt);
     };
-    auto upload = [&](Uploader& up, std::vector<const void*>& d) {
-        return sa ? upload_scratch(c, *sa, up, d) : upload_meta(c, up, d, kMetaMatch);
-    };
-    // the bucket tables (device work): placed, their image and table views
-    // uploaded, the bucket kernel launched
-    std::vector<const void*> d;
+    // the bucket tables placed, and their image and table views
     auto tables = [&]() -> int {
         uint8_t* tbase = nullptr;
         if (sa) {
@@ -1111,28 +1115,24 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
             J.imgs[m].off = touts[m].off;
             J.imgs[m].ent = touts[m].ent;
         }
-        Uploader up1;  // image views, table outputs, train list
-        up1.add(J.imgs);
-        up1.add(touts);
-        up1.add(train_list);
-        RETCHK(upload(up1, d));
-        P.dI = (const ImgDev*)d[0];
-        HIPCHK(launch_bucket(c->stream, J.epi, P.dI, (const TableOut*)d[1], (const int32_t*)d[2],
-                             (int)train_list.size()));
+        up.add(J.imgs);
+        up.add(touts);
+        up.add(train_list);
         return CASHASH_OK;
     };
+    plan();
     if (sa) {
         // the whole call must fit the scratch before any device work starts
-        plan();
         const size_t up1_bytes = ((((size_t)n_img * sizeof(ImgDev) + 255) & ~size_t(255)) +
                                   (((size_t)n_img * sizeof(TableOut) + 255) & ~size_t(255)) +
                                   train_list.size() * sizeof(int32_t));
+        const size_t up2_bytes = ((pd.size() * sizeof(PairDev) + 255) & ~size_t(255)) + pt.size() * sizeof(PairTiles);
         ScratchArea probe;
         probe.base = sa->base;
         probe.cap = sa->cap;
         probe.used = sa->used;
         const size_t pieces[] = {std::max<size_t>(tbytes, 1), std::max<size_t>(up1_bytes, 1),
-                                 std::max<size_t>(up2.host.size(), 1), (size_t)max_items * sizeof(Item),
+                                 std::max<size_t>(up2_bytes, 1), (size_t)max_items * sizeof(Item),
                                  (size_t)kCtlWords * 4, 64};
         size_t need = 0;
         for (size_t n : pieces) need = ((need + 255) & ~size_t(255)) + n;
@@ -1140,14 +1140,21 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
             if (!probe.take(n))
                 return fail(CASHASH_E_LIMIT, "the call needs %zu bytes of scratch, more than its %zu bytes", need,
                             sa->cap);
-        RETCHK(tables());
-    } else {
-        // the bucket tables are built while the host plans the pairs
-        RETCHK(tables());
-        plan();
     }
-    RETCHK(upload(up2, d));
-    P.dP = (const PairDev*)d[0];
+    RETCHK(tables());
+    up.add(pd);
+    up.add(pt);
+    std::vector<const void*> d;
+    if (sa) {
+        RETCHK(upload_scratch(c, *sa, up, d));
+    } else {
+        // always the same one of the two areas, so that the tables' addresses
+        // stay from call to call
+        c->meta_turn[kMetaMatch] = 0;
+        RETCHK(upload_meta(c, up, d, kMetaMatch));
+    }
+    P.dI = (const ImgDev*)d[0];
+    P.dP = (const PairDev*)d[3];
     P.prm.k = c->cfg.k;
     P.prm.tau = c->cfg.max_hamming;
     P.prm.num2 = (int64_t)c->cfg.ratio_num * c->cfg.ratio_num;
@@ -1165,11 +1172,17 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
     }
 
     const int64_t n_items = first[n_pairs];
-    RETCHK(make_items(c, P, shape.qt, (const PairTiles*)d[1], (int32_t)pt.size(), n_items));
+    ItemArgs ia;
+    RETCHK(item_args(P, shape.qt, (const PairTiles*)d[4], (int32_t)pt.size(), n_items, &ia));
+    HIPCHK(launch_bucket(c->stream, J.epi, P.dI, (const TableOut*)d[1], (const int32_t*)d[2], (int)train_list.size(),
+                         ia));
     J.turn = c->job_turn;
     c->job_turn ^= 1;
+    int64_t n_queries = 0;
+    for (int64_t p = 0; p < n_pairs; ++p) n_queries += J.imgs[J.pair_q[p]].n;
     HIPCHK(hipEventRecord(c->job_ev[J.turn][0], c->stream));
-    RETCHK(enqueue_matcher(c, P, J, shape, batched, first, n_pairs, n_items, &c->last_launches, sa == nullptr));
+    RETCHK(enqueue_matcher(c, P, J, shape, batched, first, n_pairs, n_items, n_queries, &c->last_launches,
+                           sa == nullptr));
     HIPCHK(hipEventRecord(c->job_ev[J.turn][1], c->stream));
     c->last_shape_qt = shape.qt;
     c->last_shape_bpc = shape.bpc;

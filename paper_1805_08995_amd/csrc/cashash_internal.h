@@ -154,6 +154,15 @@ inline __host__ __device__ unsigned long long* stat_slot(uint32_t* ctl, int i) {
     return reinterpret_cast<unsigned long long*>(ctl + (i % kSegments) * kCtlStride + 16 * (1 + i / kSegments));
 }
 
+// What the work items of a match call are made of.
+struct ItemArgs {
+    const PairTiles* pt;
+    const PairDev* pairs;
+    Item* items;
+    uint32_t* ctl;
+    int32_t n_pt, qt, n_items, pad;
+};
+
 struct MatchParams {
     int32_t k;
     int32_t tau;

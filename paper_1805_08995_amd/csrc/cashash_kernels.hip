@@ -30,21 +30,18 @@ __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
 // whose first tile is <= i (binary search); its queries are tile (i - first)
 // of that pair's query image, qt per tile.  Also clears the matcher's control
 // words.
-__global__ void make_items_kernel(const PairTiles* __restrict__ pt, int32_t n_pt, const PairDev* __restrict__ pairs,
-                                  const ImgDev* __restrict__ imgs, int32_t qt, Item* __restrict__ items,
-                                  int32_t n_items, uint32_t* __restrict__ ctl) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kCtlWords) ctl[i] = 0u;
-    if (i >= n_items) return;
-    int32_t lo = 0, hi = n_pt - 1;
+__device__ __forceinline__ void make_item(const ItemArgs& a, const ImgDev* __restrict__ imgs, int32_t i) {
+    if (i < kCtlWords) a.ctl[i] = 0u;
+    if (i >= a.n_items) return;
+    int32_t lo = 0, hi = a.n_pt - 1;
     while (lo < hi) {
         const int32_t mid = (lo + hi + 1) >> 1;
-        if (pt[mid].first <= i) lo = mid; else hi = mid - 1;
+        if (a.pt[mid].first <= i) lo = mid; else hi = mid - 1;
     }
-    const int32_t p = pt[lo].pair;
-    const int32_t q0 = (i - pt[lo].first) * qt;
-    const int32_t nq = imgs[pairs[p].qi].n;
-    items[i] = Item{p, q0, min(qt, nq - q0), 0};
+    const int32_t p = a.pt[lo].pair;
+    const int32_t q0 = (i - a.pt[lo].first) * a.qt;
+    const int32_t nq = imgs[a.pairs[p].qi].n;
+    a.items[i] = Item{p, q0, min(a.qt, nq - q0), 0};
 }
 
 // ------------------------------------------------------------------ column sums
@@ -730,7 +727,13 @@ __device__ __forceinline__ uint64_t entry_word(int t, uint32_t k03, uint32_t k45
 template <bool EPI>
 __global__ __launch_bounds__(64 * kBucketWaves) void bucket_kernel(const ImgDev* __restrict__ imgs,
                                                                    const TableOut* __restrict__ touts,
-                                                                   const int32_t* __restrict__ train_list) {
+                                                                   const int32_t* __restrict__ train_list,
+                                                                   int32_t n_train, ItemArgs ia) {
+    // blocks after the tables' make the work items
+    if ((int)blockIdx.x >= n_train * kTables) {
+        make_item(ia, imgs, ((int32_t)blockIdx.x - n_train * kTables) * (64 * kBucketWaves) + (int32_t)threadIdx.x);
+        return;
+    }
     __shared__ uint32_t cnt[kBucketWaves][256];  // per-wave counts, then per-wave write positions
     __shared__ uint32_t wsum[4];
     const int lane = threadIdx.x & 63;
@@ -821,14 +824,6 @@ hipError_t launch_fill_u32(hipStream_t s, uint32_t* p, int64_t n, uint32_t v) {
     return hipSuccess;
 }
 
-hipError_t launch_make_items(hipStream_t s, const PairTiles* pt, int32_t n_pt, const PairDev* pairs,
-                             const ImgDev* imgs, int32_t qt, Item* items, int32_t n_items, uint32_t* ctl) {
-    const unsigned threads = (unsigned)std::max(n_items, kCtlWords);
-    CH_LAUNCH(make_items_kernel, dim3((threads + 255) / 256), dim3(256), 0, s, pt, n_pt, pairs, imgs, qt, items, n_items,
-              ctl);
-    return hipSuccess;
-}
-
 hipError_t launch_colsum(hipStream_t s, const ImgDev* imgs, const RowChunk* chunks, int n_chunks,
                          unsigned long long* S) {
     if (n_chunks <= 0) return hipSuccess;
@@ -880,13 +875,13 @@ hipError_t launch_proj_fp32(hipStream_t s, const ImgDev* imgs, const CodeOut* ou
 }
 
 hipError_t launch_bucket(hipStream_t s, bool epi, const ImgDev* imgs, const TableOut* touts, const int32_t* train_list,
-                         int n_train) {
-    if (n_train <= 0) return hipSuccess;
+                         int n_train, const ItemArgs& ia) {
+    const unsigned per = 64 * kBucketWaves;
+    const unsigned grid = (unsigned)n_train * kTables + ((unsigned)std::max(ia.n_items, kCtlWords) + per - 1) / per;
     if (epi)
-        CH_LAUNCH(bucket_kernel<true>, dim3(n_train * kTables), dim3(64 * kBucketWaves), 0, s, imgs, touts, train_list);
+        CH_LAUNCH(bucket_kernel<true>, dim3(grid), dim3(per), 0, s, imgs, touts, train_list, n_train, ia);
     else
-        CH_LAUNCH(bucket_kernel<false>, dim3(n_train * kTables), dim3(64 * kBucketWaves), 0, s, imgs, touts,
-                  train_list);
+        CH_LAUNCH(bucket_kernel<false>, dim3(grid), dim3(per), 0, s, imgs, touts, train_list, n_train, ia);
     return hipSuccess;
 }
 

@@ -511,6 +511,31 @@ def test_graph_replays_match_eager(mats, monkeypatch):
     assert replays >= 3
 
 
+@pytest.mark.parametrize("n_query", [1, 8192, 8193])
+def test_direct_and_replayed_launches(mats, n_query):
+    """Calls of up to 8192 queries launch the matcher directly, larger ones
+    replay a captured launch; repeated calls with eager work in between."""
+    _say(f"direct and replayed launches, {n_query} queries")
+    rng = np.random.default_rng(41)
+    ims = [synth.desc(rng, 700), synth.desc(rng, n_query)]
+    oc, ok = oracle.build_codes(ims, *mats)
+    pairs = np.array([[1, 0]], dtype=np.int32)
+    exp = _oracle_all(ims, oc, ok, pairs, k=10)
+    m = binding.Matcher(*mats)
+    dimgs, codes, keys, _ = _gpu_codes(m, ims)
+    out = tuple(torch.full((n_query,), -7, dtype=torch.int32, device="cuda") for _ in range(3))
+    replays = 0
+    for it in range(4):
+        for o in out:
+            o.fill_(-7)
+        got, st = m.match_pairs(dimgs, codes, keys, pairs, out=out)
+        replays += st["graph_replayed"]
+        torch.cuda.synchronize()
+        _assert_match(got, exp, f"call {it}")
+        m.build_codes(dimgs)
+    assert (replays > 0) == (n_query > 8192)
+
+
 def test_autotune_cache_file_and_fixed_shape(mats, monkeypatch, tmp_path):
     """The autotuner writes its choice as a JSON line to CASHASH_AUTOTUNE_CACHE
     and a new context reuses it; CASHASH_AUTOTUNE=0 uses the fixed default.
