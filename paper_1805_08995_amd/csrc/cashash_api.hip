@@ -1019,7 +1019,7 @@ static int upload_scratch(cashash_ctx* c, ScratchArea& sa, Uploader& up, std::ve
 // With a scratch area (sa) every device buffer of the job is taken from it,
 // the launch shape is the cached or default one (no tuning) and no graph is
 // captured, so nothing is allocated.
-static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullptr) {
+static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullptr, bool replay = true) {
     const int n_img = (int)J.imgs.size();
     const int64_t n_pairs = (int64_t)J.pair_q.size();
     // bucket tables for every train image
@@ -1182,7 +1182,7 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
     for (int64_t p = 0; p < n_pairs; ++p) n_queries += J.imgs[J.pair_q[p]].n;
     HIPCHK(hipEventRecord(c->job_ev[J.turn][0], c->stream));
     RETCHK(enqueue_matcher(c, P, J, shape, batched, first, n_pairs, n_items, n_queries, &c->last_launches,
-                           sa == nullptr));
+                           replay && !sa));
     HIPCHK(hipEventRecord(c->job_ev[J.turn][1], c->stream));
     c->last_shape_qt = shape.qt;
     c->last_shape_bpc = shape.bpc;
@@ -1455,9 +1455,13 @@ static int build_codes_host(cashash_ctx* c, const cashash_images* im, uint64_t* 
 // part's kernels.  A part costs a launch and the bucket tables of its train
 // images, so steps before the last use parts of up to 2^25 queries: their
 // tails overlap the next step's parts.  The last step's tail is exposed, so
-// it uses parts of a fifth of its queries, between 2^23 and 2^24.
+// it uses parts of a fifth of its queries, between 2^20 and 2^24: of 3.5 million
+// queries (30 images of 8000) one part measured 4141 us per call, parts of 2^21
+// 3382, 2^20 3200, 2^19 3798; of 14 million two parts 11175, 2^22 9836, 2^21
+// 9967, 2^20 10707.  The parts are launched directly: they differ, and captured
+// launches of more than four of them would replace each other.
 constexpr int64_t kPartQueries = (int64_t)1 << 25;
-constexpr int64_t kLastPartMin = (int64_t)1 << 23, kLastPartMax = (int64_t)1 << 24;
+constexpr int64_t kLastPartMin = (int64_t)1 << 20, kLastPartMax = (int64_t)1 << 24;
 
 // CASHASH_PART_QUERIES, if set (1 .. 2^27), fixes the part size of every
 // step (small inputs then run as many parts, as tests do); 0 otherwise.
@@ -1635,7 +1639,7 @@ static int match_host(cashash_ctx* c, const cashash_images* im, const uint64_t* 
             Js.o_d1 = Js.o_idx + nq;
             Js.o_d2 = Js.o_d1 + nq;
             RETCHK(c->pin_out[turn].ensure((size_t)std::max<int64_t>(nq, 1) * 12));
-            RETCHK(launch_match_job(c, Js));
+            RETCHK(launch_match_job(c, Js, nullptr, false));
             HIPCHK(hipEventRecord(c->slot_free_ev[si], c->stream));
             HIPCHK(hipEventRecord(c->slot_free_ev[sk], c->stream));
             // the download runs on its own stream once the part's kernels
