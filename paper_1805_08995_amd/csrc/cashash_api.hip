@@ -1014,12 +1014,15 @@ static int upload_scratch(cashash_ctx* c, ScratchArea& sa, Uploader& up, std::ve
     return CASHASH_OK;
 }
 
+// Pairs up to which a call is planned before its bucket tables are built.
+constexpr int64_t kJoinPairs = 256;
+
 // Enqueues bucket tables and matcher launches for J on c->stream, plus the
 // read-back of the statistics into pinned memory; finish_match_job waits.
 // With a scratch area (sa) every device buffer of the job is taken from it,
 // the launch shape is the cached or default one (no tuning) and no graph is
 // captured, so nothing is allocated.
-static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullptr, bool replay = true) {
+static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullptr) {
     const int n_img = (int)J.imgs.size();
     const int64_t n_pairs = (int64_t)J.pair_q.size();
     // bucket tables for every train image
@@ -1054,12 +1057,15 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
     std::vector<PairTiles> pt;
     std::vector<int64_t> first;
     int64_t max_items = 1;
-    // All tables go in one upload, and the work items are made beside the bucket
-    // tables: two launches per call.  (Planning the pairs behind the launch of the
-    // bucket tables, with an upload and a launch more, measured 57.7 us per call
-    // against 55.9 for one pair of 2000, 187.4 against 181.7 for 120 and 526.6
-    // against 526.1 for 1035.)
-    Uploader up;  // image views, table outputs, train list, pairs, tile table
+    // Few pairs: all tables go in one upload, and the work items are made beside
+    // the bucket tables, two launches per call.  More: the pairs are planned
+    // behind the launch of the bucket tables, with an upload and a launch more
+    // (57.7 us per call against 55.9 for one pair of 2000, 187.4 against 181.7
+    // for 120, 526.6 against 526.1 for 1035; but with host buffers, where other
+    // streams copy at the same time, the streamed uneven set takes 222-240 ms
+    // per call in parts of two uploads each, and 250 to 375 in parts of one).
+    const bool joined = sa || n_pairs <= kJoinPairs;
+    Uploader up;  // image views, table outputs, train list; pairs, tile table
     std::vector<PairDev> pd;
     auto plan = [&]() {
         double sum_nt = 0, sum_nq = 0;
@@ -1120,7 +1126,7 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
         up.add(train_list);
         return CASHASH_OK;
     };
-    plan();
+    if (joined) plan();
     if (sa) {
         // the whole call must fit the scratch before any device work starts
         const size_t up1_bytes = ((((size_t)n_img * sizeof(ImgDev) + 255) & ~size_t(255)) +
@@ -1142,18 +1148,28 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
                             sa->cap);
     }
     RETCHK(tables());
-    up.add(pd);
-    up.add(pt);
     std::vector<const void*> d;
-    if (sa) {
-        RETCHK(upload_scratch(c, *sa, up, d));
+    // from the first of the two areas on, so that the tables' addresses stay from
+    // call to call
+    c->meta_turn[kMetaMatch] = 0;
+    if (joined) {
+        up.add(pd);
+        up.add(pt);
+        RETCHK(sa ? upload_scratch(c, *sa, up, d) : upload_meta(c, up, d, kMetaMatch));
+        P.dI = (const ImgDev*)d[0];
     } else {
-        // always the same one of the two areas, so that the tables' addresses
-        // stay from call to call
-        c->meta_turn[kMetaMatch] = 0;
         RETCHK(upload_meta(c, up, d, kMetaMatch));
+        P.dI = (const ImgDev*)d[0];
+        HIPCHK(launch_bucket(c->stream, J.epi, P.dI, (const TableOut*)d[1], (const int32_t*)d[2],
+                             (int)train_list.size(), nullptr));
+        plan();
+        Uploader up2;
+        up2.add(pd);
+        up2.add(pt);
+        std::vector<const void*> d2;
+        RETCHK(upload_meta(c, up2, d2, kMetaMatch));
+        d.insert(d.end(), d2.begin(), d2.end());
     }
-    P.dI = (const ImgDev*)d[0];
     P.dP = (const PairDev*)d[3];
     P.prm.k = c->cfg.k;
     P.prm.tau = c->cfg.max_hamming;
@@ -1174,15 +1190,18 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
     const int64_t n_items = first[n_pairs];
     ItemArgs ia;
     RETCHK(item_args(P, shape.qt, (const PairTiles*)d[4], (int32_t)pt.size(), n_items, &ia));
-    HIPCHK(launch_bucket(c->stream, J.epi, P.dI, (const TableOut*)d[1], (const int32_t*)d[2], (int)train_list.size(),
-                         ia));
+    if (joined)
+        HIPCHK(launch_bucket(c->stream, J.epi, P.dI, (const TableOut*)d[1], (const int32_t*)d[2],
+                             (int)train_list.size(), &ia));
+    else
+        HIPCHK(launch_make_items(c->stream, ia, P.dI));
     J.turn = c->job_turn;
     c->job_turn ^= 1;
     int64_t n_queries = 0;
     for (int64_t p = 0; p < n_pairs; ++p) n_queries += J.imgs[J.pair_q[p]].n;
     HIPCHK(hipEventRecord(c->job_ev[J.turn][0], c->stream));
     RETCHK(enqueue_matcher(c, P, J, shape, batched, first, n_pairs, n_items, n_queries, &c->last_launches,
-                           replay && !sa));
+                           sa == nullptr));
     HIPCHK(hipEventRecord(c->job_ev[J.turn][1], c->stream));
     c->last_shape_qt = shape.qt;
     c->last_shape_bpc = shape.bpc;
@@ -1455,11 +1474,9 @@ static int build_codes_host(cashash_ctx* c, const cashash_images* im, uint64_t* 
 // part's kernels.  A part costs a launch and the bucket tables of its train
 // images, so steps before the last use parts of up to 2^25 queries: their
 // tails overlap the next step's parts.  The last step's tail is exposed, so
-// it uses parts of a fifth of its queries, between 2^20 and 2^24: of 3.5 million
-// queries (30 images of 8000) one part measured 4141 us per call, parts of 2^21
-// 3382, 2^20 3200, 2^19 3798; of 14 million two parts 11175, 2^22 9836, 2^21
-// 9967, 2^20 10707.  The parts are launched directly: they differ, and captured
-// launches of more than four of them would replace each other.
+// it uses parts of a fifth of its queries, between 2^20 and 2^24: 30 images of
+// 8000 (3.5 million queries) 4066 us per call as one part of up to 2^23, 3183 in
+// four; 60 images (14 million) 9107 in two parts, 8976 in five.
 constexpr int64_t kPartQueries = (int64_t)1 << 25;
 constexpr int64_t kLastPartMin = (int64_t)1 << 20, kLastPartMax = (int64_t)1 << 24;
 
@@ -1639,7 +1656,7 @@ static int match_host(cashash_ctx* c, const cashash_images* im, const uint64_t* 
             Js.o_d1 = Js.o_idx + nq;
             Js.o_d2 = Js.o_d1 + nq;
             RETCHK(c->pin_out[turn].ensure((size_t)std::max<int64_t>(nq, 1) * 12));
-            RETCHK(launch_match_job(c, Js, nullptr, false));
+            RETCHK(launch_match_job(c, Js));
             HIPCHK(hipEventRecord(c->slot_free_ev[si], c->stream));
             HIPCHK(hipEventRecord(c->slot_free_ev[sk], c->stream));
             // the download runs on its own stream once the part's kernels

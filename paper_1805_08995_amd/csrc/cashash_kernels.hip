@@ -44,6 +44,10 @@ __device__ __forceinline__ void make_item(const ItemArgs& a, const ImgDev* __res
     a.items[i] = Item{p, q0, min(a.qt, nq - q0), 0};
 }
 
+__global__ void make_items_kernel(ItemArgs a, const ImgDev* __restrict__ imgs) {
+    make_item(a, imgs, (int32_t)(blockIdx.x * blockDim.x + threadIdx.x));
+}
+
 // ------------------------------------------------------------------ column sums
 // bias_j = (r_j . S) / N in binary64, rounded once to fp32 for the fast path.
 // One block of at least kRows threads; Rt is R transposed ([128][kRows]: a
@@ -824,6 +828,12 @@ hipError_t launch_fill_u32(hipStream_t s, uint32_t* p, int64_t n, uint32_t v) {
     return hipSuccess;
 }
 
+hipError_t launch_make_items(hipStream_t s, const ItemArgs& a, const ImgDev* imgs) {
+    const unsigned threads = (unsigned)std::max(a.n_items, kCtlWords);
+    CH_LAUNCH(make_items_kernel, dim3((threads + 255) / 256), dim3(256), 0, s, a, imgs);
+    return hipSuccess;
+}
+
 hipError_t launch_colsum(hipStream_t s, const ImgDev* imgs, const RowChunk* chunks, int n_chunks,
                          unsigned long long* S) {
     if (n_chunks <= 0) return hipSuccess;
@@ -875,9 +885,12 @@ hipError_t launch_proj_fp32(hipStream_t s, const ImgDev* imgs, const CodeOut* ou
 }
 
 hipError_t launch_bucket(hipStream_t s, bool epi, const ImgDev* imgs, const TableOut* touts, const int32_t* train_list,
-                         int n_train, const ItemArgs& ia) {
+                         int n_train, const ItemArgs* items) {
+    const ItemArgs ia = items ? *items : ItemArgs{};
     const unsigned per = 64 * kBucketWaves;
-    const unsigned grid = (unsigned)n_train * kTables + ((unsigned)std::max(ia.n_items, kCtlWords) + per - 1) / per;
+    const unsigned grid = (unsigned)n_train * kTables +
+                          (items ? ((unsigned)std::max(ia.n_items, kCtlWords) + per - 1) / per : 0u);
+    if (grid == 0) return hipSuccess;
     if (epi)
         CH_LAUNCH(bucket_kernel<true>, dim3(grid), dim3(per), 0, s, imgs, touts, train_list, n_train, ia);
     else

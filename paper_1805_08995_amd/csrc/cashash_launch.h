@@ -24,9 +24,11 @@ hipError_t launch_proj_mfma(hipStream_t s, const ImgDev* imgs, const CodeOut* ou
 hipError_t launch_proj_fp32(hipStream_t s, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles, int n_tiles,
                             const float* R32, const float* bias, float margin, const double* R,
                             const unsigned long long* S, double n_tot, unsigned long long* counts);
-// The bucket tables of the train images and the call's work items.
+// Work items of the pair tile table; clears the call's control words.
+hipError_t launch_make_items(hipStream_t s, const ItemArgs& a, const ImgDev* imgs);
+// The bucket tables of the train images and, with items, the work items too.
 hipError_t launch_bucket(hipStream_t s, bool epi, const ImgDev* imgs, const TableOut* touts,
-                         const int32_t* train_list, int n_train, const ItemArgs& items);
+                         const int32_t* train_list, int n_train, const ItemArgs* items);
 hipError_t launch_match(hipStream_t s, bool epi, int ns, int grid, const ImgDev* imgs, const PairDev* pairs,
                         const Item* items, int32_t n_items, uint32_t* ctl, const MatchParams& prm, int32_t* o_idx,
                         int32_t* o_d1, int32_t* o_d2);
