@@ -45,16 +45,16 @@ HBM_PEAK_GBS = 8000.0
 # SQ_INSTS_VALU.  Valid only for the matcher sources they were taken on
 # (sha256 over MATCHER_SOURCES, in order); null otherwise.
 MATCHER_SOURCES = ("cashash_match.hip", "cashash_device.h", "cashash_internal.h")
-MEASURED_COUNTERS = {"sources_sha256": "0626d8f506a995414bcf9a91e016c82361edccdffa95a25744cfbd3f6c0314b0",
+MEASURED_COUNTERS = {"sources_sha256": "2be94965240baedd82cc3917b62477f9b4e1bd8b2b7cb110599e6ac482307cdf",
                      "workload": "scenes_100x8000_exhaustive_4950pairs",
-                     "fetch_bytes": int(4442402.8 * 1024 * 2), "write_bytes": int(479141.9 * 1024),
-                     "valu_insts": 8436676742}
+                     "fetch_bytes": int(4612593.8 * 1024 * 2), "write_bytes": int(798009.6 * 1024),
+                     "valu_insts": 6241148131}
 # The same for one full band-kernel launch on the epipolar workload
 # (profiles/band_kernel_epipolar_500x12000.md).
-EPIPOLAR_COUNTERS = {"sources_sha256": "0626d8f506a995414bcf9a91e016c82361edccdffa95a25744cfbd3f6c0314b0",
+EPIPOLAR_COUNTERS = {"sources_sha256": "2be94965240baedd82cc3917b62477f9b4e1bd8b2b7cb110599e6ac482307cdf",
                      "workload": "epipolar_500x12000_15000pairs_band4px",
-                     "fetch_bytes": int(56264521.5 * 1024 * 2), "write_bytes": int(3739488.0 * 1024),
-                     "valu_insts": 30729692054}
+                     "fetch_bytes": int(49839804.9 * 1024 * 2), "write_bytes": int(2131974.6 * 1024),
+                     "valu_insts": 29488336904}
 # VALU issue limit: 256 CUs x 4 SIMDs, one wave64 VALU instruction per SIMD
 # every 4 cycles (16 lanes per cycle), 2.4 GHz: 614.4 G instructions/s
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4
@@ -82,7 +82,7 @@ def band_roofline(workload, kernel_ms, queries):
     matcher sources change."""
     t = measured_counters(workload, EPIPOLAR_COUNTERS)
     sec = kernel_ms * 1e-3
-    out = {"bound": "alu", "kernel": "match_kernel<true, 4, true>", "kernel_ms": round(kernel_ms, 4),
+    out = {"bound": "alu", "kernel": "band_match_kernel", "kernel_ms": round(kernel_ms, 4),
            "unit": "G VALU wave64 instructions/s", "peak": round(VALU_ISSUE_PEAK / 1e9, 1),
            "achieved": None, "frac": None, "traffic": None, "hbm": None}
     if t is not None:
@@ -104,7 +104,7 @@ def roofline(workload, kernel_ms, stats):
     t = measured_counters(workload)
     sec = kernel_ms * 1e-3
     abytes = algorithmic_bytes(stats)
-    out = {"bound": "alu", "kernel": "match_kernel<false, 4, false>", "kernel_ms": round(kernel_ms, 4),
+    out = {"bound": "alu", "kernel": "plain_match_kernel<4>", "kernel_ms": round(kernel_ms, 4),
            "unit": "G VALU wave64 instructions/s", "peak": round(VALU_ISSUE_PEAK / 1e9, 1),
            "achieved": None, "frac": None, "traffic": None,
            "hbm": None,
@@ -370,7 +370,7 @@ def epipolar_leg(binding, synth, torch, mats, reps=5):
     dt, (_, st) = _median_calls(call, reps)
     P = len(w.pairs)
     res = {"workload": f"epipolar_500x12000_{P}pairs_band4px", "pairs_per_s": round(P / dt, 1),
-           "ms_per_call_median": round(dt * 1e3, 3), "kernel": "match_kernel<true, 4, true>",
+           "ms_per_call_median": round(dt * 1e3, 3), "kernel": "band_match_kernel",
            "kernel_ms_median": round(float(np.median(kms)), 3), "calls": reps,
            "bucket_entries_per_query": round(st["bucket_entries"] / st["queries"], 2),
            "band_survivors_per_query": round(st["union_size"] / st["queries"], 2),
