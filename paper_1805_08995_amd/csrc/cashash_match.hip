@@ -716,7 +716,7 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(false, NC)) void plain_mat
                     select_64(list, hist, n_pass, K, kk, lane, sel, sel_n, hG);
                 } else {
                     select_keys<kPassSlots>(list, n_pass, K, kk, lane, sel, sel_n, hG);
-                    hK = max(hK, 5u << 16) - 0x10000u;
+                    hK = min(tauK, max(hK, (5u << 16) | 0xFFFFu) - 0x10000u);
                 }
             }
             v_kept = lane == qi ? (sel_n - at) | (at << 16) : v_kept;
