@@ -1067,6 +1067,11 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
     const bool joined = sa || n_pairs <= kJoinPairs;
     Uploader up;  // image views, table outputs, train list; pairs, tile table
     std::vector<PairDev> pd;
+    auto tile = [&]() {
+        pt = pair_tiles(J, P.order, shape.qt, &first);
+        max_items = std::max<int64_t>(1, first[n_pairs]);
+        P.items_cap = max_items;
+    };
     auto plan = [&]() {
         double sum_nt = 0, sum_nq = 0;
         for (int64_t p = 0; p < n_pairs; ++p) {
@@ -1095,9 +1100,7 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
                           batched ? std::max(1, hit->second.bpc) : 0};
         else if (tuned && !sa && n_pairs > 0)
             tune_cache_store(c, key, shape);
-        pt = pair_tiles(J, P.order, shape.qt, &first);
-        max_items = std::max<int64_t>(1, first[n_pairs]);
-        P.items_cap = max_items;
+        tile();
         pd.resize(n_pairs);
         for (int64_t p = 0; p < n_pairs; ++p) {
             pd[p].qi = J.pair_q[p];
@@ -1132,20 +1135,33 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
         const size_t up1_bytes = ((((size_t)n_img * sizeof(ImgDev) + 255) & ~size_t(255)) +
                                   (((size_t)n_img * sizeof(TableOut) + 255) & ~size_t(255)) +
                                   train_list.size() * sizeof(int32_t));
-        const size_t up2_bytes = ((pd.size() * sizeof(PairDev) + 255) & ~size_t(255)) + pt.size() * sizeof(PairTiles);
-        ScratchArea probe;
-        probe.base = sa->base;
-        probe.cap = sa->cap;
-        probe.used = sa->used;
-        const size_t pieces[] = {std::max<size_t>(tbytes, 1), std::max<size_t>(up1_bytes, 1),
-                                 std::max<size_t>(up2_bytes, 1), (size_t)max_items * sizeof(Item),
-                                 (size_t)kCtlWords * 4, 64};
         size_t need = 0;
-        for (size_t n : pieces) need = ((need + 255) & ~size_t(255)) + n;
-        for (size_t n : pieces)
-            if (!probe.take(n))
-                return fail(CASHASH_E_LIMIT, "the call needs %zu bytes of scratch, more than its %zu bytes", need,
-                            sa->cap);
+        auto fits = [&]() {
+            const size_t up2_bytes =
+                ((pd.size() * sizeof(PairDev) + 255) & ~size_t(255)) + pt.size() * sizeof(PairTiles);
+            ScratchArea probe;
+            probe.base = sa->base;
+            probe.cap = sa->cap;
+            probe.used = sa->used;
+            const size_t pieces[] = {std::max<size_t>(tbytes, 1), std::max<size_t>(up1_bytes, 1),
+                                     std::max<size_t>(up2_bytes, 1), (size_t)max_items * sizeof(Item),
+                                     (size_t)kCtlWords * 4, 64};
+            need = 0;
+            for (size_t n : pieces) need = ((need + 255) & ~size_t(255)) + n;
+            for (size_t n : pieces)
+                if (!probe.take(n)) return false;
+            return true;
+        };
+        bool ok = fits();
+        if (!ok && batched) {
+            // small tiles are faster in a small call but take up to eight times
+            // the work items: the largest tiles decide what fits
+            shape.qt = std::min(kMaxTile, std::max(1, kSelCap / c->cfg.k));
+            tile();
+            ok = fits();
+        }
+        if (!ok)
+            return fail(CASHASH_E_LIMIT, "the call needs %zu bytes of scratch, more than its %zu bytes", need, sa->cap);
     }
     RETCHK(tables());
     std::vector<const void*> d;
