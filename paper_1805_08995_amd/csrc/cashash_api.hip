@@ -775,7 +775,9 @@ static bool autotune_enabled() {
 
 // With CASHASH_AUTOTUNE_CACHE naming a file, the shapes used are kept there as
 // JSON lines, per (form, epipolar, k, train size class, query size class, call
-// size class), and a shape found there is used instead of the rule's.
+// size class), and a shape found there is used instead of the rule's; a line
+// without the call size class holds for every call size.  CASHASH_AUTOTUNE=0
+// adds no line.
 static std::string tune_key(bool batched, bool epi, int k, double mean_nt, double mean_nq, double queries) {
     char b[160];
     auto cls = [](double v) { return (int)std::lround(std::log2(std::max(1.0, v))); };
@@ -1091,14 +1093,14 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
         // launch shape: from the cache file, or the rule's
         tune_cache_load(c);
         shape = choose_shape(c, c->cfg.k, batched, J.epi, (int64_t)sum_nq);
-        const bool tuned = autotune_enabled();
-        const std::string key = tune_key(batched, J.epi, c->cfg.k, n_pairs ? sum_nt / n_pairs : 0.0,
-                                         n_pairs ? sum_nq / n_pairs : 0.0, sum_nq);
+        const double mean_nt = n_pairs ? sum_nt / n_pairs : 0.0, mean_nq = n_pairs ? sum_nq / n_pairs : 0.0;
+        const std::string key = tune_key(batched, J.epi, c->cfg.k, mean_nt, mean_nq, sum_nq);
         auto hit = c->tuned.find(key);
-        if (tuned && hit != c->tuned.end())
+        if (hit == c->tuned.end()) hit = c->tuned.find(key.substr(0, key.rfind('/')));
+        if (hit != c->tuned.end())
             shape = Shape{std::max(1, std::min({hit->second.qt, kMaxTile, kSelCap / c->cfg.k})),
                           batched ? std::max(1, hit->second.bpc) : 0};
-        else if (tuned && !sa && n_pairs > 0)
+        else if (autotune_enabled() && !sa && n_pairs > 0)
             tune_cache_store(c, key, shape);
         tile();
         pd.resize(n_pairs);
