@@ -668,14 +668,15 @@ static int run_project(cashash_ctx* c, const std::vector<ImgDev>& imgs, std::vec
     }
     const float coef = (float)c->cfg.margin_coef;
     unsigned long long* counts = c->dCount.as<unsigned long long>();
-    if (c->cfg.mode == CASHASH_MODE_BATCHED_BF16X2) {
-        const ProjPlan pl = proj_plan(n_tiles, c->n_cu);
-        if (pl.near_bytes()) RETCHK(c->near.ensure(pl.near_bytes()));
+    const bool mfma = c->cfg.mode == CASHASH_MODE_BATCHED_BF16X2;
+    const ProjPlan pl = mfma ? proj_plan(n_tiles, c->n_cu) : plain_plan(n_tiles);
+    if (pl.near_bytes()) RETCHK(c->near.ensure(pl.near_bytes()));
+    if (mfma)
         HIPCHK(launch_proj_mfma(c->stream, dI, dO, dT, n_tiles, c->dFrag.as<uint4>(), c->dBias.as<float>(), coef,
                                 c->dR64.as<double>(), S, n_tot, counts, pl, c->near.p));
-    } else
+    else
         HIPCHK(launch_proj_fp32(c->stream, dI, dO, dT, n_tiles, c->dR32.as<float>(), c->dBias.as<float>(), coef,
-                                c->dR64.as<double>(), S, n_tot, counts));
+                                c->dR64.as<double>(), S, n_tot, counts, pl, c->near.p));
     return CASHASH_OK;
 }
 

@@ -81,6 +81,16 @@ inline ProjPlan proj_plan(int n_tiles, int n_cu) {
     return p;
 }
 
+// The plain FP32 form: a block per 16 tiles (a thread per descriptor), always
+// with the near list.
+inline ProjPlan plain_plan(int n_tiles) {
+    ProjPlan p;
+    p.tpg = 16;
+    p.groups = p.grid = (n_tiles + 15) / 16;
+    p.fused = false;
+    return p;
+}
+
 // Column sums of a whole set: kSumSlots copies of kDim sums, the ticket of the
 // blocks that added to them, and the totals.  Sums over several launches use
 // the first kDim words alone.

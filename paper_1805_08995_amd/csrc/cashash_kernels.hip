@@ -652,24 +652,27 @@ __global__ __launch_bounds__(kNearThreads) void near_kernel(const ImgDev* __rest
 }
 
 // Plain FP32 form: one thread per descriptor, 176 fp32 FMA chains over the
-// descriptor held in registers; the rows are wave-uniform scalar loads.
+// descriptor held in registers; the rows are wave-uniform scalar loads.  What
+// lies inside the margin goes into the block's three segments of the near list
+// (256 entries each), in any order.
+// Bound by the fp32 multiply-adds: 240k descriptors 330 us, and 19 for near_kernel
+// (506 us with the recompute in this kernel).
 __global__ __launch_bounds__(256) void proj_fp32_kernel(const ImgDev* __restrict__ imgs,
                                                         const CodeOut* __restrict__ outs,
                                                         const RowChunk* __restrict__ tiles, int n_tiles,
                                                         const float* __restrict__ R32,
                                                         const float* __restrict__ bias, float margin_coef,
-                                                        const double* __restrict__ R,
-                                                        const unsigned long long* __restrict__ S, double n_tot,
-                                                        unsigned long long* __restrict__ counts) {
-    __shared__ ProjBlock<256> blk;
+                                                        NearEntry* __restrict__ near,
+                                                        uint32_t* __restrict__ seg_count) {
+    __shared__ uint32_t s_cnt[3];
     const int tid = threadIdx.x;
-    if (tid < kDim) blk.S[tid] = (double)S[tid];
+    if (tid < 3) s_cnt[tid] = 0u;
+    __syncthreads();
     const int t = blockIdx.x * blockDim.x + tid;
     const int tile = min(t >> 4, n_tiles - 1), n = t & 15;
     const RowChunk tc = tiles[tile];
     const bool live = (t >> 4) < n_tiles && n < tc.nr;
-    const uint8_t* x = imgs[tc.img].desc + (int64_t)(tc.r0 + (live ? n : 0)) * kDim;
-    const uint4* xp = reinterpret_cast<const uint4*>(x);
+    const uint4* xp = reinterpret_cast<const uint4*>(imgs[tc.img].desc + (int64_t)(tc.r0 + (live ? n : 0)) * kDim);
     float xf[kDim];
     uint32_t sq = 0;
 #pragma unroll
@@ -683,13 +686,14 @@ __global__ __launch_bounds__(256) void proj_fp32_kernel(const ImgDev* __restrict
             for (int b = 0; b < 4; ++b) xf[c * 16 + a * 4 + b] = (float)((ws[a] >> (8 * b)) & 0xFFu);
         }
     }
-    const float base_margin = live ? margin_coef * sqrtf((float)sq) + 0x1p-26f : -__builtin_inff();
-    blk.x[tid] = x;
-    for (int wd = 0; wd < 6; ++wd) {
-        uint32_t w = 0, m = 0;
-        const int rows = wd < 5 ? 32 : kRows - 160;
+    const float base_margin = margin_coef * sqrtf((float)sq) + 0x1p-26f;
+    uint64_t w[3] = {0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        uint64_t m = 0;
+        const int rows = k < 2 ? 64 : kRows - 128;
         for (int rr = 0; rr < rows; ++rr) {
-            const int r = 32 * wd + rr;
+            const int r = 64 * k + rr;
             const float* rp = R32 + r * kDim;
             float acc = 0.f;
 #pragma unroll
@@ -698,15 +702,21 @@ __global__ __launch_bounds__(256) void proj_fp32_kernel(const ImgDev* __restrict
             const float v = acc - bv;
             const float M = base_margin + 0x1p-20f * fabsf(bv);
             const bool nr = !(fabsf(v) > M);
-            w |= (uint32_t)(!nr && v > 0.f) << rr;
-            m |= (uint32_t)nr << rr;
+            const bool bit = !nr && v > 0.f;
+            w[k] |= (uint64_t)bit << rr;
+            m |= (uint64_t)nr << rr;
         }
-        blk.bits[tid][wd] = w;
-        blk.near[tid][wd] = m;
+        if (live && m != 0)
+            gstore(reinterpret_cast<uint4*>(near + (size_t)(3 * blockIdx.x + k) * 256 + atomicAdd(&s_cnt[k], 1u)),
+                   make_uint4((uint32_t)tc.img, (uint32_t)(tc.r0 + n), (uint32_t)m, (uint32_t)(m >> 32)));
+    }
+    if (live) {
+        const uint32_t b[6] = {(uint32_t)w[0], (uint32_t)(w[0] >> 32), (uint32_t)w[1], (uint32_t)(w[1] >> 32),
+                               (uint32_t)w[2], (uint32_t)(w[2] >> 32)};
+        store_code(outs[tc.img], tc.r0 + n, b);
     }
     __syncthreads();
-    blk.recompute(R, n_tot, counts);
-    if (live) store_code(outs[tc.img], tc.r0 + n, blk.bits[tid]);
+    if (tid < 3) seg_count[3 * blockIdx.x + tid] = s_cnt[tid];
 }
 
 // ------------------------------------------------------------------ bucket tables
@@ -855,6 +865,15 @@ hipError_t launch_bias(hipStream_t s, const double* Rt, const unsigned long long
     return hipSuccess;
 }
 
+// The recompute of what a projection of plan pl left in its near list.
+static hipError_t launch_near(hipStream_t s, const ImgDev* imgs, const CodeOut* outs, const ProjPlan& pl,
+                              const NearEntry* list, const uint32_t* seg_count, const double* R,
+                              const unsigned long long* S, double n_tot, unsigned long long* counts) {
+    CH_LAUNCH(near_kernel, dim3((unsigned)((pl.grid + kNearSegs - 1) / kNearSegs * 3)), dim3(kNearThreads), 0, s, imgs,
+              outs, list, seg_count, pl.seg_cap(), (uint32_t)pl.grid, R, S, n_tot, counts);
+    return hipSuccess;
+}
+
 hipError_t launch_proj_mfma(hipStream_t s, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles, int n_tiles,
                             const uint4* frag, const float* bias, float margin, const double* R,
                             const unsigned long long* S, double n_tot, unsigned long long* counts, const ProjPlan& pl,
@@ -869,19 +888,19 @@ hipError_t launch_proj_mfma(hipStream_t s, const ImgDev* imgs, const CodeOut* ou
     NearEntry* list = reinterpret_cast<NearEntry*>(static_cast<uint8_t*>(near) + pl.count_bytes());
     CH_LAUNCH(proj_mfma_kernel<false>, dim3((unsigned)pl.grid), dim3(256), 0, s, imgs, outs, tiles, n_tiles, pl.tpg,
               pl.groups, frag, bias, margin, R, S, n_tot, counts, list, seg_count, pl.seg_cap());
-    CH_LAUNCH(near_kernel, dim3((unsigned)((pl.grid + kNearSegs - 1) / kNearSegs * 3)), dim3(kNearThreads), 0, s, imgs,
-              outs, (const NearEntry*)list, (const uint32_t*)seg_count, pl.seg_cap(), (uint32_t)pl.grid, R, S, n_tot,
-              counts);
-    return hipSuccess;
+    return launch_near(s, imgs, outs, pl, list, seg_count, R, S, n_tot, counts);
 }
 
 hipError_t launch_proj_fp32(hipStream_t s, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles, int n_tiles,
                             const float* R32, const float* bias, float margin, const double* R,
-                            const unsigned long long* S, double n_tot, unsigned long long* counts) {
+                            const unsigned long long* S, double n_tot, unsigned long long* counts, const ProjPlan& pl,
+                            void* near) {
     if (n_tiles <= 0) return hipSuccess;
-    CH_LAUNCH(proj_fp32_kernel, dim3((unsigned)((n_tiles + 15) / 16)), dim3(256), 0, s, imgs, outs, tiles, n_tiles, R32,
-              bias, margin, R, S, n_tot, counts);
-    return hipSuccess;
+    uint32_t* seg_count = static_cast<uint32_t*>(near);
+    NearEntry* list = reinterpret_cast<NearEntry*>(static_cast<uint8_t*>(near) + pl.count_bytes());
+    CH_LAUNCH(proj_fp32_kernel, dim3((unsigned)pl.grid), dim3(256), 0, s, imgs, outs, tiles, n_tiles, R32, bias, margin,
+              list, seg_count);
+    return launch_near(s, imgs, outs, pl, list, seg_count, R, S, n_tot, counts);
 }
 
 hipError_t launch_bucket(hipStream_t s, bool epi, const ImgDev* imgs, const TableOut* touts, const int32_t* train_list,

@@ -23,7 +23,8 @@ hipError_t launch_proj_mfma(hipStream_t s, const ImgDev* imgs, const CodeOut* ou
                             void* near);
 hipError_t launch_proj_fp32(hipStream_t s, const ImgDev* imgs, const CodeOut* outs, const RowChunk* tiles, int n_tiles,
                             const float* R32, const float* bias, float margin, const double* R,
-                            const unsigned long long* S, double n_tot, unsigned long long* counts);
+                            const unsigned long long* S, double n_tot, unsigned long long* counts, const ProjPlan& pl,
+                            void* near);
 // Work items of the pair tile table; clears the call's control words.
 hipError_t launch_make_items(hipStream_t s, const ItemArgs& a, const ImgDev* imgs);
 // The bucket tables of the train images and, with items, the work items too.
