@@ -354,99 +354,122 @@ __device__ __forceinline__ void scan_chunks(int lane, const char* code, const ch
     }
 }
 
-// The kk smallest of the n listed keys (all <= K, distinct, n >= kk >= 1, S
-// registers per lane): their indices appended to the tile list.
-// Step 3: the Hamming distance H* of the kk-th by counting with ballots from
-// the previous query's H* (hG), ties there by index.
+// The n listed keys, S registers per lane (~0u past them).
 template <int S>
-__device__ __forceinline__ void select_keys(const uint32_t* list, uint32_t n, uint32_t K, uint32_t kk, int lane,
-                                            uint16_t* sel, uint32_t& sel_n, int32_t& hG) {
-    uint32_t r[S];
+__device__ __forceinline__ void read_list(uint32_t (&r)[S], const uint32_t* list, uint32_t n, int lane) {
 #pragma unroll
     for (int s = 0; s < S; ++s) {
         const uint32_t v = list[64 * s + lane];
         r[s] = 64u * s + (uint32_t)lane < n ? v : ~0u;
     }
-    auto count = [&](uint32_t x) {  // listed keys <= x
+}
+
+// A bound that exactly the kk smallest of the n keys r (all <= K, distinct,
+// n > kk >= 1) are within.  Step 3: the Hamming distance H* of the kk-th by
+// counting with ballots from the previous query's H* (hG), ties there by index.
+template <int S>
+__device__ __forceinline__ uint32_t kth_bound(const uint32_t (&r)[S], uint32_t n, uint32_t K, uint32_t kk,
+                                              int32_t& hG) {
+    auto count = [&](uint32_t x) {  // keys <= x
         uint32_t c = 0;
 #pragma unroll
         for (int s = 0; s < S; ++s) c += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(r[s] <= x));
         return c;
     };
     auto upto = [](int32_t h) { return ((uint32_t)h << 16) | 0xFFFFu; };
-    uint32_t tkey = K;
-    if (n > kk) {
-        int32_t lo = -1, hi = (int32_t)(K >> 16), step = 2;
-        uint32_t chi = n;  // keys of Hamming distance <= hi; fewer than kk at lo
-        const int32_t g = min(hG, hi - 1);
-        if (g >= 0) {
-            uint32_t c = count(upto(g));
-            if (c >= kk) {
-                hi = g;
+    int32_t lo = -1, hi = (int32_t)(K >> 16), step = 2;
+    uint32_t chi = n;  // keys of Hamming distance <= hi; fewer than kk at lo
+    const int32_t g = min(hG, hi - 1);
+    if (g >= 0) {
+        uint32_t c = count(upto(g));
+        if (c >= kk) {
+            hi = g;
+            chi = c;
+            while (hi - step > lo) {
+                c = count(upto(hi - step));
+                if (c < kk) {
+                    lo = hi - step;
+                    break;
+                }
+                hi -= step;
                 chi = c;
-                while (hi - step > lo) {
-                    c = count(upto(hi - step));
-                    if (c < kk) {
-                        lo = hi - step;
-                        break;
-                    }
-                    hi -= step;
+                step += step;
+            }
+        } else {
+            lo = g;
+            while (lo + step < hi) {
+                c = count(upto(lo + step));
+                if (c >= kk) {
+                    hi = lo + step;
                     chi = c;
-                    step += step;
+                    break;
                 }
-            } else {
-                lo = g;
-                while (lo + step < hi) {
-                    c = count(upto(lo + step));
-                    if (c >= kk) {
-                        hi = lo + step;
-                        chi = c;
-                        break;
-                    }
-                    lo += step;
-                    step += step;
-                }
-            }
-        }
-        while (hi - lo > 1) {
-            const int32_t mid = (lo + hi) >> 1;
-            const uint32_t c = count(upto(mid));
-            if (c >= kk) {
-                hi = mid;
-                chi = c;
-            } else {
-                lo = mid;
-            }
-        }
-        hG = hi;
-        tkey = min(K, upto(hi));
-        if (chi > kk) {
-            // more at H* than needed: the one with exactly kk keys up to it
-            const uint32_t at = (uint32_t)hi << 16, top = tkey;
-            bool found = false;
-            tkey = max(at, 1u) - 1u;
-#pragma unroll
-            for (int s = 0; s < S; ++s) {
-                if (found) break;
-                uint64_t m = __builtin_amdgcn_ballot_w64(r[s] >= at) & __builtin_amdgcn_ballot_w64(r[s] <= top);
-                while (m != 0) {
-                    const uint32_t x = readlane(r[s], __ffsll((unsigned long long)m) - 1);
-                    if (count(x) == kk) {
-                        tkey = x;
-                        found = true;
-                        break;
-                    }
-                    m &= m - 1;
-                }
+                lo += step;
+                step += step;
             }
         }
     }
+    while (hi - lo > 1) {
+        const int32_t mid = (lo + hi) >> 1;
+        const uint32_t c = count(upto(mid));
+        if (c >= kk) {
+            hi = mid;
+            chi = c;
+        } else {
+            lo = mid;
+        }
+    }
+    hG = hi;
+    const uint32_t top = min(K, upto(hi));
+    if (chi == kk) return top;
+    // more at H* than needed: by halves over the indices (the keys are
+    // distinct, so the count goes through kk)
+    uint32_t from = (uint32_t)hi << 16, to = top;
+    while (from < to) {
+        const uint32_t mid = from + ((to - from) >> 1);
+        const uint32_t c = count(mid);
+        if (c == kk) return mid;
+        if (c < kk)
+            from = mid + 1u;
+        else
+            to = mid;
+    }
+    return max((uint32_t)hi << 16, 1u) - 1u;
+}
+
+// The kk smallest of the n listed keys (all <= K, distinct, n >= kk >= 1, S
+// registers per lane): their indices appended to the tile list.
+template <int S>
+__device__ __forceinline__ void select_keys(const uint32_t* list, uint32_t n, uint32_t K, uint32_t kk, int lane,
+                                            uint16_t* sel, uint32_t& sel_n, int32_t& hG) {
+    uint32_t r[S];
+    read_list(r, list, n, lane);
+    const uint32_t tkey = n > kk ? kth_bound(r, n, K, kk, hG) : K;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
         const bool keep = r[s] <= tkey;
         const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
         if (keep) list_at(sel, sel_n, m) = (uint16_t)r[s];
         sel_n += (uint32_t)__popcll(m);
+    }
+}
+
+// The list brought down to the kk smallest of its n > kk keys; K: the bound
+// that keys yet to come must be within.
+__device__ __forceinline__ void shorten_list(uint32_t* list, uint32_t& n, uint32_t& K, uint32_t kk, int lane,
+                                             int32_t& hG) {
+    uint32_t r[kListKeys / 64];
+    wave_sync();
+    read_list(r, list, n, lane);
+    K = kth_bound(r, n, K, kk, hG);
+    wave_sync();
+    n = 0;
+#pragma unroll
+    for (int s = 0; s < kListKeys / 64; ++s) {
+        const bool keep = r[s] <= K;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+        if (keep) list_at(list, n, m) = r[s];
+        n += (uint32_t)__popcll(m);
     }
 }
 
@@ -928,42 +951,37 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(true, 4)) void band_match_
                     list_at(list, 0u, m) = key;
                 }
             } else {
-                Threshold th;
-                do {
-                    n_pass = n_union = 0;
-                    auto add = [&](uint64_t ok, uint32_t key) {
+                // once through them: a list that gets full is brought down to
+                // its k smallest, and only smaller keys follow.  With more
+                // inside the band than the places held, every entry is tested
+                // and read again.
+                const bool held = n_surv <= (uint32_t)kBandCap;
+#pragma unroll 1
+                for (int t = 0; t < (held ? 1 : kTables); ++t) {
+                    const uint2 run = *reinterpret_cast<const uint2*>(qrow + 2 * t);
+                    const uint32_t b = uniform(run.x), n = held ? n_surv : uniform(run.y);
+#pragma unroll 1
+                    for (uint32_t i0 = 0; i0 < n; i0 += 64) {
+                        const uint32_t i = i0 + (uint32_t)lane;
+                        uint64_t live = __builtin_amdgcn_ballot_w64(i < n);
+                        uint32_t pos = b + i, t8 = 8u * (uint32_t)t;
+                        if (held) {
+                            const uint32_t e = i < n ? place[i] : 0u;
+                            pos = e & 0xFFFFFFu;
+                            t8 = e >> 24;
+                        } else {
+                            live &= __builtin_amdgcn_ballot_w64(in_band(kp_at(pos)));
+                        }
+                        if (n_pass > (uint32_t)kPassCap) shorten_list(list, n_pass, K, (uint32_t)prm.k, lane, hG);
+                        uint32_t key;
+                        const uint64_t ok = entry(t8, pos, live, key);
                         n_union += (uint32_t)__popcll(ok);
                         const uint64_t m = ok & __builtin_amdgcn_ballot_w64(key <= K);
                         if (__builtin_amdgcn_inverse_ballot_w64(m)) list_at(list, n_pass, m) = key;
                         n_pass += (uint32_t)__popcll(m);
-                    };
-                    if (n_surv <= (uint32_t)kBandCap) {
-                        for (uint32_t base = 0; base < n_surv && n_pass <= (uint32_t)kPassCap; base += 64) {
-                            const uint32_t i = base + (uint32_t)lane;
-                            const uint32_t e = i < n_surv ? place[i] : 0u;
-                            uint32_t key;
-                            const uint64_t ok =
-                                entry(e >> 24, e & 0xFFFFFFu, __builtin_amdgcn_ballot_w64(i < n_surv), key);
-                            add(ok, key);
-                        }
-                    } else {
-                        // more inside the band than the places held: every
-                        // entry is tested and read again
-                        for (int t = 0; t < kTables; ++t) {
-                            const uint2 run = *reinterpret_cast<const uint2*>(qrow + 2 * t);
-                            const uint32_t b = uniform(run.x), n = uniform(run.y);
-                            for (uint32_t i0 = 0; i0 < n && n_pass <= (uint32_t)kPassCap; i0 += 64) {
-                                const uint32_t pos = b + i0 + (uint32_t)lane;
-                                const uint64_t live = __builtin_amdgcn_ballot_w64(in_band(kp_at(pos))) &
-                                                      __builtin_amdgcn_ballot_w64(i0 + (uint32_t)lane < n);
-                                uint32_t key;
-                                const uint64_t ok = entry(8u * (uint32_t)t, pos, live, key);
-                                add(ok, key);
-                            }
-                        }
                     }
-                } while (!settled(n_pass, (uint32_t)prm.k, K, tauK) && th.move(K, n_pass, (uint32_t)prm.k, tauK));
-                n_pass = min(n_pass, (uint32_t)kPassCap);
+                }
+                if (n_pass > (uint32_t)kPassCap) shorten_list(list, n_pass, K, (uint32_t)prm.k, lane, hG);
             }
             wave_sync();
             t_union += n_union;

@@ -1,7 +1,7 @@
-"""The plain matcher's carried threshold against the oracle, bit for bit, on
-codes and keys made for it: equal keys make every train point a candidate of
-every query, and the codes set the Hamming distances.  What one query leaves
-behind must not change what the next one of its tile keeps."""
+"""The matcher's threshold and its list of candidates against the oracle, bit for
+bit, on codes and keys made for them: equal keys make every train point a
+candidate of every query, and the codes set the Hamming distances.  What one
+query leaves behind must not change what the next one of its tile keeps."""
 import numpy as np
 import pytest
 
@@ -26,7 +26,7 @@ def _codes(rng, base, distances):
     return out
 
 
-def _check(images, codes, keys, pairs, tag, **kw):
+def _check(images, codes, keys, pairs, tag, band=False, **kw):
     exp = oracle.match_pairs(images, codes, keys, pairs, **kw)
     dev = [torch.from_numpy(im).cuda() for im in images]
     dc = [torch.from_numpy(c.view(np.int64)).cuda() for c in codes]
@@ -37,6 +37,12 @@ def _check(images, codes, keys, pairs, tag, **kw):
         got, _ = m.match_pairs(dev, dc, dk, pairs)
         for g, e, name in zip(got, exp, ("match_idx", "d1sq", "d2sq")):
             assert np.array_equal(g.cpu().numpy(), e), f"{tag} {mode}: {name}"
+        if band:  # a band wider than the images: the same candidates
+            kp = [torch.rand(len(im), 2, device="cuda") * 1000 for im in images]
+            F = np.tile(np.array([0.0, 0, 0, 0, 0, -1, 0, 1, 0]), (len(pairs), 1))
+            got, _ = m.match_pairs_epipolar(dev, dc, dk, kp, pairs, F, 1e5)
+            for g, e, name in zip(got, exp, ("match_idx", "d1sq", "d2sq")):
+                assert np.array_equal(g.cpu().numpy(), e), f"{tag} {mode} band: {name}"
         m.close()
 
 
@@ -61,3 +67,25 @@ def test_limit_holds_after_a_crowded_query(tau, k):
         codes.append(np.ascontiguousarray(tc[perm]))
         keys.append(np.zeros((len(tc), 6), np.uint8))
     _check(images, codes, keys, np.array(pairs, np.int32), f"tau={tau} k={k}", k=k, tau=tau)
+
+
+@pytest.mark.parametrize("k", [1, 10, 40, 64])
+@pytest.mark.parametrize("tau", [128, 40])
+@pytest.mark.parametrize("order", ["nearer", "farther", "equal", "mixed"])
+def test_more_candidates_than_the_list_holds(k, tau, order):
+    """Around and past the 192 and 256 keys of the list, with the distances
+    falling, rising or equal along the index, or crowded at two of them, in the
+    plain form and in a band that holds them all."""
+    rng = np.random.default_rng(1000 + k)
+    a = rng.integers(0, 1 << 63, 2).astype(np.uint64)
+    nq = 40
+    images, codes, keys = [synth.desc(rng, nq)], [_codes(rng, a, [0, 1, 64] * 13 + [2])], [np.zeros((nq, 6), np.uint8)]
+    pairs = []
+    for n in (64, 65, 191, 192, 193, 255, 256, 257, 321, 700, 3000):
+        d = {"nearer": np.linspace(60, 0, n).astype(int), "farther": np.linspace(0, 60, n).astype(int),
+             "equal": np.full(n, 7), "mixed": rng.choice([3, 30, 31, 60], n)}[order]
+        pairs.append((0, len(images)))
+        images.append(synth.desc(rng, n))
+        codes.append(_codes(rng, a, d))
+        keys.append(np.zeros((n, 6), np.uint8))
+    _check(images, codes, keys, np.array(pairs, np.int32), f"{order} k={k} tau={tau}", band=True, k=k, tau=tau)
