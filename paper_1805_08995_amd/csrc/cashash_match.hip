@@ -422,19 +422,33 @@ __device__ __forceinline__ uint32_t kth_bound(const uint32_t (&r)[S], uint32_t n
     hG = hi;
     const uint32_t top = min(K, upto(hi));
     if (chi == kk) return top;
-    // more at H* than needed: by halves over the indices (the keys are
-    // distinct, so the count goes through kk)
-    uint32_t from = (uint32_t)hi << 16, to = top;
-    while (from < to) {
-        const uint32_t mid = from + ((to - from) >> 1);
-        const uint32_t c = count(mid);
-        if (c == kk) return mid;
-        if (c < kk)
-            from = mid + 1u;
-        else
-            to = mid;
+    // more at H* than needed: the bound with exactly kk keys within it (the
+    // keys are distinct, so the count goes through kk), key by key if few are
+    // there, else by halves over the indices
+    const uint32_t at = (uint32_t)hi << 16;
+    if (chi - kk < 8u) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            uint64_t m = __builtin_amdgcn_ballot_w64(r[s] >= at) & __builtin_amdgcn_ballot_w64(r[s] <= top);
+            while (m != 0) {
+                const uint32_t x = readlane(r[s], __ffsll((unsigned long long)m) - 1);
+                if (count(x) == kk) return x;
+                m &= m - 1;
+            }
+        }
+    } else {
+        uint32_t from = at, to = top;
+        while (from < to) {
+            const uint32_t mid = from + ((to - from) >> 1);
+            const uint32_t c = count(mid);
+            if (c == kk) return mid;
+            if (c < kk)
+                from = mid + 1u;
+            else
+                to = mid;
+        }
     }
-    return max((uint32_t)hi << 16, 1u) - 1u;
+    return max(at, 1u) - 1u;
 }
 
 // The kk smallest of the n listed keys (all <= K, distinct, n >= kk >= 1, S
@@ -951,34 +965,41 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(true, 4)) void band_match_
                     list_at(list, 0u, m) = key;
                 }
             } else {
-                // once through them: a list that gets full is brought down to
-                // its k smallest, and only smaller keys follow.  With more
-                // inside the band than the places held, every entry is tested
-                // and read again.
-                const bool held = n_surv <= (uint32_t)kBandCap;
-#pragma unroll 1
-                for (int t = 0; t < (held ? 1 : kTables); ++t) {
-                    const uint2 run = *reinterpret_cast<const uint2*>(qrow + 2 * t);
-                    const uint32_t b = uniform(run.x), n = held ? n_surv : uniform(run.y);
-#pragma unroll 1
-                    for (uint32_t i0 = 0; i0 < n; i0 += 64) {
-                        const uint32_t i = i0 + (uint32_t)lane;
-                        uint64_t live = __builtin_amdgcn_ballot_w64(i < n);
-                        uint32_t pos = b + i, t8 = 8u * (uint32_t)t;
-                        if (held) {
-                            const uint32_t e = i < n ? place[i] : 0u;
-                            pos = e & 0xFFFFFFu;
-                            t8 = e >> 24;
-                        } else {
-                            live &= __builtin_amdgcn_ballot_w64(in_band(kp_at(pos)));
-                        }
-                        if (n_pass > (uint32_t)kPassCap) shorten_list(list, n_pass, K, (uint32_t)prm.k, lane, hG);
+                auto add = [&](uint64_t ok, uint32_t key) {
+                    n_union += (uint32_t)__popcll(ok);
+                    const uint64_t m = ok & __builtin_amdgcn_ballot_w64(key <= K);
+                    if (__builtin_amdgcn_inverse_ballot_w64(m)) list_at(list, n_pass, m) = key;
+                    n_pass += (uint32_t)__popcll(m);
+                };
+                if (n_surv <= (uint32_t)kBandCap) {
+                    static_assert(kBandCap <= kListKeys, "the list holds them all");
+                    for (uint32_t base = 0; base < n_surv; base += 64) {
+                        const uint32_t i = base + (uint32_t)lane;
+                        const uint32_t e = i < n_surv ? place[i] : 0u;
                         uint32_t key;
-                        const uint64_t ok = entry(t8, pos, live, key);
-                        n_union += (uint32_t)__popcll(ok);
-                        const uint64_t m = ok & __builtin_amdgcn_ballot_w64(key <= K);
-                        if (__builtin_amdgcn_inverse_ballot_w64(m)) list_at(list, n_pass, m) = key;
-                        n_pass += (uint32_t)__popcll(m);
+                        const uint64_t ok = entry(e >> 24, e & 0xFFFFFFu, __builtin_amdgcn_ballot_w64(i < n_surv), key);
+                        add(ok, key);
+                    }
+                } else {
+                    // more inside the band than the places held: every entry
+                    // is tested and read again, once: a list that gets full is
+                    // brought down to its k smallest, and only smaller keys
+                    // follow
+#pragma unroll 1
+                    for (int t = 0; t < kTables; ++t) {
+                        const uint2 run = *reinterpret_cast<const uint2*>(qrow + 2 * t);
+                        const uint32_t b = uniform(run.x), n = uniform(run.y);
+#pragma unroll 1
+                        for (uint32_t i0 = 0; i0 < n; i0 += 64) {
+                            if (n_pass > (uint32_t)kListKeys - 64u)
+                                shorten_list(list, n_pass, K, (uint32_t)prm.k, lane, hG);
+                            const uint32_t pos = b + i0 + (uint32_t)lane;
+                            const uint64_t live = __builtin_amdgcn_ballot_w64(in_band(kp_at(pos))) &
+                                                  __builtin_amdgcn_ballot_w64(i0 + (uint32_t)lane < n);
+                            uint32_t key;
+                            const uint64_t ok = entry(8u * (uint32_t)t, pos, live, key);
+                            add(ok, key);
+                        }
                     }
                 }
                 if (n_pass > (uint32_t)kPassCap) shorten_list(list, n_pass, K, (uint32_t)prm.k, lane, hG);
