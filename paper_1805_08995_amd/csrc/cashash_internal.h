@@ -147,7 +147,7 @@ struct RowChunk {       // rows [r0, r0 + nr) of image img
 
 // Resident blocks per compute unit the matcher kernels are compiled for, and
 // their persistent launches use (LDS per block: 18.6 KB, 22.7 KB in the 8-slot
-// form, 21.6 KB in the band form; 8 blocks leave 64 registers, 7 leave 72).
+// form, 20.6 KB in the band form; 8 blocks leave 64 registers, 7 leave 72).
 // 60 x 8000 points: 4 blocks 5.8 ms, 6 4.9, 7 4.53, 8 4.40; 40 x 12000 (8
 // slots): 6 blocks 4.29 ms, 7 4.06.
 constexpr int match_blocks_per_cu(bool epi, int ns) { return epi || ns > 4 ? 7 : 8; }

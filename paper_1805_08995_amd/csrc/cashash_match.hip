@@ -146,6 +146,7 @@ struct Grab {
 __device__ __forceinline__ void finish_tile(int lane, int nq, int32_t q0, const uint8_t* __restrict__ qdesc,
                                             const uint8_t* __restrict__ tdesc, int64_t out, uint32_t kept,
                                             const uint16_t* sel, const Rare& rare) {
+    asm volatile("" : "+v"(lane));  // what follows from it is worked out here, not kept from tile to tile
     const int g = lane >> 2, part = lane & 3;
     const int R = (nq + 15) >> 4;
     const uint32_t part16 = (uint32_t)part << 4;
@@ -468,18 +469,19 @@ __device__ __forceinline__ void select_keys(const uint32_t* list, uint32_t n, ui
     }
 }
 
-// The list brought down to the kk smallest of its n > kk keys; K: the bound
-// that keys yet to come must be within.
+// The list brought down to the kk smallest of its n > kk keys (S registers per
+// lane); K: the bound that keys yet to come must be within.
+template <int S>
 __device__ __forceinline__ void shorten_list(uint32_t* list, uint32_t& n, uint32_t& K, uint32_t kk, int lane,
                                              int32_t& hG) {
-    uint32_t r[kListKeys / 64];
+    uint32_t r[S];
     wave_sync();
     read_list(r, list, n, lane);
     K = kth_bound(r, n, K, kk, hG);
     wave_sync();
     n = 0;
 #pragma unroll
-    for (int s = 0; s < kListKeys / 64; ++s) {
+    for (int s = 0; s < S; ++s) {
         const bool keep = r[s] <= K;
         const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
         if (keep) list_at(list, n, m) = r[s];
@@ -779,7 +781,7 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(false, NC)) void plain_mat
 // its length, then the epipolar line's three binary64 coefficients.
 constexpr int kBandWords = 12 + 6;
 // Places of the candidates inside the band held in LDS; more take the full scan.
-constexpr int kBandCap = 256;
+constexpr int kBandCap = kPassCap;  // (so they need no bound)
 
 // The band form: keypoints of all six runs first, the few candidates inside the
 // band (about 1%) read in full and kept, or ranked as in the plain form when
@@ -972,7 +974,6 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(true, 4)) void band_match_
                     n_pass += (uint32_t)__popcll(m);
                 };
                 if (n_surv <= (uint32_t)kBandCap) {
-                    static_assert(kBandCap <= kListKeys, "the list holds them all");
                     for (uint32_t base = 0; base < n_surv; base += 64) {
                         const uint32_t i = base + (uint32_t)lane;
                         const uint32_t e = i < n_surv ? place[i] : 0u;
@@ -991,18 +992,17 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(true, 4)) void band_match_
                         const uint32_t b = uniform(run.x), n = uniform(run.y);
 #pragma unroll 1
                         for (uint32_t i0 = 0; i0 < n; i0 += 64) {
-                            if (n_pass > (uint32_t)kListKeys - 64u)
-                                shorten_list(list, n_pass, K, (uint32_t)prm.k, lane, hG);
                             const uint32_t pos = b + i0 + (uint32_t)lane;
                             const uint64_t live = __builtin_amdgcn_ballot_w64(in_band(kp_at(pos))) &
                                                   __builtin_amdgcn_ballot_w64(i0 + (uint32_t)lane < n);
                             uint32_t key;
                             const uint64_t ok = entry(8u * (uint32_t)t, pos, live, key);
                             add(ok, key);
+                            if (n_pass > (uint32_t)kPassCap - 64u)
+                                shorten_list<kPassSlots>(list, n_pass, K, (uint32_t)prm.k, lane, hG);
                         }
                     }
                 }
-                if (n_pass > (uint32_t)kPassCap) shorten_list(list, n_pass, K, (uint32_t)prm.k, lane, hG);
             }
             wave_sync();
             t_union += n_union;
