@@ -560,34 +560,13 @@ __device__ __forceinline__ void run_starts(uint32_t (&P)[5], const uint32_t (&v)
     }
 }
 
-// Whether the number of keys that passed is right: at least k, or all, and no
-// more than the selection takes.
-__device__ __forceinline__ bool settled(uint32_t n_pass, uint32_t k, uint32_t K, uint32_t tauK) {
-    return n_pass >= k ? n_pass <= (uint32_t)kPassCap : K == tauK;
-}
-// The search for a threshold K that settles: by steps until both sides are
-// known, then by halves.  Keys are distinct, so one settles; move() returns
-// false when none is left, which only happens if the buffers change under the
-// kernel.
-struct Threshold {
-    int32_t klo = -1, khi = INT32_MAX;  // too few pass klo, too many khi
-    __device__ __forceinline__ bool move(uint32_t& K, uint32_t n_pass, uint32_t k, uint32_t tauK) {
-        if (n_pass < k) {
-            klo = (int32_t)K;
-            K = khi != INT32_MAX ? (uint32_t)(klo + ((khi - klo) >> 1)) : min(tauK, K + (6u << 16));
-        } else {
-            khi = (int32_t)K;
-            K = klo >= 0 || khi < (4 << 16) ? (uint32_t)(klo + ((khi - klo) >> 1)) : K - (4u << 16);
-        }
-        return khi - klo > 1;
-    }
-};
-
 // The plain form.  Per query: the six runs' candidates in 64-wide chunks, up to
 // four chunks' loads in flight together, the keys that pass the threshold to
-// the LDS list, then the selection.  A threshold that lets too few or too many
-// pass is moved and the runs are read again (a few queries in a thousand: the
-// list takes up to 192 keys, and the k-th distance varies by a few bits).  So no
+// the LDS list, then the selection.  A threshold that lets fewer than k pass is
+// raised and the runs are read again (once per query at most for the next 6
+// bits, then once without a threshold; a few queries in a thousand at k = 10,
+// a few in a hundred at k = 40 or 64); a list that gets full is brought down to its k
+// smallest keys on the way, so crowded distances cost no second reading.  So no
 // candidate is kept in a register past its chunk, the number of chunks has no
 // limit, and the ranking works on one register per lane instead of one per
 // chunk.  NC: chunks with start masks.
@@ -598,7 +577,10 @@ struct Threshold {
 // 0.72 of the pipes' rates, and 61 L2 lines, 26 of the 29 TB/s that a plain read
 // of such runs gets from L2 here.  Against that form: 100 x 8000 points 15.4 ->
 // 11.9 ms, 16 x 20000 3.65 -> 1.65 ms (half of its queries had more candidates
-// than its eight registers).
+// than its eight registers).  Crowded distances, 12 x 8000 points of which 250 /
+// 600 / 3000 are equal: 0.37 / 0.58 / 4.6 ms, of which the widest bucket runs are
+// most (with the threshold moved down by rereading 0.61 / 1.1 / 8.6; every
+// candidate in registers or a list 0.57 / 4.0 / 71).
 template <int NC>
 __global__ __launch_bounds__(256, match_blocks_per_cu(false, NC)) void plain_match_kernel(
     const ImgDev* __restrict__ imgs, const PairDev* __restrict__ pairs, const Item* __restrict__ items,
@@ -712,16 +694,22 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(false, NC)) void plain_mat
             } else if (total != 0u) {
                 SCAN(1, true, 0, noP);
             }
-            // Further chunks, two or one at a time while the list has room for
-            // all their candidates; and, when the number that passed is not
-            // right, all chunks again with another threshold
-            if (total > 256u || !settled(n_pass, (uint32_t)prm.k, K, tauK)) {
+            // Further chunks, two or one at a time as the list has room; a full
+            // list is brought down to its k smallest, and only smaller keys
+            // follow.  Fewer than k: all chunks again with a wider threshold,
+            // then with none but the limit.
+            if (total > 256u || n_pass > (uint32_t)kPassCap || (n_pass < (uint32_t)prm.k && K != tauK)) {
                 const int nch = (int)((total + 63u) >> 6);
-                Threshold th;
                 int u0 = 4;
+                bool again = false;
                 for (;;) {
 #pragma unroll 1
-                    while (u0 < nch && n_pass <= (uint32_t)kPassCap) {
+                    for (;;) {
+                        if (n_pass > (uint32_t)kPassCap) {
+                            shorten_list<kListKeys / 64>(list, n_pass, K, (uint32_t)prm.k, lane, hG);
+                            hK = min(tauK, max(hK, (5u << 16) | 0xFFFFu) - 0x10000u);
+                        }
+                        if (u0 >= nch) break;
                         const bool two = nch - u0 >= 2 && n_pass <= (uint32_t)kListKeys - 128u;
                         if (u0 + 2 <= NC) {
                             if (two)
@@ -738,12 +726,13 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(false, NC)) void plain_mat
                         }
                         u0 += two ? 2 : 1;
                     }
-                    if (settled(n_pass, (uint32_t)prm.k, K, tauK) || !th.move(K, n_pass, (uint32_t)prm.k, tauK)) break;
-                    hK = min(K | 0xFFFFu, tauK);
+                    if (n_pass >= (uint32_t)prm.k || K == tauK) break;
+                    K = again ? tauK : min(tauK, K + (6u << 16));
+                    if (!again) hK = K;
+                    again = true;
                     n_pass = n_union = 0;
                     u0 = 0;
                 }
-                n_pass = min(n_pass, (uint32_t)kPassCap);
             }
 #undef SCAN
             wave_sync();
@@ -755,7 +744,7 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(false, NC)) void plain_mat
                     select_64(list, hist, n_pass, K, kk, lane, sel, sel_n, hG);
                 } else {
                     select_keys<kPassSlots>(list, n_pass, K, kk, lane, sel, sel_n, hG);
-                    hK = min(tauK, max(hK, (5u << 16) | 0xFFFFu) - 0x10000u);
+                    if (n_pass > 2u * (uint32_t)prm.k) hK = min(tauK, max(hK, (5u << 16) | 0xFFFFu) - 0x10000u);
                 }
             }
             v_kept = lane == qi ? (sel_n - at) | (at << 16) : v_kept;
