@@ -515,8 +515,9 @@ static int follow_caller(cashash_ctx* c) {
 }
 
 // Uploads small tables on the compute stream (so they follow the kernels that
-// read the previous contents).  Two buffers alternate; a buffer's pinned
-// source is rewritten only after its previous copy has completed.
+// read the previous contents).  Two buffers alternate (the matcher starts each
+// call at the first); a buffer's pinned source is rewritten only after its
+// previous copy has completed.
 enum { kMetaCodes = 0, kMetaMatch = 1, kMetaGeo = 2 };
 
 static int upload_meta(cashash_ctx* c, Uploader& up, std::vector<const void*>& dptr, int area) {
@@ -527,8 +528,8 @@ static int upload_meta(cashash_ctx* c, Uploader& up, std::vector<const void*>& d
     std::vector<uint8_t>& last = c->meta_last[area][b];
     if (!(need <= dev.cap && c->meta_last_at[area][b] == dev.p && last.size() == need &&
           std::memcmp(last.data(), up.host.data(), need) == 0)) {
-        // the buffer does not hold these bytes already (a call on the same
-        // inputs two calls ago left them there: no copy then)
+        // the buffer does not hold these bytes already (an earlier call on the
+        // same buffers left them there: no copy then)
         HIPCHK(hipEventSynchronize(c->meta_ev[area][b]));
         HostPinned& host = c->meta_host[area][b];
         if (need > dev.cap) RETCHK(dev.ensure(std::max<size_t>({need, 2 * dev.cap, (size_t)1 << 20})));
@@ -565,7 +566,7 @@ struct CodeJob {
     std::vector<CodeOut> outs;
 };
 
-// Column sums over `imgs`, accumulated into c->dS (not cleared here).
+// The images' rows in chunks of up to `rows`.
 static void row_chunks(const std::vector<ImgDev>& imgs, int rows, std::vector<RowChunk>& v) {
     for (int m = 0; m < (int)imgs.size(); ++m)
         for (int r0 = 0; r0 < imgs[m].n; r0 += rows) v.push_back({m, r0, std::min(rows, imgs[m].n - r0), 0});
@@ -599,27 +600,18 @@ static int cached_chunks(cashash_ctx* c, const std::vector<ImgDev>& imgs) {
     return CASHASH_OK;
 }
 
-// Column sums of imgs into c->dS; dchunks: device chunks (cached_chunks), or
-// nullptr to build and upload them with the image table.
-// dI: the image table already on the device (with dchunks), or nullptr.
-static int run_colsum(cashash_ctx* c, const std::vector<ImgDev>& imgs, const RowChunk* dchunks = nullptr,
-                      int n_chunks = 0, const ImgDev* dI = nullptr) {
+// Column sums of imgs, added to the first set in c->dS.
+static int run_colsum(cashash_ctx* c, const std::vector<ImgDev>& imgs) {
     std::vector<RowChunk> chunks;
-    if (!dchunks) {
-        row_chunks(imgs, 2048, chunks);
-        n_chunks = (int)chunks.size();
-    }
-    if (n_chunks == 0) return CASHASH_OK;
-    if (!dI || !dchunks) {
-        Uploader up;
-        up.add(imgs);
-        if (!dchunks) up.add(chunks);
-        std::vector<const void*> d;
-        RETCHK(upload_meta(c, up, d, kMetaCodes));
-        dI = (const ImgDev*)d[0];
-        if (!dchunks) dchunks = (const RowChunk*)d[1];
-    }
-    HIPCHK(launch_colsum(c->stream, dI, dchunks, n_chunks, c->dS.as<unsigned long long>()));
+    row_chunks(imgs, 2048, chunks);
+    if (chunks.empty()) return CASHASH_OK;
+    Uploader up;
+    up.add(imgs);
+    up.add(chunks);
+    std::vector<const void*> d;
+    RETCHK(upload_meta(c, up, d, kMetaCodes));
+    HIPCHK(launch_colsum(c->stream, (const ImgDev*)d[0], (const RowChunk*)d[1], (int)chunks.size(),
+                         c->dS.as<unsigned long long>()));
     return CASHASH_OK;
 }
 
@@ -989,7 +981,7 @@ static uint32_t* job_ctl_host(cashash_ctx* c, int turn) {
 }
 
 // One caller-fixed device region that a match job carves its scratch out of
-// (bucket tables, uploaded tables, work items, counters, statistics) instead
+// (bucket tables, uploaded tables, work items, counters and statistics) instead
 // of the context's growable buffers: the allocation-free entry point.
 struct ScratchArea {
     uint8_t* base = nullptr;
@@ -1022,9 +1014,8 @@ constexpr int64_t kJoinPairs = 256;
 
 // Enqueues bucket tables and matcher launches for J on c->stream, plus the
 // read-back of the statistics into pinned memory; finish_match_job waits.
-// With a scratch area (sa) every device buffer of the job is taken from it,
-// the launch shape is the cached or default one (no tuning) and no graph is
-// captured, so nothing is allocated.
+// With a scratch area (sa) every device buffer of the job is taken from it and
+// no graph is captured, so nothing is allocated.
 static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullptr) {
     const int n_img = (int)J.imgs.size();
     const int64_t n_pairs = (int64_t)J.pair_q.size();
@@ -1148,7 +1139,7 @@ static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullp
             probe.used = sa->used;
             const size_t pieces[] = {std::max<size_t>(tbytes, 1), std::max<size_t>(up1_bytes, 1),
                                      std::max<size_t>(up2_bytes, 1), (size_t)max_items * sizeof(Item),
-                                     (size_t)kCtlWords * 4, 64};
+                                     (size_t)kCtlWords * 4};
             need = 0;
             for (size_t n : pieces) need = ((need + 255) & ~size_t(255)) + n;
             for (size_t n : pieces)

@@ -149,15 +149,6 @@ __device__ __forceinline__ uint32_t bf16_pair(uint32_t w, int sh) {
     return (__float_as_uint(f0) >> 16) | (__float_as_uint(f1) & 0xFFFF0000u);
 }
 
-__device__ __forceinline__ bf16x8 bytes_to_bf16x8(uint2 w) {
-    union {
-        uint4 u;
-        bf16x8 v;
-    } cv;
-    cv.u = make_uint4(bf16_pair(w.x, 0), bf16_pair(w.x, 16), bf16_pair(w.y, 0), bf16_pair(w.y, 16));
-    return cv.v;
-}
-
 __device__ __forceinline__ bf16x8 load_frag(const uint4* __restrict__ frag, int idx) {
     union {
         uint4 u;
