@@ -45,16 +45,16 @@ HBM_PEAK_GBS = 8000.0
 # SQ_INSTS_VALU.  Valid only for the matcher sources they were taken on
 # (sha256 over MATCHER_SOURCES, in order); null otherwise.
 MATCHER_SOURCES = ("cashash_match.hip", "cashash_device.h", "cashash_internal.h")
-MEASURED_COUNTERS = {"sources_sha256": "2be94965240baedd82cc3917b62477f9b4e1bd8b2b7cb110599e6ac482307cdf",
+MEASURED_COUNTERS = {"sources_sha256": "296edea5e601966402ce5724516e056143059a96c41204104d9a37d2426f736e",
                      "workload": "scenes_100x8000_exhaustive_4950pairs",
-                     "fetch_bytes": int(4612593.8 * 1024 * 2), "write_bytes": int(798009.6 * 1024),
-                     "valu_insts": 6241148131}
+                     "fetch_bytes": int(4382236.9 * 1024 * 2), "write_bytes": int(795824.4 * 1024),
+                     "valu_insts": 6051581425}
 # The same for one full band-kernel launch on the epipolar workload
 # (profiles/band_kernel_epipolar_500x12000.md).
-EPIPOLAR_COUNTERS = {"sources_sha256": "2be94965240baedd82cc3917b62477f9b4e1bd8b2b7cb110599e6ac482307cdf",
+EPIPOLAR_COUNTERS = {"sources_sha256": "296edea5e601966402ce5724516e056143059a96c41204104d9a37d2426f736e",
                      "workload": "epipolar_500x12000_15000pairs_band4px",
-                     "fetch_bytes": int(49839804.9 * 1024 * 2), "write_bytes": int(2131974.6 * 1024),
-                     "valu_insts": 29488336904}
+                     "fetch_bytes": int(49745397.2 * 1024 * 2), "write_bytes": int(2131975.6 * 1024),
+                     "valu_insts": 29516316264}
 # VALU issue limit: 256 CUs x 4 SIMDs, one wave64 VALU instruction per SIMD
 # every 4 cycles (16 lanes per cycle), 2.4 GHz: 614.4 G instructions/s
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4

@@ -280,7 +280,8 @@ __device__ __forceinline__ void store_code(const CodeOut& o, int row, const uint
 // 800k descriptors: 89 us (123 with R from L2 for each wavefront and the bits
 // unpacked in every lane), of which the products alone are 31 and the vector
 // instructions around them 41; leaving out loads or stores changes nothing.
-// 4000 descriptors: 10 us with the recompute (17.5 + 29 as four launches).
+// 4000 descriptors: 10 us with the recompute (17.5 + 29 as four launches; three
+// of its 256 registers are spilled, once per block).
 template <bool FUSED>
 __global__ __launch_bounds__(256, 2) void proj_mfma_kernel(const ImgDev* __restrict__ imgs,
                                                            const CodeOut* __restrict__ outs,

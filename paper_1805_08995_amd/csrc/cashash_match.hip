@@ -106,7 +106,7 @@ struct Rare {
 // whose train images stay in that XCD's L2, and moves to the other segments
 // when that one is exhausted.  A segment found exhausted is noted for the whole
 // block, so that at the end of a launch a counter is asked once per block and
-// not by each of up to 7168 wavefronts.
+// not by each of up to 8192 wavefronts.
 struct Grab {
     int32_t cur = 0, end = 0;
     // false: every segment is exhausted
@@ -243,7 +243,7 @@ __device__ __forceinline__ void finish_tile(int lane, int nq, int32_t q0, const 
 //   words 2o, 2o+1  : of the o-th non-empty run (table t), the byte offset that
 //                     takes candidate e's 16 e to its entry's code, 16 (t n +
 //                     b_t - start), and the query's keys as table t's entries
-//                     are compared with them (see loaded_dup)
+//                     are compared with them (see first_seen)
 //   words 12 ..     : per 64-candidate chunk u < NC the 64-bit mask of run
 //                     starts (bit j: a run other than the first starts at
 //                     candidate 64u + j + 1), so that a lane counts the starts
@@ -274,8 +274,7 @@ __device__ __forceinline__ uint64_t first_seen(uint2 kw, uint32_t qlo, uint32_t 
 // chunk's keys (Hamming << 16 | index) and whether the lane's candidate is a
 // valid one (inside the runs and not a repeat).  ORD: positions by the chunk
 // start masks (chunk u0 + c < NC); else by comparing with the run starts P.
-// Lanes past the last run read on from it, at most 63 entries past the last
-// table, which the caller's buffers allow, and are not valid.
+// Lanes past the last run neither load nor are valid.
 template <int C, bool ORD>
 struct Chunks {
     uint32_t key[C];
@@ -563,24 +562,28 @@ __device__ __forceinline__ void run_starts(uint32_t (&P)[5], const uint32_t (&v)
 // The plain form.  Per query: the six runs' candidates in 64-wide chunks, up to
 // four chunks' loads in flight together, the keys that pass the threshold to
 // the LDS list, then the selection.  A threshold that lets fewer than k pass is
-// raised and the runs are read again (once per query at most for the next 6
-// bits, then once without a threshold; a few queries in a thousand at k = 10,
-// a few in a hundred at k = 40 or 64); a list that gets full is brought down to its k
-// smallest keys on the way, so crowded distances cost no second reading.  So no
+// raised and the runs are read again (at most twice per query: six bits wider,
+// then without a threshold; none of 2000 queries among 8000 points at k = 10,
+// 3.5% at k = 40, 1.9% at k = 64); a list that gets full is brought down to its
+// k smallest keys on the way, so crowded distances cost no second reading.  So no
 // candidate is kept in a register past its chunk, the number of chunks has no
 // limit, and the ranking works on one register per lane instead of one per
 // chunk.  NC: chunks with start masks.
 //
-// What bounds it (100 x 8000 points, rocprofv3): issue.  Per query 157 VALU and
-// 132 SALU instructions (213 and 132 when every candidate was kept in registers,
-// ranked by an index table over all of them and compacted from them), 0.86 and
-// 0.72 of the pipes' rates, and 61 L2 lines, 26 of the 29 TB/s that a plain read
+// What bounds it (100 x 8000 points, rocprofv3): issue.  Per query 153 VALU and
+// 134 SALU instructions (213 and 132 when every candidate was kept in registers,
+// ranked by an index table over all of them and compacted from them), 0.83 and
+// 0.74 of the pipes' rates, and 61 L2 lines, 26 of the 29 TB/s that a plain read
 // of such runs gets from L2 here.  Against that form: 100 x 8000 points 15.4 ->
-// 11.9 ms, 16 x 20000 3.65 -> 1.65 ms (half of its queries had more candidates
-// than its eight registers).  Crowded distances, 12 x 8000 points of which 250 /
+// 11.8 ms, 16 x 20000 3.88 -> 1.77 ms per call (half of its queries had more
+// candidates than its eight registers).  Crowded distances, 12 x 8000 points of which 250 /
 // 600 / 3000 are equal: 0.37 / 0.58 / 4.6 ms, of which the widest bucket runs are
 // most (with the threshold moved down by rereading 0.61 / 1.1 / 8.6; every
 // candidate in registers or a list 0.57 / 4.0 / 71).
+// The 4-slot form's eight blocks leave 64 registers: the wavefront's count of
+// bucket entries lies in scratch, read and written once per tile (the launch
+// writes 0.34 GB more than its 0.48 GB of outputs; with seven blocks there is
+// no scratch and 60 x 8000 points take 3% longer, see match_blocks_per_cu).
 template <int NC>
 __global__ __launch_bounds__(256, match_blocks_per_cu(false, NC)) void plain_match_kernel(
     const ImgDev* __restrict__ imgs, const PairDev* __restrict__ pairs, const Item* __restrict__ items,
@@ -774,8 +777,10 @@ constexpr int kBandCap = kPassCap;  // (so they need no bound)
 
 // The band form: keypoints of all six runs first, the few candidates inside the
 // band (about 1%) read in full and kept, or ranked as in the plain form when
-// there are more than k.
-
+// there are more than k.  Bound by L1 accesses (164 per query, 0.91 of one per
+// cycle) and vector issue together: 500 x 12000 points in a band of 4 px 64 ms.
+// Wide bands, 20 x 12000 points: 150 px 1.39 ms, 400 px 2.14, all 2.29 (1.88,
+// 2.58 and 3.67 with the candidates in registers or a list of all of them).
 __global__ __launch_bounds__(256, match_blocks_per_cu(true, 4)) void band_match_kernel(const ImgDev* __restrict__ imgs,
                                                             const PairDev* __restrict__ pairs,
                                                             const Item* __restrict__ items, int32_t n_items,
