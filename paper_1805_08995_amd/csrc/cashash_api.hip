@@ -161,7 +161,7 @@ struct cashash_ctx {
     bool sum_clean[2] = {false, false};
     // uploaded tables (images, pairs, tiles ...): one double-buffered area for
     // the code builder and one for the matcher, so that the matcher's table
-    // addresses (baked into captured launches) do not move between calls
+    // addresses (baked into the graphs) do not move between calls
     DevBuf meta[3][2];
     HostPinned meta_host[3][2];
     hipEvent_t meta_ev[3][2] = {{nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
@@ -191,7 +191,7 @@ struct cashash_ctx {
     double last_ms = 0.0;
     int64_t last_launches = 0;
     DevBuf items;             // matcher work items of the current job
-    // captured persistent-matcher launches, keyed by their launch arguments
+    // graphs of persistent-matcher launches, keyed by their launch arguments
     struct GraphEntry {
         std::string key;
         hipGraphExec_t exec;
@@ -872,17 +872,12 @@ constexpr int64_t kDirectQueries = 8192;
 static int enqueue_matcher(cashash_ctx* c, const MatchPlan& P, MatchJob& J, Shape sh, bool batched,
                            const std::vector<int64_t>& first_of, int64_t n_pairs_run, int64_t n_items,
                            int64_t n_queries, int64_t* launches, bool use_graph) {
-    uint32_t* ctl = P.ctl;
     const Item* items = P.items;
+    const MatchLaunch plain{J.epi, 4, 0, P.dI, P.dP, items, 0, P.ctl, P.prm, J.o_idx, J.o_d1, J.o_d2};
     if (batched) {
         // one persistent launch per instantiation (pairs are ordered
         // small-train group first), each over its own item range
-        struct Launch {
-            int ns, grid;
-            int64_t item_lo, n;
-            MatchParams prm;
-        };
-        std::vector<Launch> ls;
+        std::vector<MatchLaunch> ls;
         int64_t oi = 0;
         while (oi < n_pairs_run) {
             const int ns = slots_for(J, P.order[oi]);
@@ -890,48 +885,34 @@ static int enqueue_matcher(cashash_ctx* c, const MatchPlan& P, MatchJob& J, Shap
             while (oe < n_pairs_run && slots_for(J, P.order[oe]) == ns) ++oe;
             const int64_t ilo = first_of[oi], ihi = std::min(first_of[oe], n_items);
             if (ihi > ilo) {
-                Launch L;
+                const int64_t n = ihi - ilo;
+                const int blocks_needed = (int)((n + kWavesPerBlock - 1) / kWavesPerBlock);
+                const int bpc = std::min(sh.bpc, match_blocks_per_cu(J.epi, ns));
+                MatchLaunch L = plain;
                 L.ns = ns;
-                L.item_lo = ilo;
-                L.n = ihi - ilo;
-                const int blocks_needed = (int)((L.n + kWavesPerBlock - 1) / kWavesPerBlock);
-                L.grid = std::max(1, std::min(blocks_needed, c->n_cu * std::min(sh.bpc, match_blocks_per_cu(J.epi, ns))));
-                L.prm = P.prm;
+                L.grid = std::max(1, std::min(blocks_needed, c->n_cu * bpc));
+                L.items = items + ilo;
+                L.n_items = (int32_t)n;
                 L.prm.set = (int32_t)ls.size();
                 // segments of about equal estimated cost (queries x train size), one per XCD
                 segment_bounds(J, P.order, first_of, sh.qt, oi, oe, ilo, ihi, L.prm.seg);
                 const int64_t waves = (int64_t)L.grid * kWavesPerBlock;
-                L.prm.grab = (int32_t)std::max<int64_t>(1, std::min<int64_t>(8, L.n / std::max<int64_t>(1, waves * 64)));
+                L.prm.grab = (int32_t)std::max<int64_t>(1, std::min<int64_t>(8, n / std::max<int64_t>(1, waves * 64)));
                 ls.push_back(L);
             }
             oi = oe;
         }
-        auto issue = [&]() -> hipError_t {
-            for (const Launch& L : ls) {
-                const hipError_t e = launch_match(c->stream, J.epi, L.ns, L.grid, P.dI, P.dP, items + L.item_lo,
-                                                  (int32_t)L.n, ctl, L.prm, J.o_idx, J.o_d1, J.o_d2);
-                if (e != hipSuccess) return e;
-            }
-            return hipSuccess;
-        };
         c->last_replayed = false;
         // (Events taken by the launch itself instead of recorded around it: 67.9 us
         // for 2 x 2000 points, direct 55.3.)
         if (use_graph && c->use_graphs && n_queries > kDirectQueries && !ls.empty()) {
-            // the persistent launches as one captured graph, replayed while
-            // the launch arguments are unchanged
+            // the persistent launches as one graph, replayed while the launch
+            // arguments are unchanged
             std::string key;
-            auto put = [&key](const void* v, size_t n) { key.append(static_cast<const char*>(v), n); };
-            const int epi = J.epi ? 1 : 0;
-            const void* ptrs[] = {P.dI, P.dP, items, ctl, J.o_idx, J.o_d1, J.o_d2};
-            put(&epi, sizeof epi);
-            put(ptrs, sizeof ptrs);
-            for (const Launch& L : ls) {
-                put(&L.ns, sizeof L.ns);
-                put(&L.grid, sizeof L.grid);
-                put(&L.item_lo, sizeof L.item_lo);
-                put(&L.n, sizeof L.n);
-                put(&L.prm, sizeof L.prm);
+            auto put = [&key](const auto& v) { key.append(reinterpret_cast<const char*>(&v), sizeof v); };
+            for (const MatchLaunch& L : ls) {
+                put(L.epi), put(L.ns), put(L.grid), put(L.imgs), put(L.pairs), put(L.items), put(L.n_items), put(L.ctl);
+                put(L.prm), put(L.o_idx), put(L.o_d1), put(L.o_d2);
             }
             hipGraphExec_t exec = nullptr;
             for (auto& g : c->graphs)
@@ -943,14 +924,16 @@ static int enqueue_matcher(cashash_ctx* c, const MatchPlan& P, MatchJob& J, Shap
                 }
             if (!exec) {
                 hipGraph_t graph = nullptr;
-                HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-                const hipError_t e1 = issue();
-                const hipError_t e2 = hipStreamEndCapture(c->stream, &graph);
-                HIPCHK(e1);
-                HIPCHK(e2);
-                const hipError_t e3 = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+                // made of nodes, not captured: what other threads do meanwhile (a
+                // synchronous copy) would end a capture with an error, and fail itself
+                HIPCHK(hipGraphCreate(&graph, 0));
+                hipError_t e = hipSuccess;
+                std::vector<hipGraphNode_t> nodes(ls.size());
+                for (size_t i = 0; i < ls.size() && e == hipSuccess; ++i)
+                    e = add_match_node(graph, &nodes[i], i ? &nodes[i - 1] : nullptr, ls[i]);
+                if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
                 hipGraphDestroy(graph);
-                HIPCHK(e3);
+                HIPCHK(e);
                 if (c->graphs.size() >= 4) {
                     auto old = std::min_element(c->graphs.begin(), c->graphs.end(),
                                                 [](const auto& a, const auto& b) { return a.used < b.used; });
@@ -961,16 +944,19 @@ static int enqueue_matcher(cashash_ctx* c, const MatchPlan& P, MatchJob& J, Shap
             }
             HIPCHK(hipGraphLaunch(exec, c->stream));
         } else {
-            HIPCHK(issue());
+            for (const MatchLaunch& L : ls) HIPCHK(launch_match(c->stream, L));
         }
         *launches += (int64_t)ls.size();
     } else {
         for (int64_t oi = 0; oi < n_pairs_run; ++oi) {
             const int64_t nit = first_of[oi + 1] - first_of[oi];
             if (nit == 0) continue;
-            HIPCHK(launch_match(c->stream, J.epi, slots_for(J, P.order[oi]),
-                                (int)((nit + kWavesPerBlock - 1) / kWavesPerBlock), P.dI, P.dP, items + first_of[oi],
-                                (int32_t)nit, ctl, P.prm, J.o_idx, J.o_d1, J.o_d2));
+            MatchLaunch L = plain;
+            L.ns = slots_for(J, P.order[oi]);
+            L.grid = (int)((nit + kWavesPerBlock - 1) / kWavesPerBlock);
+            L.items = items + first_of[oi];
+            L.n_items = (int32_t)nit;
+            HIPCHK(launch_match(c->stream, L));
             *launches += 1;
         }
     }
@@ -1018,7 +1004,7 @@ constexpr int64_t kJoinPairs = 256;
 // Enqueues bucket tables and matcher launches for J on c->stream, plus the
 // read-back of the statistics into pinned memory; finish_match_job waits.
 // With a scratch area (sa) every device buffer of the job is taken from it and
-// no graph is captured, so nothing is allocated.
+// no graph is made, so nothing is allocated.
 static int launch_match_job(cashash_ctx* c, MatchJob& J, ScratchArea* sa = nullptr) {
     const int n_img = (int)J.imgs.size();
     const int64_t n_pairs = (int64_t)J.pair_q.size();

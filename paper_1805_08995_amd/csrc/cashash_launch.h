@@ -30,9 +30,20 @@ hipError_t launch_make_items(hipStream_t s, const ItemArgs& a, const ImgDev* img
 // The bucket tables of the train images and, with items, the work items too.
 hipError_t launch_bucket(hipStream_t s, bool epi, const ImgDev* imgs, const TableOut* touts,
                          const int32_t* train_list, int n_train, const ItemArgs* items);
-hipError_t launch_match(hipStream_t s, bool epi, int ns, int grid, const ImgDev* imgs, const PairDev* pairs,
-                        const Item* items, int32_t n_items, uint32_t* ctl, const MatchParams& prm, int32_t* o_idx,
-                        int32_t* o_d1, int32_t* o_d2);
+// One matcher launch over items [0, n_items), or the same as a node of a graph.
+struct MatchLaunch {
+    bool epi;
+    int ns, grid;
+    const ImgDev* imgs;
+    const PairDev* pairs;
+    const Item* items;
+    int32_t n_items;
+    uint32_t* ctl;
+    MatchParams prm;
+    int32_t *o_idx, *o_d1, *o_d2;
+};
+hipError_t launch_match(hipStream_t s, const MatchLaunch& L);
+hipError_t add_match_node(hipGraph_t graph, hipGraphNode_t* node, const hipGraphNode_t* after, const MatchLaunch& L);
 }  // namespace cashash
 
 // Geometry-aware first stage (defined in cashash_geometry.hip).

@@ -13,6 +13,7 @@
 // launch (two when small and large train images meet) with per-XCD work
 // segments.
 #include "cashash_device.h"
+#include "cashash_launch.h"
 
 namespace cashash {
 
@@ -1024,18 +1025,28 @@ __global__ __launch_bounds__(256, match_blocks_per_cu(true, 4)) void band_match_
 }
 
 // ------------------------------------------------------------------ launcher
-hipError_t launch_match(hipStream_t s, bool epi, int ns, int grid, const ImgDev* imgs, const PairDev* pairs,
-                        const Item* items, int32_t n_items, uint32_t* ctl, const MatchParams& prm, int32_t* o_idx,
-                        int32_t* o_d1, int32_t* o_d2) {
-    if (n_items <= 0 || grid <= 0) return hipSuccess;
-    const dim3 g(grid), b(64 * kWavesPerBlock);
-    if (epi)
-        CH_LAUNCH(band_match_kernel, g, b, 0, s, imgs, pairs, items, n_items, ctl, prm, o_idx, o_d1, o_d2);
-    else if (ns > 4)
-        CH_LAUNCH(plain_match_kernel<8>, g, b, 0, s, imgs, pairs, items, n_items, ctl, prm, o_idx, o_d1, o_d2);
-    else
-        CH_LAUNCH(plain_match_kernel<4>, g, b, 0, s, imgs, pairs, items, n_items, ctl, prm, o_idx, o_d1, o_d2);
+using MatchKernel = void (*)(const ImgDev*, const PairDev*, const Item*, int32_t, uint32_t*, MatchParams, int32_t*,
+                             int32_t*, int32_t*);
+static MatchKernel match_kernel(bool epi, int ns) {
+    return epi ? band_match_kernel : ns > 4 ? plain_match_kernel<8> : plain_match_kernel<4>;
+}
+
+hipError_t launch_match(hipStream_t s, const MatchLaunch& L) {
+    if (L.n_items <= 0 || L.grid <= 0) return hipSuccess;
+    CH_LAUNCH(match_kernel(L.epi, L.ns), dim3((unsigned)L.grid), dim3(64 * kWavesPerBlock), 0, s, L.imgs, L.pairs,
+              L.items, L.n_items, L.ctl, L.prm, L.o_idx, L.o_d1, L.o_d2);
     return hipSuccess;
+}
+
+hipError_t add_match_node(hipGraph_t graph, hipGraphNode_t* node, const hipGraphNode_t* after, const MatchLaunch& L) {
+    MatchLaunch a = L;  // (the node copies the arguments)
+    void* args[] = {&a.imgs, &a.pairs, &a.items, &a.n_items, &a.ctl, &a.prm, &a.o_idx, &a.o_d1, &a.o_d2};
+    hipKernelNodeParams p{};
+    p.func = reinterpret_cast<void*>(match_kernel(L.epi, L.ns));
+    p.gridDim = dim3((unsigned)L.grid);
+    p.blockDim = dim3(64 * kWavesPerBlock);
+    p.kernelParams = args;
+    return hipGraphAddKernelNode(node, graph, after, after ? 1 : 0, &p);
 }
 
 }  // namespace cashash
