@@ -353,14 +353,17 @@ __device__ __forceinline__ bool null8(double (&A)[8][9], double (&f)[9]) {
 
 // The estimator runs as three kernels: the fit of the best hypothesis up to the
 // refit's normal matrix (a block per pair), the refit's eigenvector (27 lanes per
-// pair) and the inlier count of its matrix (a block per pair).  The 360 rotations of the 9 x 9 Jacobi are one long chain of
-// dependent divisions and square roots; in one kernel they kept a 256-thread
-// block of 253 registers waiting, two blocks per CU, and everything sequential in
-// match order ran in one thread: 667 us for 600 pairs of 400 matches (256
-// hypotheses each), now 161 + 154 + 4 us.  What is left is the binary64 work of
-// the hypotheses (19 thousand VALU instructions per wavefront of the fit; four
-// tests at a time or a third block per CU with its spills changed nothing) and
-// the rotations' chain.
+// pair) and the inlier count of its matrix (a block per pair).  The 360 rotations
+// of the 9 x 9 Jacobi are one long chain of dependent divisions and square roots;
+// in one kernel they kept a 256-thread block of 253 registers waiting, two blocks
+// per CU, and everything sequential in match order ran in one thread: 667 us for
+// 600 pairs of 400 matches (256 hypotheses each), now 161 + 154 + 4 us.  What is
+// left is the binary64 work of the hypotheses (19 thousand VALU instructions per
+// wavefront of the fit; four tests at a time or a third block per CU with its
+// spills changed nothing) and the rotations' chain.
+// The fit's design rows take 18 KB of LDS, so above about 3950 points per query
+// image one block fits a CU (the one kernel had two up to 4800): 600 pairs of 400
+// matches on images of 3800 / 4400 points 382 / 440 us per call, against 698 / 722.
 
 // Sequential sum of v over the first n lanes of consecutive 64-lane chunks,
 // s = ((s + v_0) + v_1) + .. : the lanes hold a chunk's values, the sum is
