@@ -48,7 +48,7 @@ def test_largest_tiles_decide_what_fits(k, largest):
     ref, _ = m.match_pairs(images, codes, keys, pairs, out=outs())
     for a, b in zip(got, ref):
         assert torch.equal(a, b)
-    # one point more than fits even so
+    # eight points more do not fit even so
     over = torch.cat([images[4], base[:8]])
     images[4] = over
     codes, keys, _ = m.build_codes(images)
